@@ -288,7 +288,7 @@ def main():
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": None,
             "kernel": "k_dslash (R_oo^-1 H_oe, 12 RHS, FP16 spinors, 12-parameter binary16 links, "
-                      "autotuned RHS tile)",
+                      "one block of 64 sites for all RHS)",
             "avg_launch_us": dslash_s * 1e6,
             "bytes_model": "achieved and frac: reference bytes, 144 B per site-RHS (FP32 links with 18 "
                            "parameters, FP16 spinors) x 12 RHS x V/2 = %.3f GB per launch; own_*: the "

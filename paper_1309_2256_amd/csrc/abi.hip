@@ -182,6 +182,9 @@ extern "C" int tm_create(tm_ctx **out, const tm_lattice *lat, int device)
     c->geo.vh = (int)(V / 2);
     c->geo.vsh = lat->L[0] * lat->L[1] * lat->L[2] / 2;
     c->geo.hs = half_stride(c->geo.vh);
+    c->geo.by_lxh = fast_div(c->geo.lxh);
+    c->geo.by_y = fast_div(lat->L[1]);
+    c->geo.by_z = fast_div(lat->L[2]);
     c->kappa = lat->kappa;
     c->eps = lat->two_kappa_mu;
     c->t_bc = lat->t_bc;

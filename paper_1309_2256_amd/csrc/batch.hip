@@ -26,8 +26,7 @@ struct tm_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<int> graph_set;  // instances captured in the current graph
-    int graph_iters = 0, graph_R = 0;
-    std::map<std::vector<int>, int> tuned_R;  // (prec, nrhs...) -> RHS per thread
+    int graph_iters = 0;
     PersistBatch pb;
     std::vector<int> pb_set;  // instances of the prepared persistent launch
     // launch form per (precision, nrhs...): 1 persistent kernel, 0 graph;
@@ -82,14 +81,14 @@ int bguard(tm_batch *b, F &&f)
     }
 }
 
-void prepare_stages(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int R)
+void prepare_stages(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int rpb)
 {
     std::vector<tm_ctx *> cs;
     for (int i : set) cs.push_back(S[i].c);
     for (int k = 0; k < 4; k++) {
         std::vector<DslashCall> dcs;
         for (int i : set) dcs.push_back(S[i].stage(k + 1));
-        multi_dslash_prepare(b->md[k], cs, dcs, R, b->stream);
+        multi_dslash_prepare(b->md[k], cs, dcs, rpb, b->stream);
     }
 }
 
@@ -112,56 +111,20 @@ void launch_iteration(tm_batch *b, std::vector<Solver> &S, const std::vector<int
     cg_tail_multi(t, S[set[0]].w.prec, S[set[0]].w.xprec, s);
 }
 
-// right-hand sides per Dslash thread for the batch: the fastest (timed on the
-// side-effect-free first stage) among the tiles that divide every nrhs
-int choose_R(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set)
+// right-hand sides per Dslash block for the batch (results do not depend on it)
+int choose_rpb(const std::vector<Solver> &S, const std::vector<int> &set)
 {
-    const int prec = S[set[0]].lp;
-    if (prec == TM_F64) return 1;
-    if (const char *e = getenv("TM_BATCH_RHS_TILE")) {  // fixed tile, if it divides every nrhs
-        const int R = atoi(e);
-        bool ok = R >= 1 && R <= 3;
-        for (int i : set) ok = ok && S[i].nrhs % R == 0;
-        if (ok) return R;
-    }
-    std::vector<int> key{prec};
-    for (int i : set) key.push_back(S[i].nrhs);
-    auto it = b->tuned_R.find(key);
-    if (it != b->tuned_R.end()) return it->second;
-    hipEvent_t e0, e1;
-    TM_HIP(hipEventCreate(&e0));
-    TM_HIP(hipEventCreate(&e1));
-    float best = 1e30f;
-    int bestR = 1;
-    for (int R : {1, 2, 3}) {
-        bool ok = true;
-        for (int i : set) ok &= S[i].nrhs % R == 0;
-        if (!ok) continue;
-        prepare_stages(b, S, set, R);
-        multi_dslash_launch(b->md[0], b->stream);
-        TM_HIP(hipEventRecord(e0, b->stream));
-        multi_dslash_launch(b->md[0], b->stream);
-        multi_dslash_launch(b->md[0], b->stream);
-        TM_HIP(hipEventRecord(e1, b->stream));
-        TM_HIP(hipEventSynchronize(e1));
-        float ms = 0;
-        TM_HIP(hipEventElapsedTime(&ms, e0, e1));
-        if (ms < best) {
-            best = ms;
-            bestR = R;
-        }
-    }
-    TM_HIP(hipEventDestroy(e0));
-    TM_HIP(hipEventDestroy(e1));
-    b->tuned_R[key] = bestR;
-    return bestR;
+    if (const char *e = getenv("TM_BATCH_RHS_TILE"))
+        if (atoi(e) > 0) return atoi(e);
+    std::vector<std::pair<tm_ctx *, int>> inst;
+    for (int i : set) inst.push_back({S[i].c, S[i].nrhs});
+    return multi_rhs_per_block(inst);
 }
 
 void build_graph(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int iters)
 {
     drop_graph(b);
-    const int R = b->single_launches ? 1 : choose_R(b, S, set);
-    if (!b->single_launches) prepare_stages(b, S, set, R);
+    if (!b->single_launches) prepare_stages(b, S, set, choose_rpb(S, set));
     TM_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     try {
         for (int k = 0; k < iters; k++) launch_iteration(b, S, set);
@@ -175,7 +138,6 @@ void build_graph(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &se
     TM_HIP(hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
     b->graph_set = set;
     b->graph_iters = iters;
-    b->graph_R = R;
 }
 
 // the persistent kernel runs the FP32-arithmetic solvers (FP32, FP16 or
@@ -199,7 +161,6 @@ std::vector<int> form_key(const std::vector<Solver> &S, const std::vector<int> &
 bool run_persist(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int K, bool timed)
 {
     if (b->pb_set != set) {
-        const int R = choose_R(b, S, set);
         std::vector<PersistInst> v;
         for (int i : set) {
             PersistInst q;
@@ -210,7 +171,7 @@ bool run_persist(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &se
             q.delta = S[i].delta;
             v.push_back(q);
         }
-        persist_prepare(b->pb, v, R, b->stream);
+        persist_prepare(b->pb, v, choose_rpb(S, set), b->stream);
         b->pb_set = set;
     }
     if (timed) TM_HIP(hipEventRecord(b->ev[0], b->stream));
@@ -266,7 +227,7 @@ void run_batch(tm_batch *b, std::vector<Solver> &S)
                 if (!ran) b->persist = 0;  // refused: the graph path from now on
             }
             if (!ran && b->eager) {
-                if (!b->single_launches) prepare_stages(b, S, set, choose_R(b, S, set));
+                if (!b->single_launches) prepare_stages(b, S, set, choose_rpb(S, set));
                 for (int k = 0; k < K; k++) launch_iteration(b, S, set);
             } else if (!ran) {
                 if (b->graph_set != set || b->graph_iters != K) build_graph(b, S, set, K);

@@ -58,8 +58,19 @@ __device__ __forceinline__ double block_sum(double v)
 // tree; result valid in thread 0
 __device__ __forceinline__ double sum_partials(const double *part, int nblk, int idx)
 {
+    const double *p = part + (size_t)idx * nblk;
     double acc = 0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) acc += ld_coh(part + (size_t)idx * nblk + b);
+    int b = threadIdx.x;
+    // eight loads in flight: one at a time, 64 of them (32^3 x 64) would each
+    // wait for the memory latency
+    for (; b + 7 * kThreads < nblk; b += 8 * kThreads) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = ld_coh(p + b + k * kThreads);
+#pragma unroll
+        for (int k = 0; k < 8; k++) acc += v[k];
+    }
+    for (; b < nblk; b += kThreads) acc += ld_coh(p + b);
     return block_sum(acc);
 }
 

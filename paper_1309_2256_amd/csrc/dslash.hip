@@ -1,19 +1,36 @@
 // Even-odd twisted-mass hopping kernel for gfx950.
 //
-// One thread per output half-site and R right-hand sides; each thread loads
-// each of its 8 links once and reuses it for its R spinors.  Per direction the
-// neighbour 4-spinor is projected to a 2-spinor with (1 -+ gamma_mu) (chiral
-// basis, appendix A.1 operator), multiplied by the colour link, and
-// reconstructed into the accumulator; the epilogue applies the spin-diagonal
-// local terms (twist R = 1 + i eps gamma5, its inverse, gamma5, -kappa) so that
-// the fused forms R^-1 H and R x - H y of the Schur operator (eq. A.2) cost no
-// extra memory pass.
+// A block of four waves takes 64 output half-sites and up to `rpb` right-hand
+// sides, one after the other.  Wave mu holds the two links of direction mu
+// (x + mu and x - mu) of its 64 sites in registers for all of them.  Per
+// right-hand side it loads the two neighbour spinors, projects each to a
+// 2-spinor with (1 -+ gamma_mu) (chiral basis, appendix A.1 operator),
+// multiplies by the colour link and leaves the result in LDS.  Three of the
+// waves then each sum one colour over the eight directions in fixed order,
+// rebuild the four spins and apply the spin-diagonal local terms (twist R =
+// 1 + i eps gamma5, its inverse, gamma5, -kappa), so that the fused forms
+// R^-1 H and R x - H y of the Schur operator (eq. A.2) cost no extra memory
+// pass.
+//
+// What bounds it, and why this split (32^3 x 64, 12 right-hand sides, R^-1 H,
+// against one thread per site walking the eight directions with 1-4
+// right-hand sides): the misses of the 4 MB L2 of each XCD.  A block is short
+// lived and its four directions' loads are in flight together, so the blocks
+// resident at a time cover a quarter of the sites and meet their neighbours'
+// spinors in the L2, and the links are loaded and rebuilt once for all
+// right-hand sides.  FP16: 533 -> 459 us, 2.26 -> 1.59 GB fetched past the L2;
+// FP64: 2449 -> 1780 us, 15.6 -> 10.2 GB (7.1 TB/s with the writes, what the
+// memory side cache gives); FP32 1285 -> 982, BF16 617 -> 544 us.  On small
+// lattices the serial chain of a thread is two directions and an LDS exchange
+// instead of eight directions: 16^3 x 32, one right-hand side, FP16 8.6 -> 7.1,
+// FP64 15.0 -> 14.2 us.
 //
 // Memory layout (all coalesced over the half-site index i):
 //   spinors  [rhs][spin*3 + colour][hs] (hs >= vh, the padded plane stride)
 //   links    [direction 0..7][row*3 + col][vh] for the output parity; the
 //            backward links are stored conjugated and the antiperiodic
 //            boundary phase is folded in, so the kernel has no branch on it.
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -21,12 +38,17 @@
 
 namespace {
 
-constexpr int kBlock = 256;
-// resident waves per SIMD requested from the compiler (bounds the registers
-// per lane to 512 / waves): one FP64 right-hand side fits in ~150 registers,
-// two in 256; one or two FP32-arithmetic right-hand sides fit in 128
-template <typename T, int R>
-constexpr int waves_for() { return sizeof(T) == 8 ? (R == 1 ? 3 : 2) : (R <= 2 ? 4 : R == 3 ? 3 : 2); }
+constexpr int kBlock = 256;  // four waves, one per direction mu
+constexpr int kSites = 64;   // output half-sites of a block
+// resident blocks per CU (and waves per SIMD) requested from the compiler:
+// bounded by the LDS exchange (24 KB per block in FP32, 48 KB in FP64, of
+// 160 KB) and by the registers (512 / waves per lane)
+template <typename SS, typename LS, typename T, bool ONE = false>
+constexpr int waves_for()
+{
+    if (sizeof(T) == 8) return ONE && !std::is_same<LS, L8D>::value ? 4 : 3;
+    return std::is_same<SS, h2>::value && !std::is_same<LS, float2>::value ? 5 : 4;
+}
 
 // 16-byte aligned so that an array of records keeps every complex field
 // naturally aligned
@@ -39,7 +61,8 @@ struct alignas(16) DParams {
     Geo g;
     int p;          // output parity
     int nrhs;
-    int ngroups;    // nrhs / R right-hand-side groups
+    int rpb;        // right-hand sides per block
+    int ngroups;    // right-hand-side groups, ceil(nrhs / rpb)
     cx<T> own_u, own_l, hop_u, hop_l;
     // +1, passed at run time so that the +-1 factors of the spin projection
     // stay FMAs (which take the FP16 inputs directly) instead of being folded
@@ -98,8 +121,9 @@ __device__ __forceinline__ cx<T> p_addi(rawc<L> u, rawc<L> l, T s)
     return {fma(-s, (T)l.i, (T)u.r), fma(s, (T)l.r, (T)u.i)};
 }
 
-// acc += (1 - S gamma_MU) (W (x) 1) psi  for S = +1 or -1 in the half-spinor
-// form: h = P psi (two spins), w = W h, the lower spins rebuilt from w.
+// Hop of one direction, (1 - S gamma_MU) (W (x) 1) psi for S = +1 or -1, in
+// the half-spinor form: h = P psi (two spins), w = W h, the lower spins
+// rebuilt from w (see rebuild).
 // gamma_k = [[0, -i s_k], [i s_k, 0]]:  h = u + S (i s_k) l,  lower = -S (i s_k) w
 // gamma_4 = [[0, 1], [1, 0]]:           h = u - S l,          lower = -S w
 // with i s_1 = [[0, i], [i, 0]], i s_2 = [[0, 1], [-1, 0]], i s_3 = [[i, 0], [0, -i]].
@@ -117,63 +141,62 @@ __device__ __forceinline__ void lmac(cx<T> &acc, rawc<_Float16> a, cx<T> b)
     acc.i = fma((T)a.i, b.r, acc.i);
 }
 
-template <int MU, int S, typename T, typename L, typename WT>
-__device__ __forceinline__ void hop_dir(cx<T> acc[12], const WT W[9], const rawc<L> psi[12], T one)
+// Component A (0 or 1) of the half-spinor takes u = spin A and l = spin
+// kLower<MU, A>.
+template <int MU, int A>
+constexpr int kLower = MU < 2 ? 3 - A : 2 + A;
+template <int MU, int S, int A, typename T, typename L, typename WT>
+__device__ __forceinline__ void half_hop_comp(cx<T> w[3], const WT W[9], const rawc<L> u[3], const rawc<L> l[3], T one)
 {
     const T s = (T)S * one;
-    cx<T> h0[3], h1[3];
+    cx<T> h[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
-        const rawc<L> u0 = psi[c], u1 = psi[3 + c], l0 = psi[6 + c], l1 = psi[9 + c];
-        if (MU == 0) {          // h0 = u0 + S i l1, h1 = u1 + S i l0
-            h0[c] = p_addi(u0, l1, s);
-            h1[c] = p_addi(u1, l0, s);
-        } else if (MU == 1) {   // h0 = u0 + S l1,   h1 = u1 - S l0
-            h0[c] = p_add(u0, l1, s);
-            h1[c] = p_add(u1, l0, -s);
-        } else if (MU == 2) {   // h0 = u0 + S i l0, h1 = u1 - S i l1
-            h0[c] = p_addi(u0, l0, s);
-            h1[c] = p_addi(u1, l1, -s);
-        } else {                // h0 = u0 - S l0,   h1 = u1 - S l1
-            h0[c] = p_add(u0, l0, -s);
-            h1[c] = p_add(u1, l1, -s);
-        }
+        if (MU == 0)        // h0 = u0 + S i l1, h1 = u1 + S i l0
+            h[c] = p_addi(u[c], l[c], s);
+        else if (MU == 1)   // h0 = u0 + S l1,   h1 = u1 - S l0
+            h[c] = p_add(u[c], l[c], A ? -s : s);
+        else if (MU == 2)   // h0 = u0 + S i l0, h1 = u1 - S i l1
+            h[c] = p_addi(u[c], l[c], A ? -s : s);
+        else                // h0 = u0 - S l0,   h1 = u1 - S l1
+            h[c] = p_add(u[c], l[c], -s);
     }
-    cx<T> w0[3], w1[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
-        cx<T> a = {0, 0}, b = {0, 0};
+        w[r] = {0, 0};
 #pragma unroll
-        for (int c = 0; c < 3; c++) {
-            lmac(a, W[3 * r + c], h0[c]);
-            lmac(b, W[3 * r + c], h1[c]);
-        }
-        w0[r] = a;
-        w1[r] = b;
+        for (int c = 0; c < 3; c++) lmac(w[r], W[3 * r + c], h[c]);
     }
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        acc[c].r += w0[c].r;
-        acc[c].i += w0[c].i;
-        acc[3 + c].r += w1[c].r;
-        acc[3 + c].i += w1[c].i;
-        cx<T> &l0 = acc[6 + c], &l1 = acc[9 + c];
-        // explicit FMAs: the rounding must not depend on what the compiler
-        // contracts in a given instantiation (results are bit-identical for
-        // every right-hand-side tile)
-        if (MU == 0) {          // lower = -S (i w1, i w0)
-            l0.r = fma(s, w1[c].i, l0.r); l0.i = fma(-s, w1[c].r, l0.i);
-            l1.r = fma(s, w0[c].i, l1.r); l1.i = fma(-s, w0[c].r, l1.i);
-        } else if (MU == 1) {   // lower = -S (w1, -w0)
-            l0.r = fma(-s, w1[c].r, l0.r); l0.i = fma(-s, w1[c].i, l0.i);
-            l1.r = fma(s, w0[c].r, l1.r); l1.i = fma(s, w0[c].i, l1.i);
-        } else if (MU == 2) {   // lower = -S (i w0, -i w1)
-            l0.r = fma(s, w0[c].i, l0.r); l0.i = fma(-s, w0[c].r, l0.i);
-            l1.r = fma(-s, w1[c].i, l1.r); l1.i = fma(s, w1[c].r, l1.i);
-        } else {                // lower = -S (w0, w1)
-            l0.r = fma(-s, w0[c].r, l0.r); l0.i = fma(-s, w0[c].i, l0.i);
-            l1.r = fma(-s, w1[c].r, l1.r); l1.i = fma(-s, w1[c].i, l1.i);
-        }
+}
+template <int MU, int S, typename T, typename L, typename WT>
+__device__ __forceinline__ void half_hop(cx<T> w0[3], cx<T> w1[3], const WT W[9], const rawc<L> psi[12], T one)
+{
+    half_hop_comp<MU, S, 0>(w0, W, psi, psi + 3 * kLower<MU, 0>, one);
+    half_hop_comp<MU, S, 1>(w1, W, psi + 3, psi + 3 * kLower<MU, 1>, one);
+}
+
+// acc[spin] += the four spins of one colour of a hop, from its half-spinor
+// (w0, w1).  The rounding is that of one add per component, whatever the
+// instantiation.
+template <int MU, int S, typename T>
+__device__ __forceinline__ void rebuild(cx<T> acc[4], cx<T> w0, cx<T> w1)
+{
+    acc[0] = acc[0] + w0;
+    acc[1] = acc[1] + w1;
+    auto add = [](cx<T> &a, bool plus, cx<T> w) { a = plus ? a + w : a - w; };
+    const cx<T> iw0 = times_i(w0), iw1 = times_i(w1);
+    if (MU == 0) {          // lower = -S (i w1, i w0)
+        add(acc[2], S < 0, iw1);
+        add(acc[3], S < 0, iw0);
+    } else if (MU == 1) {   // lower = -S (w1, -w0)
+        add(acc[2], S < 0, w1);
+        add(acc[3], S > 0, w0);
+    } else if (MU == 2) {   // lower = -S (i w0, -i w1)
+        add(acc[2], S < 0, iw0);
+        add(acc[3], S > 0, iw1);
+    } else {                // lower = -S (w0, w1)
+        add(acc[2], S < 0, w0);
+        add(acc[3], S < 0, w1);
     }
 }
 
@@ -182,6 +205,7 @@ __device__ __forceinline__ void hop_dir(cx<T> acc[12], const WT W[9], const rawc
 // lives in SGPRs, each lane supplies a 32-bit byte offset and the component
 // stride is a scalar offset, so a neighbour costs one VGPR of address state.
 using rsrc_t = __amdgpu_buffer_rsrc_t;
+typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
 // the builtins' own (GCC-style) vector types; values are moved in and out by
 // bit_cast to plain structs (element access on these vectors lowers to a
 // single-dword load with this compiler)
@@ -245,8 +269,12 @@ struct BufIO<double2> {
     template <typename T>
     __device__ __forceinline__ static void st(rsrc_t r, int voff, int soff, cx<T> c)
     {
+        // 16-byte stores take the whole offset in the VGPR: with an SGPR
+        // offset the compiler lets the next instruction overwrite the data
+        // registers, and the last lanes then stored the new value (seen on
+        // this chip; with a constant offset it keeps the needed wait state)
         D2 v{(double)c.r, (double)c.i};
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, voff, soff, kNT);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, voff + soff, 0, kNT);
     }
 };
 template <>
@@ -292,9 +320,8 @@ struct BufIO<h2> {
     template <typename T>
     __device__ __forceinline__ static void st(rsrc_t r, int voff, int soff, cx<T> c)
     {
-        h2 h;
-        h.x = (_Float16)(float)c.r;
-        h.y = (_Float16)(float)c.i;
+        // one packed conversion (v_cvt_pk_f16_f32, round to nearest even)
+        const hv2 h = {(_Float16)(float)c.r, (_Float16)(float)c.i};
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, h), r, voff, soff, kNT);
     }
 };
@@ -341,13 +368,6 @@ __device__ __forceinline__ void load_link(typename LinkEl<LS, T>::type W[9], rsr
         else
             W[k] = BufIO<LS>::template ldlink<T>(lr, voff, k * vbytes);
     }
-}
-
-template <typename SS>
-__device__ __forceinline__ void load_spinor(rawc<typename RawT<SS>::L> psi[12], rsrc_t sr, int vbytes, int voff)
-{
-#pragma unroll
-    for (int k = 0; k < 12; k++) psi[k] = BufIO<SS>::ldraw(sr, voff, k * vbytes);
 }
 
 // 12-parameter link (appendix A.1, link reconstruction): the first two rows in
@@ -440,7 +460,6 @@ __device__ __forceinline__ void load_link8(cx<T> W[9], rsrc_t lr, int vbytes, in
 // whose binary16 products are exact and whose sums are FP32.  Relative to
 // the FP32 projection this rounds h once to binary16 (the storage precision
 // of its inputs); all accumulation stays FP32.
-typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
 
 // h = u + SG l (I = false) or u + SG i l (I = true), as (conj h, swap h):
 // each one v_pk_add_f16 whose operand selection (op_sel: which half of each
@@ -472,17 +491,36 @@ __device__ __forceinline__ void proj2(hv2 u, hv2 l, hv2 &hc, hv2 &hs)
     }
 }
 
-// a.lo b.lo + a.hi b.hi (binary16 products, FP32 sum) with no accumulator
-// input: the first term of a chain, without a register cleared to zero
-__device__ __forceinline__ float dot2_first(hv2 a, hv2 b)
+// The four chains of one link row W (three entries) with both half-spinor
+// components: Re and Im of W h0 and of W h1, each three v_dot2_f32_f16 from
+// zero.  One block of assembly, since the compiler starts a chain by clearing
+// a register (a tenth of the kernel's instructions) and since no instruction
+// but another dot of the same kind (as its addend) may read the result of a
+// dot for three wait states: the compiler keeps that distance only between
+// instructions that it knows, so the block ends with the wait.
+__device__ __forceinline__ void row_dots(float &ar, float &ai, float &br, float &bi, const hv2 *W, const hv2 *c0,
+                                         const hv2 *s0, const hv2 *c1, const hv2 *s1)
 {
-    float d;
-    asm("v_dot2_f32_f16 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(b));
-    return d;
+    asm("v_dot2_f32_f16 %0, %4, %7, 0\n\t"
+        "v_dot2_f32_f16 %1, %4, %10, 0\n\t"
+        "v_dot2_f32_f16 %2, %4, %13, 0\n\t"
+        "v_dot2_f32_f16 %3, %4, %16, 0\n\t"
+        "v_dot2_f32_f16 %0, %5, %8, %0\n\t"
+        "v_dot2_f32_f16 %1, %5, %11, %1\n\t"
+        "v_dot2_f32_f16 %2, %5, %14, %2\n\t"
+        "v_dot2_f32_f16 %3, %5, %17, %3\n\t"
+        "v_dot2_f32_f16 %0, %6, %9, %0\n\t"
+        "v_dot2_f32_f16 %1, %6, %12, %1\n\t"
+        "v_dot2_f32_f16 %2, %6, %15, %2\n\t"
+        "v_dot2_f32_f16 %3, %6, %18, %3\n\t"
+        "s_nop 2"
+        : "=&v"(ar), "=&v"(ai), "=&v"(br), "=&v"(bi)
+        : "v"(W[0]), "v"(W[1]), "v"(W[2]), "v"(c0[0]), "v"(c0[1]), "v"(c0[2]), "v"(s0[0]), "v"(s0[1]), "v"(s0[2]),
+          "v"(c1[0]), "v"(c1[1]), "v"(c1[2]), "v"(s1[0]), "v"(s1[1]), "v"(s1[2]));
 }
 
 template <int MU, int S>
-__device__ __forceinline__ void hop_dir_h(cx<float> acc[12], const hv2 W[9], const hv2 psi[12])
+__device__ __forceinline__ void half_hop(cx<float> w0[3], cx<float> w1[3], const hv2 W[9], const hv2 psi[12], float)
 {
     hv2 c0[3], s0[3], c1[3], s1[3];
 #pragma unroll
@@ -502,43 +540,9 @@ __device__ __forceinline__ void hop_dir_h(cx<float> acc[12], const hv2 W[9], con
             proj2<false, -S>(u1, l1, c1[c], s1[c]);
         }
     }
-    cx<float> w0[3], w1[3];
 #pragma unroll
-    for (int r = 0; r < 3; r++) {
-        float ar = dot2_first(W[3 * r], c0[0]), ai = dot2_first(W[3 * r], s0[0]);
-        float br = dot2_first(W[3 * r], c1[0]), bi = dot2_first(W[3 * r], s1[0]);
-#pragma unroll
-        for (int c = 1; c < 3; c++) {
-            ar = __builtin_amdgcn_fdot2(W[3 * r + c], c0[c], ar, false);
-            ai = __builtin_amdgcn_fdot2(W[3 * r + c], s0[c], ai, false);
-            br = __builtin_amdgcn_fdot2(W[3 * r + c], c1[c], br, false);
-            bi = __builtin_amdgcn_fdot2(W[3 * r + c], s1[c], bi, false);
-        }
-        w0[r] = {ar, ai};
-        w1[r] = {br, bi};
-    }
-    constexpr float s = (float)S;
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        acc[c].r += w0[c].r;
-        acc[c].i += w0[c].i;
-        acc[3 + c].r += w1[c].r;
-        acc[3 + c].i += w1[c].i;
-        cx<float> &l0 = acc[6 + c], &l1 = acc[9 + c];
-        if (MU == 0) {          // lower = -S (i w1, i w0)
-            l0.r += s * w1[c].i; l0.i -= s * w1[c].r;
-            l1.r += s * w0[c].i; l1.i -= s * w0[c].r;
-        } else if (MU == 1) {   // lower = -S (w1, -w0)
-            l0.r -= s * w1[c].r; l0.i -= s * w1[c].i;
-            l1.r += s * w0[c].r; l1.i += s * w0[c].i;
-        } else if (MU == 2) {   // lower = -S (i w0, -i w1)
-            l0.r += s * w0[c].i; l0.i -= s * w0[c].r;
-            l1.r -= s * w1[c].i; l1.i += s * w1[c].r;
-        } else {                // lower = -S (w0, w1)
-            l0.r -= s * w0[c].r; l0.i -= s * w0[c].i;
-            l1.r -= s * w1[c].r; l1.i -= s * w1[c].i;
-        }
-    }
+    for (int r = 0; r < 3; r++)
+        row_dots(w0[r].r, w0[r].i, w1[r].r, w1[r].i, W + 3 * r, c0, s0, c1, s1);
 }
 
 __device__ __forceinline__ hv2 ld_hv2(rsrc_t r, int voff, int soff)
@@ -562,8 +566,8 @@ __device__ __forceinline__ void load_link_h(hv2 W[9], rsrc_t lr, int vbytes, int
         // conj(a b - c d): Re(a b) = dot2(a, conj b), Im(a b) = dot2(a, swap b)
         auto cr = [](hv2 a, hv2 b, hv2 c, hv2 d) {
             const hv2 nc = -c;
-            const float re = __builtin_amdgcn_fdot2(nc, hv2{d.x, -d.y}, dot2_first(a, hv2{b.x, -b.y}), false);
-            const float im = __builtin_amdgcn_fdot2(nc, hv2{d.y, d.x}, dot2_first(a, hv2{b.y, b.x}), false);
+            const float re = __builtin_amdgcn_fdot2(nc, hv2{d.x, -d.y}, __builtin_amdgcn_fdot2(a, hv2{b.x, -b.y}, 0.f, false), false);
+            const float im = __builtin_amdgcn_fdot2(nc, hv2{d.y, d.x}, __builtin_amdgcn_fdot2(a, hv2{b.y, b.x}, 0.f, false), false);
             return hv2{(_Float16)re, (_Float16)(-im)};
         };
         W[6] = cr(W[1], W[5], W[2], W[4]);
@@ -577,56 +581,62 @@ __device__ __forceinline__ void load_link_h(hv2 W[9], rsrc_t lr, int vbytes, int
     }
 }
 
-template <int MU, int S, typename SS, typename LS, typename T, int R>
-__device__ __forceinline__ void do_dir(cx<T> acc[R][12], const DParams<T> &a, const rsrc_t *sr, int dir, int j,
-                                       int i, int t)
+// how an instantiation holds links and spinors: FP16 spinors with binary16
+// links in the packed form, everything else as components
+template <typename SS, typename LS, typename T>
+struct Held {
+    static constexpr bool packed =
+        std::is_same<SS, h2>::value && (std::is_same<LS, L12>::value || std::is_same<LS, h2>::value);
+    using Link = std::conditional_t<packed, hv2, typename LinkEl<LS, T>::type>;
+    using Spinor = std::conditional_t<packed, hv2, rawc<typename RawT<SS>::L>>;
+};
+
+// the link of direction dir (uniform) at half-site i; cross: the link crosses
+// the time boundary
+template <typename SS, typename LS, typename T>
+__device__ __forceinline__ void load_dir_link(typename Held<SS, LS, T>::Link W[9], const DParams<T> &a, int dir, int i,
+                                              bool cross)
 {
-    if constexpr (std::is_same<SS, h2>::value && (std::is_same<LS, L12>::value || std::is_same<LS, h2>::value)) {
-        constexpr bool REC = std::is_same<LS, L12>::value;
-        constexpr int NP = REC ? 6 : 9;
-        const h2 *lbase = (const h2 *)a.links + (size_t)dir * NP * a.g.vh;
-        const rsrc_t lr = make_rsrc(lbase, (size_t)NP * a.g.vh * sizeof(h2));
-        const bool bnd = MU == 3 && (dir < 4 ? t == a.g.L[3] - 1 : t == 0);
-        hv2 W[9];
-        load_link_h<REC>(W, lr, a.g.vh * (int)sizeof(h2), i * (int)sizeof(h2), bnd, (float)a.t_bc);
+    constexpr bool rec = std::is_same<LS, L12>::value || std::is_same<LS, L12D>::value || std::is_same<LS, L12F>::value;
+    constexpr int np = std::is_same<LS, L8D>::value ? 4 : rec ? 6 : 9;
+    using RS = std::conditional_t<std::is_same<LS, L12>::value, h2,
+                                  std::conditional_t<std::is_same<LS, L12D>::value || std::is_same<LS, L8D>::value,
+                                                     double2, std::conditional_t<std::is_same<LS, L12F>::value, float2, LS>>>;
+    const RS *base = (const RS *)a.links + (size_t)dir * np * a.g.vh;
+    const rsrc_t lr = make_rsrc(base, (size_t)np * a.g.vh * sizeof(RS));
+    const int vb = a.g.vh * (int)sizeof(RS), vo = i * (int)sizeof(RS);
+    if constexpr (Held<SS, LS, T>::packed)
+        load_link_h<rec>(W, lr, vb, vo, cross, (float)a.t_bc);
+    else if constexpr (std::is_same<LS, L8D>::value)
+        load_link8<T>(W, lr, vb, vo, cross, (T)a.t_bc);
+    else if constexpr (rec)
+        load_link12<RS, T>(W, lr, vb, vo, cross, (T)a.t_bc);
+    else
+        load_link<LS, T>(W, lr, vb, vo);
+}
+
+template <typename SS, typename LS, typename T>
+__device__ __forceinline__ void load_dir_spinor(typename Held<SS, LS, T>::Spinor psi[12], rsrc_t sr, int vb, int vo)
+{
 #pragma unroll
-        for (int rr = 0; rr < R; rr++) {
-            hv2 psi[12];
+    for (int k = 0; k < 12; k++) {
+        if constexpr (Held<SS, LS, T>::packed)
+            psi[k] = ld_hv2(sr, vo, k * vb);
+        else
+            psi[k] = BufIO<SS>::ldraw(sr, vo, k * vb);
+    }
+}
+
+// the spinor components that half-spinor component A of a hop along MU takes:
+// spin A, then spin kLower<MU, A>
+template <typename SS, int MU, int A, typename L>
+__device__ __forceinline__ void load_half_spinor(rawc<L> p[6], rsrc_t sr, int vb, int vo)
+{
 #pragma unroll
-            for (int k = 0; k < 12; k++) psi[k] = ld_hv2(sr[rr], j * (int)sizeof(h2), k * a.g.hs * (int)sizeof(h2));
-            hop_dir_h<MU, S>(reinterpret_cast<cx<float> *>(acc[rr]), W, psi);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        return;
+    for (int c = 0; c < 3; c++) {
+        p[c] = BufIO<SS>::ldraw(sr, vo, (3 * A + c) * vb);
+        p[3 + c] = BufIO<SS>::ldraw(sr, vo, (3 * kLower<MU, A> + c) * vb);
     }
-    typename LinkEl<LS, T>::type W[9];
-    if constexpr (std::is_same<LS, L8D>::value) {
-        const double2 *lbase = (const double2 *)a.links + (size_t)dir * 4 * a.g.vh;
-        const rsrc_t lr = make_rsrc(lbase, (size_t)4 * a.g.vh * sizeof(double2));
-        const bool bnd = MU == 3 && (dir < 4 ? t == a.g.L[3] - 1 : t == 0);
-        load_link8<T>(W, lr, a.g.vh * (int)sizeof(double2), i * (int)sizeof(double2), bnd, (T)a.t_bc);
-    } else if constexpr (std::is_same<LS, L12>::value || std::is_same<LS, L12D>::value ||
-                         std::is_same<LS, L12F>::value) {
-        using RS = std::conditional_t<std::is_same<LS, L12>::value, h2,
-                                      std::conditional_t<std::is_same<LS, L12D>::value, double2, float2>>;
-        const RS *lbase = (const RS *)a.links + (size_t)dir * 6 * a.g.vh;
-        const rsrc_t lr = make_rsrc(lbase, (size_t)6 * a.g.vh * sizeof(RS));
-        const bool bnd = MU == 3 && (dir < 4 ? t == a.g.L[3] - 1 : t == 0);
-        load_link12<RS, T>(W, lr, a.g.vh * (int)sizeof(RS), i * (int)sizeof(RS), bnd, (T)a.t_bc);
-    } else {
-        const LS *lbase = (const LS *)a.links + (size_t)dir * 9 * a.g.vh;
-        const rsrc_t lr = make_rsrc(lbase, (size_t)9 * a.g.vh * sizeof(LS));
-        load_link<LS, T>(W, lr, a.g.vh * (int)sizeof(LS), i * (int)sizeof(LS));
-    }
-#pragma unroll
-    for (int rr = 0; rr < R; rr++) {
-        rawc<typename RawT<SS>::L> psi[12];
-        load_spinor<SS>(psi, sr[rr], a.g.hs * (int)sizeof(SS), j * (int)sizeof(SS));
-        hop_dir<MU, S>(acc[rr], W, psi, a.one);
-    }
-    // keep the loads of one direction from being hoisted above the previous
-    // direction's arithmetic: bounds the live registers to one direction
-    __builtin_amdgcn_sched_barrier(0);
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -666,141 +676,297 @@ __device__ __forceinline__ double norm2c(cx<T> v)
 //              rho = null: r only (the solver follows |rho|^2 by recurrence)
 enum { EPI_STORE = 0, EPI_NORM = 1, EPI_CG = 2 };
 
-// Block order: see map_block.
-// One block of the launch: bhw is the block's index within its instance's
-// range of nhw blocks (that range starts at a multiple of 8, so bhw % 8 is
-// still the XCD).
-template <typename SS, typename LS, typename T, int R, int DAG, int OWN, int EPI>
-__device__ __forceinline__ void dslash_block(const DParams<T> &a, int bhw, int nhw)
+// The half-spinors (w0, w1) of a right-hand side on their way from the wave
+// of their direction to the wave of their colour.  KEEP: wave mu < 3, which
+// sums colour mu itself, keeps that colour of its own two directions in
+// registers, and 18 of the 24 (direction, colour) pairs go through LDS: four
+// FP64 blocks fit a CU then instead of three.
+template <typename T, bool KEEP>
+struct Exchange {
+    static constexpr int slots = KEEP ? 18 : 24;
+    // first slot of a direction; colour c of direction dir is first(dir) + c,
+    // without the kept colour
+    static constexpr int first(int dir)
+    {
+        const int mu = dir & 3, half = dir >> 2;
+        return !KEEP ? 3 * dir : mu < 3 ? 4 * mu + 2 * half : 12 + 3 * half;
+    }
+    // (w0, w1): one 16-byte access in FP32, one each in FP64
+    alignas(16) cx<T> w[sizeof(T) == 4 ? 1 : 2][slots][kSites][sizeof(T) == 4 ? 2 : 1];
+    double norm[2][3][kSites];  // [quantity][colour][site]
+};
+template <int DIR, int A, bool KEEP>
+__device__ __forceinline__ void put_comp(Exchange<double, KEEP> &x, int lane, const cx<double> w[3], cx<double> &kept)
 {
-    int grp;
-    const int sblk = map_block(bhw, nhw, a.ngroups, a.nb_t, grp);
-    const int r0 = grp * R;
-    const int i_raw = sblk * kBlock + threadIdx.x;
-    const bool valid = i_raw < a.g.vh;
-    if (EPI == EPI_STORE && !valid) return;
-    const int i = valid ? i_raw : a.g.vh - 1;  // idle lanes join the block reduction
-    const size_t fbytes = (size_t)12 * a.g.hs * sizeof(SS);  // one right-hand side
-    rsrc_t sr[R];
 #pragma unroll
-    for (int rr = 0; rr < R; rr++) sr[rr] = make_rsrc((const char *)a.in + (r0 + rr) * fbytes, fbytes);
-
-    int x, y, z, t;
-    eo_coords(a.g, a.p, i, x, y, z, t);
-
-    cx<T> acc[R][12];
-#pragma unroll
-    for (int rr = 0; rr < R; rr++)
-#pragma unroll
-        for (int k = 0; k < 12; k++) acc[rr][k] = {0, 0};
-
-    // forward hops use (1 - gamma) for H and (1 + gamma) for H^dag
-    constexpr int SF = DAG ? -1 : 1;
-    constexpr int SB = -SF;
-    // One direction per iteration; the loop is kept rolled so that the loads
-    // of a direction are consumed before the next direction's are issued
-    // (the switch is uniform across the wavefront).
-#pragma unroll 1
-    for (int d = 0; d < 8; d++) {
-        const int mu = d & 3, step = d < 4 ? 1 : -1;
-        int c[4] = {x, y, z, t};
-        c[mu] += step;
-        if (c[mu] == a.g.L[mu]) c[mu] = 0;
-        if (c[mu] < 0) c[mu] = a.g.L[mu] - 1;
-        const int j = eo_index(a.g, c[0], c[1], c[2], c[3]);
-        switch (d) {
-        case 0: do_dir<0, SF, SS, LS, T, R>(acc, a, sr, 0, j, i, t); break;
-        case 1: do_dir<1, SF, SS, LS, T, R>(acc, a, sr, 1, j, i, t); break;
-        case 2: do_dir<2, SF, SS, LS, T, R>(acc, a, sr, 2, j, i, t); break;
-        case 3: do_dir<3, SF, SS, LS, T, R>(acc, a, sr, 3, j, i, t); break;
-        case 4: do_dir<0, SB, SS, LS, T, R>(acc, a, sr, 4, j, i, t); break;
-        case 5: do_dir<1, SB, SS, LS, T, R>(acc, a, sr, 5, j, i, t); break;
-        case 6: do_dir<2, SB, SS, LS, T, R>(acc, a, sr, 6, j, i, t); break;
-        default: do_dir<3, SB, SS, LS, T, R>(acc, a, sr, 7, j, i, t); break;
-        }
+    for (int c = 0, n = 0; c < 3; c++) {
+        if (KEEP && c == (DIR & 3))
+            kept = w[c];
+        else
+            *(double2 *)x.w[A][x.first(DIR) + n++][lane] = make_double2(w[c].r, w[c].i);
     }
-
-    const int vb = a.g.hs * (int)sizeof(SS), vo = i * (int)sizeof(SS);
-    constexpr int NQ = EPI == EPI_CG ? 2 : 1;
-    double nrm[R][NQ];
+}
+template <int DIR, bool KEEP>
+__device__ __forceinline__ void put_half(Exchange<float, KEEP> &x, int lane, const cx<float> w0[3], const cx<float> w1[3],
+                                         cx<float> kept[2])
+{
 #pragma unroll
-    for (int rr = 0; rr < R; rr++) {
-        const rsrc_t outr = make_rsrc((char *)a.out + (r0 + rr) * fbytes, fbytes);
-        const rsrc_t ownr = make_rsrc((const char *)a.own + (r0 + rr) * fbytes, fbytes);
-        const rsrc_t rr_r = make_rsrc((char *)a.r + (r0 + rr) * fbytes, fbytes);
-        const rsrc_t rho_r = make_rsrc((char *)a.rho + (r0 + rr) * fbytes, fbytes);
-        T alpha = 0;
-        if constexpr (EPI == EPI_CG) alpha = (T)cgdev::ld_coh(&a.sc[r0 + rr].alpha);
-#pragma unroll
-        for (int q = 0; q < NQ; q++) nrm[rr][q] = 0;
-        // all loads of this right-hand side first, then arithmetic and
-        // stores: the stores may alias the loaded fields as far as the
-        // compiler knows, so interleaving them would serialise the loads
-        cx<T> o[12], rl[12];
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            o[k] = {0, 0};
-            if (OWN) o[k] = BufIO<SS>::template ld<T>(ownr, vo, k * vb);
-            if constexpr (EPI == EPI_CG) rl[k] = BufIO<SS>::template ld<T>(rr_r, vo, k * vb);
-        }
-        const bool track_rho = EPI == EPI_CG && a.rho != nullptr;  // uniform
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            cx<T> v = (k < 6 ? a.hop_u : a.hop_l) * acc[rr][k];
-            if (OWN) v = v + (k < 6 ? a.own_u : a.own_l) * o[k];
-            if constexpr (EPI == EPI_CG) {
-                const cx<T> rv = rl[k] - alpha * v;
-                if (valid) {
-                    BufIO<SS>::template st<T>(rr_r, vo, k * vb, rv);
-                    nrm[rr][0] += norm2c(stored<SS>(rv));
-                }
-            } else {
-                if (valid) {
-                    BufIO<SS>::template st<T>(outr, vo, k * vb, v);
-                    if constexpr (EPI == EPI_NORM) nrm[rr][0] += norm2c(stored<SS>(v));
-                }
-            }
-        }
-        if (track_rho) {
-            cx<T> hl[12];
-#pragma unroll
-            for (int k = 0; k < 12; k++) hl[k] = BufIO<SS>::template ld<T>(rho_r, vo, k * vb);
-#pragma unroll
-            for (int k = 0; k < 12; k++) {
-                const cx<T> hv = hl[k] - alpha * o[k];
-                if (valid) {
-                    BufIO<SS>::template st<T>(rho_r, vo, k * vb, hv);
-                    nrm[rr][1] += norm2c(stored<SS>(hv));
-                }
-            }
-        }
+    for (int c = 0, n = 0; c < 3; c++) {
+        if (KEEP && c == (DIR & 3))
+            kept[0] = w0[c], kept[1] = w1[c];
+        else
+            *(float4 *)x.w[0][x.first(DIR) + n++][lane] = make_float4(w0[c].r, w0[c].i, w1[c].r, w1[c].i);
     }
-    if constexpr (EPI != EPI_STORE) {
-        // deterministic block reduction: wave shuffles, then the 4 waves in order
-        __shared__ double red[kBlock / 64][R * NQ];
-        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-        for (int rr = 0; rr < R; rr++)
-#pragma unroll
-            for (int q = 0; q < NQ; q++) {
-                double v = wave_sum(nrm[rr][q]);
-                if (lane == 0) red[w][rr * NQ + q] = v;
-            }
-        __syncthreads();
-        if (threadIdx.x < R * NQ) {
-            const int rr = threadIdx.x / NQ, q = threadIdx.x % NQ;
-            double s = 0;
-#pragma unroll
-            for (int k = 0; k < kBlock / 64; k++) s += red[k][threadIdx.x];
-            cgdev::st_coh(a.part + ((size_t)q * a.nrhs + r0 + rr) * a.nblk + sblk, s);
-        }
+}
+// acc += colour c of direction DIR (kept: that of this wave's own directions)
+template <int DIR, int S, typename T, bool KEEP>
+__device__ __forceinline__ void add_half(cx<T> acc[4], const Exchange<T, KEEP> &x, const cx<T> kept[2][2], int c, int lane)
+{
+    constexpr int mu = DIR & 3;
+    if (KEEP && mu < 3 && c == mu) {  // uniform
+        rebuild<mu, S>(acc, kept[DIR >> 2][0], kept[DIR >> 2][1]);
+        return;
+    }
+    const int slot = x.first(DIR) + (KEEP && mu < 3 && c > mu ? c - 1 : c);
+    if constexpr (sizeof(T) == 4) {
+        const float4 v = *(const float4 *)x.w[0][slot][lane];
+        rebuild<mu, S>(acc, cx<T>{v.x, v.y}, cx<T>{v.z, v.w});
+    } else {
+        const double2 v0 = *(const double2 *)x.w[0][slot][lane], v1 = *(const double2 *)x.w[1][slot][lane];
+        rebuild<mu, S>(acc, cx<T>{v0.x, v0.y}, cx<T>{v1.x, v1.y});
     }
 }
 
-template <typename SS, typename LS, typename T, int R, int DAG, int OWN, int EPI>
-__global__ __launch_bounds__(kBlock, (waves_for<T, R>())) void k_dslash(DParams<T> a)
+// one per block, whatever forms a kernel calls (the persistent kernel runs four)
+template <typename T, bool KEEP>
+__device__ __forceinline__ Exchange<T, KEEP> &exchange()
 {
-    dslash_block<SS, LS, T, R, DAG, OWN, EPI>(a, blockIdx.x, gridDim.x);
+    __shared__ Exchange<T, KEEP> x;
+    return x;
+}
+
+// workgroup barrier that orders LDS accesses only: loads from memory stay in
+// flight across it (__syncthreads would wait for them)
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The two hops of wave MU for one right-hand side (field sr) into the
+// exchange; vf / vk: byte offsets of its lanes' neighbours at +-MU.  The links
+// come from flink and blink (a call each, so that one right-hand side need not
+// hold both).
+template <typename SS, typename LS, typename T, int MU, int SF, bool ONE, typename LF, typename LB>
+__device__ __forceinline__ void wave_hops(Exchange<T, ONE> &ex, cx<T> kept[2][2], rsrc_t sr, int vb, int vf, int vk,
+                                          int lane, LF &&flink, LB &&blink, T one)
+{
+    constexpr int SB = -SF;
+    if constexpr (sizeof(T) == 8) {
+        // a quarter of the two hops' input at a time, the next quarter's
+        // loads issued before the arithmetic of the previous one: the two
+        // links take 72 registers, a whole spinor 48
+        cx<T> w[3];
+        rawc<T> p0[6], p1[6];
+        load_half_spinor<SS, MU, 0>(p0, sr, vb, vf);
+        load_half_spinor<SS, MU, 1>(p1, sr, vb, vf);
+        {
+            const auto *W = flink();
+            half_hop_comp<MU, SF, 0>(w, W, p0, p0 + 3, one);
+            put_comp<MU, 0>(ex, lane, w, kept[0][0]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_half_spinor<SS, MU, 0>(p0, sr, vb, vk);
+            half_hop_comp<MU, SF, 1>(w, W, p1, p1 + 3, one);
+            put_comp<MU, 1>(ex, lane, w, kept[0][1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        load_half_spinor<SS, MU, 1>(p1, sr, vb, vk);
+        const auto *W = blink();
+        half_hop_comp<MU, SB, 0>(w, W, p0, p0 + 3, one);
+        put_comp<4 + MU, 0>(ex, lane, w, kept[1][0]);
+        __builtin_amdgcn_sched_barrier(0);
+        half_hop_comp<MU, SB, 1>(w, W, p1, p1 + 3, one);
+        put_comp<4 + MU, 1>(ex, lane, w, kept[1][1]);
+    } else {
+        typename Held<SS, LS, T>::Spinor pf[12], pb[12];
+        load_dir_spinor<SS, LS, T>(pf, sr, vb, vf);
+        load_dir_spinor<SS, LS, T>(pb, sr, vb, vk);
+        const auto *Wf = flink();
+        const auto *Wb = blink();
+        cx<T> w0[3], w1[3];
+        half_hop<MU, SF>(w0, w1, Wf, pf, one);
+        put_half<MU>(ex, lane, w0, w1, kept[0]);
+        half_hop<MU, SB>(w0, w1, Wb, pb, one);
+        put_half<4 + MU>(ex, lane, w0, w1, kept[1]);
+    }
+}
+
+// One block of the launch: bhw is the block's index within its instance's
+// range of nhw blocks (that range starts at a multiple of 8, so bhw % 8 is
+// still the XCD).  Block order: see map_block.  ONE: a single right-hand side
+// per block, so that the links need not be kept past its hops.
+template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI, bool ONE = false>
+__device__ __forceinline__ void dslash_block(const DParams<T> &a, int bhw, int nhw)
+{
+    Exchange<T, ONE> &ex = exchange<T, ONE>();
+    int grp;
+    const int sblk = map_block(bhw, nhw, a.ngroups, a.nb_t, grp);
+    const int r0 = grp * a.rpb, r1 = min(r0 + a.rpb, a.nrhs);
+    const int lane = threadIdx.x & 63;
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i_raw = sblk * kSites + lane;
+    const bool valid = i_raw < a.g.vh;
+    const int i = valid ? i_raw : a.g.vh - 1;  // idle lanes take part in the barriers
+    int x, y, z, t;
+    eo_coords(a.g, a.p, i, x, y, z, t);
+    // neighbours by the row strides; a wrap is one compare and select
+    const int sy = a.g.lxh, sz = sy * a.g.L[1], st = a.g.vsh;
+    int jf, jb;
+    if (mu == 0) {
+        const int xh = x >> 1;
+        jf = x & 1 ? (xh == sy - 1 ? i - (sy - 1) : i + 1) : i;
+        jb = x & 1 ? i : (xh == 0 ? i + (sy - 1) : i - 1);
+    } else if (mu == 1) {
+        jf = y == a.g.L[1] - 1 ? i - (sz - sy) : i + sy;
+        jb = y == 0 ? i + (sz - sy) : i - sy;
+    } else if (mu == 2) {
+        jf = z == a.g.L[2] - 1 ? i - (st - sz) : i + sz;
+        jb = z == 0 ? i + (st - sz) : i - sz;
+    } else {
+        jf = t == a.g.L[3] - 1 ? i - (a.g.vh - st) : i + st;
+        jb = t == 0 ? i + (a.g.vh - st) : i - st;
+    }
+    // the links of this wave: held for all right-hand sides, or (ONE) loaded
+    // where they are used
+    using Link = typename Held<SS, LS, T>::Link;
+    const bool cf = mu == 3 && t == a.g.L[3] - 1, cb = mu == 3 && t == 0;
+    Link Wf[9], Wb[9];
+    auto flink = [&]() -> const Link * {
+        if constexpr (ONE) load_dir_link<SS, LS, T>(Wf, a, mu, i, cf);
+        return Wf;
+    };
+    auto blink = [&]() -> const Link * {
+        if constexpr (ONE) load_dir_link<SS, LS, T>(Wb, a, 4 + mu, i, cb);
+        return Wb;
+    };
+    if constexpr (!ONE) {
+        load_dir_link<SS, LS, T>(Wf, a, mu, i, cf);
+        load_dir_link<SS, LS, T>(Wb, a, 4 + mu, i, cb);
+    }
+
+    // forward hops use (1 - gamma) for H and (1 + gamma) for H^dag
+    constexpr int SF = DAG ? -1 : 1, SB = -SF;
+    constexpr int NQ = EPI == EPI_CG ? 2 : 1;
+    const size_t fbytes = (size_t)12 * a.g.hs * sizeof(SS);  // one right-hand side
+    const int vb = a.g.hs * (int)sizeof(SS), vo = i * (int)sizeof(SS);
+    const int vf = jf * (int)sizeof(SS), vk = jb * (int)sizeof(SS);
+    const bool track_rho = EPI == EPI_CG && a.rho != nullptr;  // uniform
+    auto field = [&](const void *base, int r) { return make_rsrc((const char *)base + r * fbytes, fbytes); };
+#pragma unroll 1
+    for (int r = r0; r < r1; r++) {
+        const rsrc_t sr = field(a.in, r);
+        cx<T> kept[2][2];
+        if (mu == 0)
+            wave_hops<SS, LS, T, 0, SF, ONE>(ex, kept, sr, vb, vf, vk, lane, flink, blink, a.one);
+        else if (mu == 1)
+            wave_hops<SS, LS, T, 1, SF, ONE>(ex, kept, sr, vb, vf, vk, lane, flink, blink, a.one);
+        else if (mu == 2)
+            wave_hops<SS, LS, T, 2, SF, ONE>(ex, kept, sr, vb, vf, vk, lane, flink, blink, a.one);
+        else
+            wave_hops<SS, LS, T, 3, SF, ONE>(ex, kept, sr, vb, vf, vk, lane, flink, blink, a.one);
+        // the fields of the own site: ahead of the barrier when the links are
+        // no longer needed, else after the sum (registers)
+        const int c = mu;  // the colour that this wave sums
+        const rsrc_t rr_r = field(a.r, r), rho_r = field(a.rho, r);
+        cx<T> o[4], rl[4];
+        auto load_own = [&]() {
+#pragma unroll
+            for (int sp = 0; sp < 4; sp++) {
+                const int so = (3 * sp + c) * vb;
+                if (OWN) o[sp] = BufIO<SS>::template ld<T>(field(a.own, r), vo, so);
+                if constexpr (EPI == EPI_CG) rl[sp] = BufIO<SS>::template ld<T>(rr_r, vo, so);
+            }
+        };
+        if constexpr (ONE)
+            if (mu < 3) load_own();
+        lds_barrier();
+        if (mu < 3) {
+            // all loads first, then arithmetic and stores: the stores may
+            // alias the loaded fields as far as the compiler knows
+            cx<T> acc[4];
+#pragma unroll
+            for (int sp = 0; sp < 4; sp++) acc[sp] = {0, 0};
+            if constexpr (!ONE && sizeof(T) == 4) load_own();
+            add_half<0, SF>(acc, ex, kept, c, lane);
+            add_half<1, SF>(acc, ex, kept, c, lane);
+            add_half<2, SF>(acc, ex, kept, c, lane);
+            add_half<3, SF>(acc, ex, kept, c, lane);
+            add_half<4, SB>(acc, ex, kept, c, lane);
+            add_half<5, SB>(acc, ex, kept, c, lane);
+            add_half<6, SB>(acc, ex, kept, c, lane);
+            add_half<7, SB>(acc, ex, kept, c, lane);
+            if constexpr (!ONE && sizeof(T) == 8) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_own();
+            }
+            T alpha = 0;
+            if constexpr (EPI == EPI_CG) alpha = (T)cgdev::ld_coh(&a.sc[r].alpha);
+            double nrm[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; q++) nrm[q] = 0;
+#pragma unroll
+            for (int sp = 0; sp < 4; sp++) {
+                const int so = (3 * sp + c) * vb;
+                cx<T> v = (sp < 2 ? a.hop_u : a.hop_l) * acc[sp];
+                if (OWN) v = v + (sp < 2 ? a.own_u : a.own_l) * o[sp];
+                if constexpr (EPI == EPI_CG) {
+                    const cx<T> rv = rl[sp] - alpha * v;
+                    if (valid) BufIO<SS>::template st<T>(rr_r, vo, so, rv);
+                    nrm[0] += norm2c(stored<SS>(rv));
+                } else {
+                    if (valid) BufIO<SS>::template st<T>(field(a.out, r), vo, so, v);
+                    if constexpr (EPI == EPI_NORM) nrm[0] += norm2c(stored<SS>(v));
+                }
+            }
+            if (track_rho) {
+                cx<T> hl[4];
+#pragma unroll
+                for (int sp = 0; sp < 4; sp++) hl[sp] = BufIO<SS>::template ld<T>(rho_r, vo, (3 * sp + c) * vb);
+#pragma unroll
+                for (int sp = 0; sp < 4; sp++) {
+                    const cx<T> hv = hl[sp] - alpha * o[sp];
+                    if (valid) BufIO<SS>::template st<T>(rho_r, vo, (3 * sp + c) * vb, hv);
+                    nrm[NQ - 1] += norm2c(stored<SS>(hv));
+                }
+            }
+            if constexpr (EPI != EPI_STORE) {
+#pragma unroll
+                for (int q = 0; q < NQ; q++) ex.norm[q][c][lane] = valid ? nrm[q] : 0.0;
+            }
+        }
+        if constexpr (!ONE || EPI != EPI_STORE) lds_barrier();
+        if constexpr (EPI != EPI_STORE) {
+            // the wave without a colour sums the block's norms (fixed order)
+            // while the others go on; they reach ex.norm again only past the
+            // next barrier
+            if (mu == 3) {
+#pragma unroll
+                for (int q = 0; q < NQ; q++) {
+                    if (q == 1 && !track_rho) break;
+                    const double s = wave_sum(ex.norm[q][0][lane] + ex.norm[q][1][lane] + ex.norm[q][2][lane]);
+                    if (lane == 0) cgdev::st_coh(a.part + ((size_t)q * a.nrhs + r) * a.nblk + sblk, s);
+                }
+            }
+        }
+        if constexpr (ONE) break;
+    }
+}
+
+template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI, bool ONE>
+__global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T, ONE>())) void k_dslash(DParams<T> a)
+{
+    dslash_block<SS, LS, T, DAG, OWN, EPI, ONE>(a, blockIdx.x, gridDim.x);
 }
 
 // Several lattices in one launch: instance i owns hardware blocks
@@ -816,15 +982,15 @@ struct MultiArgs {
 };
 static_assert(sizeof(MultiArgs<double>) <= 4096, "kernel arguments exceed 4 KiB");
 
-template <typename SS, typename LS, typename T, int R, int DAG, int OWN, int EPI>
-__global__ __launch_bounds__(kBlock, (waves_for<T, R>())) void k_dslash_multi(const MultiArgs<T> m)
+template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
+__global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T>())) void k_dslash_multi(const MultiArgs<T> m)
 {
     int i = 0;
     while (i + 1 < m.n && (int)blockIdx.x >= m.start[i + 1]) i++;
     const int local = (int)blockIdx.x - m.start[i];
     const int nreal = m.p[i].nblk * m.p[i].ngroups;
     if (local >= nreal) return;
-    dslash_block<SS, LS, T, R, DAG, OWN, EPI>(m.p[i], local, nreal);
+    dslash_block<SS, LS, T, DAG, OWN, EPI>(m.p[i], local, nreal);
 }
 
 // ---------------------------------------------------------------- persistent batch
@@ -928,7 +1094,7 @@ __device__ __forceinline__ bool grid_sync(unsigned *bar, unsigned long long spin
 }
 
 // One Dslash stage over the virtual blocks of all instances; stage index k.
-template <typename SS, typename LS, typename T, int R, int DAG, int OWN, int EPI>
+template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
 __device__ __forceinline__ void persist_stage(const PersistArgs<T> &a, int k)
 {
     const int total = a.start[a.n];
@@ -939,9 +1105,7 @@ __device__ __forceinline__ void persist_stage(const PersistArgs<T> &a, int k)
         const int local = vb - a.start[i];
         const int nreal = p.nblk * p.ngroups;
         if (local >= nreal) continue;
-        dslash_block<SS, LS, T, R, DAG, OWN, EPI>(p, local, nreal);
-        // the block reduction of the next virtual block reuses the LDS
-        if constexpr (EPI != EPI_STORE) __syncthreads();
+        dslash_block<SS, LS, T, DAG, OWN, EPI>(p, local, nreal);
     }
 }
 
@@ -983,21 +1147,21 @@ __device__ __forceinline__ void persist_update(const PersistArgs<T> &a)
     }
 }
 
-template <typename SS, typename LS, typename T, int R>
-__global__ __launch_bounds__(kBlock, (waves_for<T, R>())) void k_batch_persist(const PersistArgs<T> *__restrict__ pa,
+template <typename SS, typename LS, typename T>
+__global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T>())) void k_batch_persist(const PersistArgs<T> *__restrict__ pa,
                                                                              int iters,
                                                                              unsigned long long spin_limit)
 {
     const PersistArgs<T> &a = *pa;
     for (int it = 0; it < iters; it++) {
-        persist_stage<SS, LS, T, R, 0, 0, EPI_STORE>(a, 0);  // t = R_oo^-1 H_oe p
+        persist_stage<SS, LS, T, 0, 0, EPI_STORE>(a, 0);  // t = R_oo^-1 H_oe p
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, R, 0, 1, EPI_NORM>(a, 1);   // q = R_ee p - H_eo t, |q|^2 partials
+        persist_stage<SS, LS, T, 0, 1, EPI_NORM>(a, 1);   // q = R_ee p - H_eo t, |q|^2 partials
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, R, 1, 0, EPI_STORE>(a, 2);  // t = R_oo^-1 H_oe^dag q
+        persist_stage<SS, LS, T, 1, 0, EPI_STORE>(a, 2);  // t = R_oo^-1 H_oe^dag q
         persist_scalars<T, false>(a);                       // alpha
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, R, 0, 1, EPI_CG>(a, 3);     // r -= alpha Ahat^dag q, partials
+        persist_stage<SS, LS, T, 0, 1, EPI_CG>(a, 3);     // r -= alpha Ahat^dag q, partials
         if (!grid_sync(a.bar, spin_limit)) return;
         persist_scalars<T, true>(a);                        // beta, flags
         if (!grid_sync(a.bar, spin_limit)) return;
@@ -1012,24 +1176,73 @@ cx<T> cvt(cx<double> v)
     return cx<T>{(T)v.r, (T)v.i};
 }
 
-template <typename SS, typename LS, typename T, int R, int DAG, int OWN>
-void launch_epi(const DslashCall &dc, dim3 grid, hipStream_t s, const DParams<T> &a)
+// The fused epilogues belong to the second halves of the Schur operator
+// (dag = 0 with the own-site term); the other forms store only.
+template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
+void launch_form(dim3 grid, hipStream_t s, const DParams<T> &a)
 {
-    switch (dc.epi) {
-    case EPI_NORM: hipLaunchKernelGGL((k_dslash<SS, LS, T, R, DAG, OWN, EPI_NORM>), grid, dim3(kBlock), 0, s, a); break;
-    case EPI_CG:
-        if constexpr (OWN == 1)
-            hipLaunchKernelGGL((k_dslash<SS, LS, T, R, DAG, OWN, EPI_CG>), grid, dim3(kBlock), 0, s, a);
-        else
-            throw TmError{TM_ERR_ARG, "fused CG epilogue needs the own-site term"};
-        break;
-    default: hipLaunchKernelGGL((k_dslash<SS, LS, T, R, DAG, OWN, EPI_STORE>), grid, dim3(kBlock), 0, s, a);
-    }
+    if (a.rpb == 1)
+        hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, true>), grid, dim3(kBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, false>), grid, dim3(kBlock), 0, s, a);
 }
 
-template <typename SS, typename LS, typename T, int R>
-DParams<T> fill_params(tm_ctx *c, const DslashCall &dc)
+template <typename SS, typename LS, typename T, int DAG, int OWN>
+void launch_epi(const DslashCall &dc, dim3 grid, hipStream_t s, const DParams<T> &a)
 {
+    if constexpr (DAG == 0 && OWN == 1) {
+        if (dc.epi == EPI_NORM) return launch_form<SS, LS, T, DAG, OWN, EPI_NORM>(grid, s, a);
+        if (dc.epi == EPI_CG) return launch_form<SS, LS, T, DAG, OWN, EPI_CG>(grid, s, a);
+    }
+    TM_REQUIRE(dc.epi == EPI_STORE, "fused epilogues need dag = 0 and the own-site term");
+    launch_form<SS, LS, T, DAG, OWN, EPI_STORE>(grid, s, a);
+}
+
+// Right-hand sides per block (at most), for instances given as (site blocks,
+// nrhs) and `slots` resident blocks: every instance splits its right-hand
+// sides evenly over the fewest blocks that keep the limit.  More of them per
+// block share one load and one rebuild of the links and keep the resident
+// blocks on fewer sites, so that neighbouring blocks find each other's spinors
+// in the L2; fewer fill the chip on small lattices.  The limit taken has the
+// least (rounds of resident blocks) x (mean block length), a block's start and
+// its links counting as one right-hand side.  TM_DSLASH_RHS_TILE /
+// TM_BATCH_RHS_TILE in the environment fix it (results are bit-identical for
+// any).
+int even_split(int nrhs, int most)
+{
+    const int groups = (nrhs + most - 1) / most;
+    return (nrhs + groups - 1) / groups;
+}
+int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots)
+{
+    int top = 1, best = 1;
+    for (const auto &[nb, nrhs] : inst) top = std::max(top, nrhs);
+    double least = 0;
+    for (int lim = 1; lim <= top; lim++) {
+        double blocks = 0, length = 0;
+        int longest = 0;
+        for (const auto &[nb, nrhs] : inst) {
+            const int rpb = even_split(nrhs, lim), g = (nrhs + rpb - 1) / rpb;
+            blocks += (double)nb * g;
+            length += (double)nb * (g + nrhs);
+            longest = std::max(longest, 1 + rpb);
+        }
+        const double cost = std::max((double)longest, std::ceil(blocks / slots) * length / blocks);
+        if (lim == 1 || cost < least) {
+            least = cost;
+            best = lim;
+        }
+    }
+    return best;
+}
+
+template <typename SS, typename LS, typename T>
+constexpr long slots_of() { return 256 * waves_for<SS, LS, T>(); }
+
+template <typename SS, typename LS, typename T>
+DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
+{
+    const int rpb = even_split(dc.nrhs, most);
     DParams<T> a;
     a.out = dc.out;
     a.in = dc.in;
@@ -1044,7 +1257,8 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc)
     a.g = c->geo;
     a.p = dc.out_parity;
     a.nrhs = dc.nrhs;
-    a.ngroups = dc.nrhs / R;
+    a.rpb = rpb;
+    a.ngroups = (dc.nrhs + rpb - 1) / rpb;
     a.own_u = cvt<T>(dc.d_own.u);
     a.own_l = cvt<T>(dc.d_own.l);
     a.hop_u = cvt<T>(dc.d_hop.u);
@@ -1055,143 +1269,37 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc)
     a.sc = dc.sc;
     a.part = dc.part;
     a.nblk = dslash_site_blocks(c);
-    a.nb_t = (c->geo.vsh % kBlock == 0 && (c->geo.vsh / kBlock) % 8 == 0) ? c->geo.vsh / kBlock : 0;
+    a.nb_t = (c->geo.vsh % kSites == 0 && (c->geo.vsh / kSites) % 8 == 0) ? c->geo.vsh / kSites : 0;
     a.t_bc = c->t_bc;
     return a;
 }
 
-template <typename SS, typename LS, typename T, int R>
+template <typename SS, typename LS, typename T>
 void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
 {
-    const DParams<T> a = fill_params<SS, LS, T, R>(c, dc);
+    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>());
+    if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
+        if (atoi(e) > 0) rpb = atoi(e);
+    const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
     dim3 grid((unsigned)(a.nblk * a.ngroups));
     // separate kernels per projector placement and per presence of the
     // own-site term (the x - H y forms read one more field)
     if (dc.dag) {
         if (dc.has_own)
-            launch_epi<SS, LS, T, R, 1, 1>(dc, grid, s, a);
+            launch_epi<SS, LS, T, 1, 1>(dc, grid, s, a);
         else
-            launch_epi<SS, LS, T, R, 1, 0>(dc, grid, s, a);
+            launch_epi<SS, LS, T, 1, 0>(dc, grid, s, a);
     } else {
         if (dc.has_own)
-            launch_epi<SS, LS, T, R, 0, 1>(dc, grid, s, a);
+            launch_epi<SS, LS, T, 0, 1>(dc, grid, s, a);
         else
-            launch_epi<SS, LS, T, R, 0, 0>(dc, grid, s, a);
+            launch_epi<SS, LS, T, 0, 0>(dc, grid, s, a);
     }
     TM_HIP(hipGetLastError());
 }
 
-// Right-hand sides per thread that fit the register budget: FP32 arithmetic
-// 1..3 (4 or more exceed 3 resident waves and spill), FP64 1..2; the packed
-// binary16 form (FP16 spinors, binary16 links) keeps its spinors in half the
-// registers and also tries 4 (at 2 waves per SIMD)
 template <typename SS, typename LS, typename T>
-constexpr int max_tile()
-{
-    if constexpr (sizeof(T) == 8) return 2;
-    if constexpr (std::is_same<SS, h2>::value && (std::is_same<LS, L12>::value || std::is_same<LS, h2>::value))
-        return 4;
-    return 3;
-}
-
-template <typename SS, typename LS, typename T>
-void launch_r(tm_ctx *c, const DslashCall &dc, int R, hipStream_t s)
-{
-    if constexpr (max_tile<SS, LS, T>() >= 4) {
-        if (R == 4) {
-            launch_t<SS, LS, T, 4>(c, dc, s);
-            return;
-        }
-    }
-    if (R == 3) {
-        if constexpr (max_tile<SS, LS, T>() >= 3) {
-            launch_t<SS, LS, T, 3>(c, dc, s);
-            return;
-        }
-    }
-    if (R >= 2)
-        launch_t<SS, LS, T, 2>(c, dc, s);
-    else
-        launch_t<SS, LS, T, 1>(c, dc, s);
-}
-
-// Right-hand sides per thread (each loaded link serves R spinors).  The first
-// side-effect-free launch for a (precision, nrhs) pair times every tile that
-// divides nrhs and keeps the fastest; results are bit-identical across tiles.
-template <typename SS, typename LS, typename T>
-void launch_rhs(tm_ctx *c, const DslashCall &dc, hipStream_t s)
-{
-    const int n = dc.nrhs;
-    // tiles are tuned per (spinor precision, link storage, operator form, nrhs):
-    // the fused epilogues favour other tiles than the plain store
-    const int lcode = std::is_same<LS, h2>::value    ? 1
-                      : std::is_same<LS, L12>::value ? 2
-                      : std::is_same<LS, L12D>::value ? 3
-                      : std::is_same<LS, L12F>::value ? 4
-                      : std::is_same<LS, L8D>::value  ? 5
-                                                      : 0;
-    const int form = dc.dag + 2 * (dc.has_own ? 1 : 0) + 4 * dc.epi;
-    const auto key = std::make_pair(dc.spinor_prec + 8 * lcode + 32 * form, n);
-    auto it = c->rhs_tile.find(key);
-    if (it != c->rhs_tile.end()) {
-        launch_r<SS, LS, T>(c, dc, it->second, s);
-        return;
-    }
-    const int def = sizeof(T) == 8 ? 1 : (n % 2 == 0 ? 2 : 1);
-    if (c->no_alloc) {  // allocation-free call: no timing launches, no events
-        launch_r<SS, LS, T>(c, dc, def, s);
-        return;
-    }
-    int fixed = 0;
-    if (const char *e = getenv("TM_DSLASH_RHS_TILE")) fixed = atoi(e);
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    TM_HIP(hipStreamIsCapturing(s, &cs));
-    // timing launches must leave the caller's fields as they were: the output
-    // distinct from both inputs, and the in-place CG update of the fused form
-    // redirected to scratch fields (its block partials are rewritten by the
-    // real launch that follows)
-    DslashCall tc = dc;
-    const bool repeatable = dc.epi == EPI_CG || (dc.out != dc.in && dc.out != dc.own);
-    if (fixed > 0 && fixed <= max_tile<SS, LS, T>() && n % fixed == 0) {
-        c->rhs_tile[key] = fixed;
-    } else if (!repeatable || cs != hipStreamCaptureStatusNone || n == 1) {
-        launch_r<SS, LS, T>(c, dc, def, s);  // tune on a later plain launch
-        return;
-    } else {
-        if (dc.epi == EPI_CG) {  // not capturing here: allocation is allowed
-            const size_t fb = (size_t)prec_bytes(dc.spinor_prec) * 12 * c->geo.hs * n;
-            tc.r = ws_get(c, "tune_r", fb);
-            tc.rho = dc.rho ? ws_get(c, "tune_rho", fb) : nullptr;
-        }
-        hipEvent_t e0, e1;
-        TM_HIP(hipEventCreate(&e0));
-        TM_HIP(hipEventCreate(&e1));
-        float best = 1e30f;
-        int bestR = def;
-        for (int R = 1; R <= max_tile<SS, LS, T>(); R++) {
-            if (n % R) continue;
-            launch_r<SS, LS, T>(c, tc, R, s);  // warm
-            TM_HIP(hipEventRecord(e0, s));
-            // enough launches that tiles a few percent apart are ranked reliably
-            for (int k = 0; k < 6; k++) launch_r<SS, LS, T>(c, tc, R, s);
-            TM_HIP(hipEventRecord(e1, s));
-            TM_HIP(hipEventSynchronize(e1));
-            float ms = 0;
-            TM_HIP(hipEventElapsedTime(&ms, e0, e1));
-            if (ms < best) {
-                best = ms;
-                bestR = R;
-            }
-        }
-        TM_HIP(hipEventDestroy(e0));
-        TM_HIP(hipEventDestroy(e1));
-        c->rhs_tile[key] = bestR;
-    }
-    launch_r<SS, LS, T>(c, dc, c->rhs_tile[key], s);
-}
-
-template <typename SS, typename LS, typename T, int R>
-void multi_fill(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs)
+void multi_fill(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int rpb)
 {
     m.args.clear();
     m.grid.clear();
@@ -1201,9 +1309,8 @@ void multi_fill(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vect
         a.n = (int)(c1 - c0);
         a.start[0] = 0;
         for (size_t k = c0; k < c1; k++) {
-            TM_REQUIRE(dcs[k].nrhs % R == 0, "RHS tile must divide every instance's nrhs");
             const int j = (int)(k - c0);
-            a.p[j] = fill_params<SS, LS, T, R>(cs[k], dcs[k]);
+            a.p[j] = fill_params<SS, LS, T>(cs[k], dcs[k], rpb);
             const int nb = a.p[j].nblk * a.p[j].ngroups;
             a.start[j + 1] = a.start[j] + (nb + 7) / 8 * 8;
         }
@@ -1213,7 +1320,7 @@ void multi_fill(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vect
     }
 }
 
-template <typename SS, typename LS, typename T, int R>
+template <typename SS, typename LS, typename T>
 void multi_go(const MultiDslash &m, hipStream_t s)
 {
     for (size_t c = 0; c < m.args.size(); c++) {
@@ -1223,13 +1330,13 @@ void multi_go(const MultiDslash &m, hipStream_t s)
         dim3 g(m.grid[c]), b(kBlock);
         // the four stage forms of a CG iteration on the Schur normal equations
         if (m.dag == 0 && m.own == 0 && m.epi == EPI_STORE)
-            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, R, 0, 0, EPI_STORE>), g, b, 0, s, a);
+            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, 0, 0, EPI_STORE>), g, b, 0, s, a);
         else if (m.dag == 1 && m.own == 0 && m.epi == EPI_STORE)
-            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, R, 1, 0, EPI_STORE>), g, b, 0, s, a);
+            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, 1, 0, EPI_STORE>), g, b, 0, s, a);
         else if (m.dag == 0 && m.own == 1 && m.epi == EPI_NORM)
-            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, R, 0, 1, EPI_NORM>), g, b, 0, s, a);
+            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, 0, 1, EPI_NORM>), g, b, 0, s, a);
         else if (m.dag == 0 && m.own == 1 && m.epi == EPI_CG)
-            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, R, 0, 1, EPI_CG>), g, b, 0, s, a);
+            hipLaunchKernelGGL((k_dslash_multi<SS, LS, T, 0, 1, EPI_CG>), g, b, 0, s, a);
         else
             throw TmError{TM_ERR_UNSUPPORTED, "multi-instance Dslash form not instantiated"};
         TM_HIP(hipGetLastError());
@@ -1237,21 +1344,11 @@ void multi_go(const MultiDslash &m, hipStream_t s)
 }
 
 template <typename F>
-void multi_dispatch(int prec, bool recon12, bool recon8, int R, F &&f)
+void multi_dispatch(int prec, bool recon12, bool recon8, F &&f)
 {
-    auto byR = [&](auto *tag) {
+    auto with = [&](auto *tag) {
         using P3 = std::remove_pointer_t<decltype(tag)>;
-        if constexpr (std::is_same<typename P3::T, double>::value) {
-            TM_REQUIRE(R == 1, "FP64 uses one right-hand side per thread");
-            f.template operator()<typename P3::SS, typename P3::LS, typename P3::T, 1>();
-        } else {
-            if (R == 3)
-                f.template operator()<typename P3::SS, typename P3::LS, typename P3::T, 3>();
-            else if (R == 2)
-                f.template operator()<typename P3::SS, typename P3::LS, typename P3::T, 2>();
-            else
-                f.template operator()<typename P3::SS, typename P3::LS, typename P3::T, 1>();
-        }
+        f.template operator()<typename P3::SS, typename P3::LS, typename P3::T>();
     };
     struct PD { using SS = double2; using LS = double2; using T = double; };
     struct PD12 { using SS = double2; using LS = L12D; using T = double; };
@@ -1265,18 +1362,18 @@ void multi_dispatch(int prec, bool recon12, bool recon8, int R, F &&f)
     switch (prec) {
     case TM_F64:
         if (recon8)
-            byR((PD8 *)nullptr);
+            with((PD8 *)nullptr);
         else
-            recon12 ? byR((PD12 *)nullptr) : byR((PD *)nullptr);
+            recon12 ? with((PD12 *)nullptr) : with((PD *)nullptr);
         break;
-    case TM_F32: recon12 ? byR((PF12 *)nullptr) : byR((PF *)nullptr); break;
-    case TM_F16: recon12 ? byR((PH12 *)nullptr) : byR((PH *)nullptr); break;
-    case TM_BF16: recon12 ? byR((PB12 *)nullptr) : byR((PB *)nullptr); break;
+    case TM_F32: recon12 ? with((PF12 *)nullptr) : with((PF *)nullptr); break;
+    case TM_F16: recon12 ? with((PH12 *)nullptr) : with((PH *)nullptr); break;
+    case TM_BF16: recon12 ? with((PB12 *)nullptr) : with((PB *)nullptr); break;
     default: throw TmError{TM_ERR_ARG, "bad precision"};
     }
 }
 
-template <typename SS, typename LS, typename T, int R>
+template <typename SS, typename LS, typename T>
 void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream_t s)
 {
     if constexpr (sizeof(T) == 8) {
@@ -1285,10 +1382,7 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     PersistArgs<T> a{};
     a.n = (int)v.size();
     for (int k = 0; k < a.n; k++) {
-        for (int st = 0; st < 4; st++) {
-            TM_REQUIRE(v[k].st[st].nrhs % R == 0, "RHS tile must divide every instance's nrhs");
-            a.st[st][k] = fill_params<SS, LS, T, R>(v[k].c, v[k].st[st]);
-        }
+        for (int st = 0; st < 4; st++) a.st[st][k] = fill_params<SS, LS, T>(v[k].c, v[k].st[st], pb.rpb);
         const int nb = a.st[0][k].nblk * a.st[0][k].ngroups;
         a.start[k + 1] = a.start[k] + (nb + 7) / 8 * 8;
         const size_t n = (size_t)12 * v[k].c->geo.hs;
@@ -1310,7 +1404,7 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     TM_HIP(hipMemcpy(pb.dev_args, &a, sizeof(a), hipMemcpyHostToDevice));
     // co-resident blocks of this instantiation: the grid of the cooperative launch
     int per_cu = 0, ncu = 0;
-    TM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_persist<SS, LS, T, R>, kBlock, 0));
+    TM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_persist<SS, LS, T>, kBlock, 0));
     TM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, v[0].c->device));
     if (pb.blocks_per_cu > 0) per_cu = std::min(per_cu, pb.blocks_per_cu);
     const int cap = per_cu * ncu / 8 * 8;
@@ -1319,7 +1413,7 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     }
 }
 
-template <typename SS, typename LS, typename T, int R>
+template <typename SS, typename LS, typename T>
 bool persist_go(const PersistBatch &pb, hipStream_t s)
 {
     if constexpr (sizeof(T) == 8) {
@@ -1330,7 +1424,7 @@ bool persist_go(const PersistBatch &pb, hipStream_t s)
     int iters = pb.iters;
     unsigned long long spin = pb.spin_limit;
     void *kargs[] = {&pa, &iters, &spin};
-    if (hipLaunchCooperativeKernel((const void *)k_batch_persist<SS, LS, T, R>, dim3(pb.grid), dim3(kBlock), kargs,
+    if (hipLaunchCooperativeKernel((const void *)k_batch_persist<SS, LS, T>, dim3(pb.grid), dim3(kBlock), kargs,
                                    0, s) != hipSuccess) {
         (void)hipGetLastError();  // refused (e.g. the grid cannot be co-resident): nothing was launched
         return false;
@@ -1341,7 +1435,7 @@ bool persist_go(const PersistBatch &pb, hipStream_t s)
 
 }  // namespace
 
-void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int R,
+void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int rpb,
                           hipStream_t s)
 {
     TM_REQUIRE(!cs.empty() && cs.size() == dcs.size(), "bad multi-instance call");
@@ -1353,7 +1447,6 @@ void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const
     m.dag = dcs[0].dag;
     m.own = dcs[0].has_own ? 1 : 0;
     m.epi = dcs[0].epi;
-    m.R = R;
     m.n = (int)cs.size();
     m.recon8 = false;
     for (size_t k = 0; k < cs.size(); k++) {
@@ -1383,14 +1476,14 @@ void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const
         }
     }
     m.recon12 = recon12_ok(cs[0], m.prec);
-    multi_dispatch(m.prec, m.recon12, m.recon8, R,
-                   [&]<typename SS, typename LS, typename T, int RR>() { multi_fill<SS, LS, T, RR>(m, cs, dcs); });
+    multi_dispatch(m.prec, m.recon12, m.recon8,
+                   [&]<typename SS, typename LS, typename T>() { multi_fill<SS, LS, T>(m, cs, dcs, rpb); });
 }
 
 void multi_dslash_launch(const MultiDslash &m, hipStream_t s)
 {
-    multi_dispatch(m.prec, m.recon12, m.recon8, m.R,
-                   [&]<typename SS, typename LS, typename T, int RR>() { multi_go<SS, LS, T, RR>(m, s); });
+    multi_dispatch(m.prec, m.recon12, m.recon8,
+                   [&]<typename SS, typename LS, typename T>() { multi_go<SS, LS, T>(m, s); });
 }
 
 bool persist_supported(int device)
@@ -1403,7 +1496,7 @@ bool persist_supported(int device)
     return coop != 0;
 }
 
-void persist_prepare(PersistBatch &pb, const std::vector<PersistInst> &v, int R, hipStream_t s)
+void persist_prepare(PersistBatch &pb, const std::vector<PersistInst> &v, int rpb, hipStream_t s)
 {
     TM_REQUIRE(!v.empty() && (int)v.size() <= kPersistInst, "persistent batch: 1 to 4 instances");
     const int prec = v[0].st[0].spinor_prec;
@@ -1417,18 +1510,18 @@ void persist_prepare(PersistBatch &pb, const std::vector<PersistInst> &v, int R,
         std::vector<tm_ctx *> cs(1, q.c);
         for (int st = 0; st < 4; st++) {
             TM_REQUIRE(q.st[st].spinor_prec == prec, "batched solves share precision");
-            multi_dslash_prepare(m, cs, std::vector<DslashCall>(1, q.st[st]), R, s);
+            multi_dslash_prepare(m, cs, std::vector<DslashCall>(1, q.st[st]), rpb, s);
         }
         TM_REQUIRE(recon12_ok(q.c, prec) == recon12_ok(c0, prec), "batched instances must share the link format");
         if (&q == &v[0]) recon8 = m.recon8;
         TM_REQUIRE(m.recon8 == recon8, "batched instances must share the link format");
     }
     pb.prec = prec;
-    pb.R = R;
+    pb.rpb = rpb;
     pb.recon12 = recon12_ok(c0, prec);
     pb.recon8 = recon8;
-    multi_dispatch(pb.prec, pb.recon12, pb.recon8, R,
-                   [&]<typename SS, typename LS, typename T, int RR>() { persist_fill<SS, LS, T, RR>(pb, v, s); });
+    multi_dispatch(pb.prec, pb.recon12, pb.recon8,
+                   [&]<typename SS, typename LS, typename T>() { persist_fill<SS, LS, T>(pb, v, s); });
 }
 
 bool persist_launch(PersistBatch &pb, int iters, unsigned long long spin_limit, hipStream_t s)
@@ -1440,8 +1533,8 @@ bool persist_launch(PersistBatch &pb, int iters, unsigned long long spin_limit, 
     // it set)
     TM_HIP(hipMemsetAsync(pb.bar, 0, pb.sync_bytes, s));
     bool ok = false;
-    multi_dispatch(pb.prec, pb.recon12, pb.recon8, pb.R,
-                   [&]<typename SS, typename LS, typename T, int RR>() { ok = persist_go<SS, LS, T, RR>(pb, s); });
+    multi_dispatch(pb.prec, pb.recon12, pb.recon8,
+                   [&]<typename SS, typename LS, typename T>() { ok = persist_go<SS, LS, T>(pb, s); });
     return ok;
 }
 
@@ -1453,7 +1546,14 @@ bool persist_failed(const PersistBatch &pb, hipStream_t s)
     return fail != 0;
 }
 
-int dslash_site_blocks(tm_ctx *c) { return (c->geo.vh + kBlock - 1) / kBlock; }
+int dslash_site_blocks(tm_ctx *c) { return (c->geo.vh + kSites - 1) / kSites; }
+
+int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst)
+{
+    std::vector<std::pair<int, int>> v;
+    for (const auto &[c, nrhs] : inst) v.push_back({dslash_site_blocks(c), nrhs});
+    return rhs_per_block(v, slots_of<h2, L12, float>());
+}
 
 void dslash_cost(tm_ctx *c, const DslashCall &dc, double &bytes, double &flops)
 {
@@ -1499,21 +1599,21 @@ void launch_dslash(tm_ctx *c, const DslashCall &dc, hipStream_t s)
     // links in the context's format, the third row rebuilt exactly up to rounding
     case TM_F64:
         if (!dc.links18 && recon8_wanted(c) && ensure_links8d(c, s)) {
-            launch_rhs<double2, L8D, double>(c, dc, s);
+            launch_t<double2, L8D, double>(c, dc, s);
         } else if (recon12_ok(c, TM_F64) && !dc.links18) {
             ensure_links12d(c, s);
-            launch_rhs<double2, L12D, double>(c, dc, s);
+            launch_t<double2, L12D, double>(c, dc, s);
         } else {
-            launch_rhs<double2, double2, double>(c, dc, s);
+            launch_t<double2, double2, double>(c, dc, s);
         }
         break;
     case TM_F32:
         if (recon12_ok(c, TM_F32)) {
             ensure_links12f(c, s);
-            launch_rhs<float2, L12F, float>(c, dc, s);
+            launch_t<float2, L12F, float>(c, dc, s);
         } else {
             ensure_links32(c, s);
-            launch_rhs<float2, float2, float>(c, dc, s);
+            launch_t<float2, float2, float>(c, dc, s);
         }
         break;
     // FP16/BF16 spinors: binary16 links in the context's format (all 18
@@ -1522,25 +1622,25 @@ void launch_dslash(tm_ctx *c, const DslashCall &dc, hipStream_t s)
     case TM_F16:
         if (c->half_links_f32) {
             ensure_links32(c, s);
-            launch_rhs<h2, float2, float>(c, dc, s);
+            launch_t<h2, float2, float>(c, dc, s);
         } else if (recon12_ok(c, TM_F16)) {
             ensure_links12(c, s);
-            launch_rhs<h2, L12, float>(c, dc, s);
+            launch_t<h2, L12, float>(c, dc, s);
         } else {
             ensure_links16(c, s);
-            launch_rhs<h2, h2, float>(c, dc, s);
+            launch_t<h2, h2, float>(c, dc, s);
         }
         break;
     case TM_BF16:
         if (c->half_links_f32) {
             ensure_links32(c, s);
-            launch_rhs<b2, float2, float>(c, dc, s);
+            launch_t<b2, float2, float>(c, dc, s);
         } else if (recon12_ok(c, TM_BF16)) {
             ensure_links12(c, s);
-            launch_rhs<b2, L12, float>(c, dc, s);
+            launch_t<b2, L12, float>(c, dc, s);
         } else {
             ensure_links16(c, s);
-            launch_rhs<b2, h2, float>(c, dc, s);
+            launch_t<b2, h2, float>(c, dc, s);
         }
         break;
     default: throw TmError{TM_ERR_ARG, "bad spinor precision"};

@@ -205,12 +205,32 @@ static inline size_t prec_bytes(int prec)
 // Lattice geometry for kernels (passed by value).  Half-site index i of parity
 // p is s >> 1 with s = x + Lx*(y + Ly*(z + Lz*t)); the row q = y + Ly*(z + Lz*t)
 // gives i = (x >> 1) + (Lx/2) * q.
+//
+// The three divisions of that decomposition are by extents known on the host:
+// n / d = (2n m >> 32) >> s for 0 <= n < 2^31 with s = ceil(log2 d) and
+// m = floor(2^(31+s) / d) + 1, two instructions and a shift where a division
+// by a run-time divisor is about twenty.
+struct FastDiv {
+    unsigned m, s;
+};
+inline FastDiv fast_div(int d)
+{
+    unsigned s = 0;
+    while ((1ll << s) < d) s++;
+    return FastDiv{(unsigned)((1ull << (31 + s)) / (unsigned)d + 1), s};
+}
+__host__ __device__ __forceinline__ int operator/(int n, FastDiv d)
+{
+    return (int)((unsigned)(((unsigned long long)(2u * (unsigned)n) * d.m) >> 32) >> d.s);
+}
+
 struct Geo {
     int L[4];
     int lxh;   // Lx / 2
     int vh;    // V / 2
     int vsh;   // half-sites per time slice, Lx*Ly*Lz / 2
     int hs;    // plane stride of half-site fields (sites), see half_stride
+    FastDiv by_lxh, by_y, by_z;  // division by lxh, L[1], L[2]
 };
 
 // Half-site fields are stored [rhs][spin*3 + colour][hs] with hs >= vh; the
@@ -229,12 +249,12 @@ inline int half_stride(int vh)
 
 __device__ __forceinline__ void eo_coords(const Geo &g, int p, int i, int &x, int &y, int &z, int &t)
 {
-    int q = i / g.lxh;
-    int xh = i - q * g.lxh;
-    y = q % g.L[1];
-    int q2 = q / g.L[1];
-    z = q2 % g.L[2];
-    t = q2 / g.L[2];
+    const int q = i / g.by_lxh;
+    const int xh = i - q * g.lxh;
+    const int q2 = q / g.by_y;
+    y = q - q2 * g.L[1];
+    t = q2 / g.by_z;
+    z = q2 - t * g.L[2];
     x = 2 * xh + ((p ^ (y + z + t)) & 1);
 }
 
@@ -308,8 +328,6 @@ struct tm_ctx {
     // (tm_set_half_spinor_links): false = binary16 copy, true = FP32 (18)
     bool half_links_f32_default = false;
     std::map<std::string, DevBuf> ws;
-    // autotuned right-hand sides per Dslash thread, keyed by (precision, nrhs)
-    std::map<std::pair<int, int>, int> rhs_tile;
     std::string err;
     hipStream_t stream = nullptr;  // stream of the current loop-driver call
     // pinned host staging for scalar read-back
@@ -332,7 +350,7 @@ struct tm_ctx {
     double acct_bytes = 0, acct_flops = 0;
     int acct_pause = 0;
     // set for the duration of an allocation-free call: ws_get refuses to
-    // allocate and the Dslash tile tuner is not run
+    // allocate
     bool no_alloc = false;
 };
 
@@ -432,21 +450,22 @@ int dslash_site_blocks(tm_ctx *c);
 void dslash_cost(tm_ctx *c, const DslashCall &dc, double &bytes, double &flops);
 
 // One launch over several contexts (lattices), one DslashCall each; all
-// share precision and operator form; R right-hand sides per thread divides
-// every nrhs.  prepare() builds the launch arguments on the host;
+// share precision and operator form; rpb right-hand sides per block.  prepare() builds the launch arguments on the host;
 // launch() is one kernel launch per chunk of instances (capturable).
 struct MultiDslash {
     // per chunk of at most kMultiInst instances: the kernel-argument block
     // (instance records + block offsets) and the grid it covers
     std::vector<std::vector<unsigned char>> args;
     std::vector<int> grid;
-    int prec = 0, dag = 0, own = 0, epi = 0, R = 1, n = 0;
+    int prec = 0, dag = 0, own = 0, epi = 0, n = 0;
     bool recon12 = false;  // links in the 12-parameter format
     bool recon8 = false;   // FP64 links in the 8-parameter format
 };
 constexpr int kMultiInst = 16;  // instances per launch (kernel-argument space)
-void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int R,
+void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int rpb,
                           hipStream_t s);
+// right-hand sides per block of a launch over several (context, nrhs)
+int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst);
 void multi_dslash_launch(const MultiDslash &m, hipStream_t s);
 
 // Persistent batch: `iters` CG iterations of up to kPersistInst instances in
@@ -465,13 +484,13 @@ struct PersistBatch {
     size_t args_bytes = 0, sync_bytes = 0;
     int grid = 0, work = 0, iters = 0;
     int blocks_per_cu = 0;             // cap on resident blocks per CU (0: as many as fit)
-    int prec = 0, R = 1;
+    int prec = 0, rpb = 1;
     bool recon12 = false, recon8 = false;
     void *bar = nullptr;               // barrier state (device)
     unsigned long long spin_limit = 0;
 };
 bool persist_supported(int device);
-void persist_prepare(PersistBatch &pb, const std::vector<PersistInst> &v, int R, hipStream_t s);
+void persist_prepare(PersistBatch &pb, const std::vector<PersistInst> &v, int rpb, hipStream_t s);
 // false if the runtime refused the cooperative launch (nothing launched)
 bool persist_launch(PersistBatch &pb, int iters, unsigned long long spin_limit, hipStream_t s);
 // reads the barrier state (synchronises the stream): true if a wait gave up
