@@ -128,12 +128,12 @@ struct Momentum {
 std::vector<Momentum> momenta_list(int p2max);
 // every |n_i| must stay below L_i / 2 (distinct momenta on the lattice)
 void check_momenta(tm_ctx *c, int p2max);
-// momentum-projected outer products, out [n_mom][Lt][16] (momentum.hip)
-void outer_momenta_host(tm_ctx *c, const void *ve, const void *vo, const void *we, const void *wo, int nrhs,
-                        const std::vector<Momentum> &mom, std::vector<cx<double>> &out, hipStream_t s);
-// one-derivative outer products D_mu, out [n_mom][4 mu][Lt][16] (momentum.hip)
-void outer_deriv_host(tm_ctx *c, const void *ve, const void *vo, const void *we, const void *wo, int nrhs,
-                      const std::vector<Momentum> &mom, std::vector<cx<double>> &out, hipStream_t s);
+// loops of the bilinears of v and w at the listed momenta, coef times the
+// Gamma insertions of `form`: host out[n_mom][n_ins][Lt] with the 16 ultra-local
+// insertions (local) and then the 64 one-derivative ones (deriv) (momentum.hip)
+void momentum_loops(tm_ctx *c, const void *ve, const void *vo, const void *we, const void *wo, int nrhs,
+                    const std::vector<Momentum> &mom, GammaForm form, cx<double> coef, bool local, bool deriv,
+                    cx<double> *out, hipStream_t s);
 // D_W f = f + H f (no twist) on FP64 half fields
 void op_wilson(tm_ctx *c, void *oe, void *oo, const void *fe, const void *fo, int nrhs, hipStream_t s);
 // exactly known part of the hopping expansion for ultra-local insertions

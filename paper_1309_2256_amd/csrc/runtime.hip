@@ -610,8 +610,7 @@ void contract_noise(tm_ctx *c, int estimators, int derivative, const void *ee, c
     const size_t per_ins = (size_t)16 * Lt;  // one block of 16 insertions
     const int n_ins = n_insertions(derivative);
     const int n_mom = mom ? (int)mom->size() : 1;
-    const size_t per_m = (size_t)Lt * n_ins;
-    const size_t per = per_m * n_mom;
+    const size_t per = (size_t)Lt * n_ins * n_mom;
     const size_t f64 = field_bytes(c, TM_F64, nrhs);
     static const std::vector<Momentum> zero{Momentum{{0, 0, 0}}};
     std::vector<cx<double>> C;
@@ -631,19 +630,14 @@ void contract_noise(tm_ctx *c, int estimators, int derivative, const void *ee, c
             }
             loops_from_outer(c, acc.data(), form, coef, out);
         } else if (mom) {
-            outer_momenta_host(c, ve, vo, we, wo, nrhs, *mom, C, s_of(c));
-            for (int m = 0; m < n_mom; m++) loops_from_outer(c, C.data() + per_ins * m, form, coef, out + per_m * m);
+            momentum_loops(c, ve, vo, we, wo, nrhs, *mom, form, coef, true, deriv, out, s_of(c));
+            return;
         } else {
             outer_slices_host(c, ve, vo, we, wo, nrhs, C, s_of(c));
             loops_from_outer(c, C.data(), form, coef, out);
         }
-        if (!deriv) return;
-        // D_mu blocks [n_mom][4][Lt][16]; per time slice = the zero momentum
-        outer_deriv_host(c, ve, vo, we, wo, nrhs, mom ? *mom : zero, C, s_of(c));
-        for (int m = 0; m < n_mom; m++)
-            for (int mu = 0; mu < 4; mu++)
-                loops_from_outer(c, C.data() + per_ins * (4 * m + mu), form, coef,
-                                 out + per_m * m + per_ins * (1 + mu));
+        // per time slice = the zero momentum
+        if (deriv) momentum_loops(c, ve, vo, we, wo, nrhs, zero, form, coef, false, true, out + per_ins, s_of(c));
     };
     int k = 0;
     if (estimators & TM_EST_STD)
