@@ -80,20 +80,21 @@ __global__ __launch_bounds__(kBlock) void k_mdot(const SV *V, size_t vstride, in
     }
 }
 
-// out[r*ld + i0 + i] = sum over halves and blocks (fixed order)
-__global__ void k_mdot_finish(const double2 *part, int nb, int nblk, int nrhs, double2 *out, int ld, int i0)
+// out[r*ld + i0 + i] = sum over halves and blocks (fixed order); one wave per
+// (r, i), block r * nb + i (a thread each walked the 512 partials in series,
+// 46 us a launch; now 3)
+__global__ __launch_bounds__(64) void k_mdot_finish(const double2 *part, int nb, int nblk, double2 *out, int ld, int i0)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nrhs * nb) return;
-    const int r = idx / nb, i = idx % nb;
+    const int r = blockIdx.x / nb, i = blockIdx.x % nb;
+    const double2 *p = part + ((size_t)r * kChunk + i) * 2 * nblk;
     double re = 0, im = 0;
-    for (int h = 0; h < 2; h++)
-        for (int b = 0; b < nblk; b++) {
-            const double2 v = part[(((size_t)r * kChunk + i) * 2 + h) * nblk + b];
-            re += v.x;
-            im += v.y;
-        }
-    out[(size_t)r * ld + i0 + i] = make_double2(re, im);
+    for (int b = threadIdx.x; b < 2 * nblk; b += 64) {
+        re += p[b].x;
+        im += p[b].y;
+    }
+    re = wave_sum(re);
+    im = wave_sum(im);
+    if (threadIdx.x == 0) out[(size_t)r * ld + i0 + i] = make_double2(re, im);
 }
 
 // w += sign * sum_i coef[r*ld + i0 + i] v_i; grid (blocks, nrhs, 2)
@@ -236,8 +237,8 @@ void mdot(Fg &f, const SV *V, size_t vstride, int nb, const double2 *w, double2 
         hipLaunchKernelGGL(k_mdot<SV>, dim3(kDotBlk, f.nrhs, 2), dim3(kBlock), 0, f.s, V + c0 * vstride, vstride, k,
                            w, f.n, f.hs, f.c->geo.vh, f.c->geo.hs, f.part);
         TM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_mdot_finish, dim3((f.nrhs * k + 63) / 64), dim3(64), 0, f.s, (const double2 *)f.part, k,
-                           kDotBlk, f.nrhs, out, ld, i0 + c0);
+        hipLaunchKernelGGL(k_mdot_finish, dim3(f.nrhs * k), dim3(64), 0, f.s, (const double2 *)f.part, k, kDotBlk,
+                           out, ld, i0 + c0);
         TM_HIP(hipGetLastError());
     }
 }
