@@ -32,7 +32,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kMaxNc = 64;
-constexpr int kGradBlocks = 240;  // site blocks of the gradient reduction
+constexpr int kGradBlocks = 512;  // blocks of the gradient reduction, two per CU
 constexpr int kKG = 3;            // paths k per thread of k_ptc_mix
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -307,19 +307,26 @@ __global__ __launch_bounds__(kBlock) void k_ptc_delta(const float2 *out, const S
     }
 }
 
-// loss += sum_b (sum of partials of both parities of sample b) / |e_b|^2 / nrhs
-__global__ void k_ptc_loss_finish(const double *part0, const double *part1, const double *en2, int nblk,
-                                  int nrhs, double *loss)
+// loss = mean over samples b of (sum of partials of both parities) / |e_b|^2:
+// one block, a wave per sample, fixed order
+__global__ __launch_bounds__(kBlock) void k_ptc_loss_finish(const double *part0, const double *part1, const double *en2,
+                                                            int nblk, int nrhs, double *loss)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double red[kBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     double l = 0;
-    for (int r = 0; r < nrhs; r++) {
+    for (int r = w; r < nrhs; r += kBlock / 64) {
         double s = 0;
-        for (int b = 0; b < nblk; b++) s += part0[(size_t)r * nblk + b];
-        for (int b = 0; b < nblk; b++) s += part1[(size_t)r * nblk + b];
-        l += s / en2[r];
+        for (int b = lane; b < nblk; b += 64) s += part0[(size_t)r * nblk + b] + part1[(size_t)r * nblk + b];
+        l += wave_sum(s) / en2[r];
     }
-    *loss = l / nrhs;
+    if (lane == 0) red[w] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        l = 0;
+        for (int k = 0; k < kBlock / 64; k++) l += red[k];
+        *loss = l / nrhs;
+    }
 }
 
 // Residual loss: w -= r (r in the pair-store precision), partial |w|^2 per
@@ -361,79 +368,121 @@ __global__ __launch_bounds__(kBlock) void k_ptc_scale(float2 *v, const double *r
     }
 }
 
-// Partial dl/dA[k][k'] on parity p: sum over the block's sites (grid-stride)
-// and all samples of (T_kbar delta)(x) (T_k' in)(x)^dag, colour traced, FP64.
-// grid (kGradBlocks, 81); part [81][kGradBlocks][32].
+// dl/dA[k][k'][a][b] = sum over sites, samples and colours of h_(k,a) conj(g_(k',b)),
+// h_k = T_kbar delta, g_k' = T_k' in: with real and imaginary parts apart it is
+// one real matrix product P = H G^T, H and G of 72 rows 2 (4k + a) + re/im and
+// a column per (colour, site, sample), FP32 values (exact in FP64), on
+// v_mfma_f64_16x16x4_f64.  A block takes 32 sites of one sample at a time: its
+// waves form the 18 transports of every site once into LDS, then wave w
+// accumulates the 16x16 tiles (w, 0..4), (4, w) and wave 0 also (4, 4) of P
+// over the 96 columns.  Rows are padded to 80 (zeros) and their stride to 100
+// floats: lane (i, k) of an operand reads bank 36 i + k mod 64, all different.
+// Operand lanes: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k, D[i][j] in
+// lane (j, g) at i = g + 4 v.
+// Bound: matrix time, 600 instructions of 64 cycles per tile; two blocks per
+// CU, so that one transports while the other multiplies.  16 samples of
+// 16^3 x 32: 1.95 ms (matrix time 1.25 ms); a block per (k, k') pair formed
+// each transport nine times and took 5.26 ms.
+constexpr int kGS = 32, kGStride = 100, kGRows = 80, kGTiles = 25;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 template <typename S>
-__global__ __launch_bounds__(kBlock) void k_ptc_grad(const S *in_same, const S *in_other, const float2 *dl_same,
-                                                     const float2 *dl_other, const float2 *links, Geo g, int p,
-                                                     int nrhs, double *part)
+__global__ __launch_bounds__(kBlock, 2) void k_ptc_grad(const S *in0, const S *in1, const float2 *dl0, const float2 *dl1,
+                                                        const float2 *links0, const float2 *links1, Geo g, int nrhs,
+                                                        int tiles, double *part)
 {
-    const int pair = blockIdx.y, k = pair / 9, kp = pair % 9;
-    const int kbar = k == 0 ? 0 : (k <= 4 ? k + 4 : k - 4);
+    __shared__ float H[kGRows * kGStride], G[kGRows * kGStride];
+    for (int k = 72 * kGStride + threadIdx.x; k < kGRows * kGStride; k += kBlock) H[k] = G[k] = 0.f;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int n = lane % 16, grp = lane / 16;
     const size_t fs = (size_t)12 * g.hs;
-    double acc[32];
+    f64x4 acc[7];
 #pragma unroll
-    for (int q = 0; q < 32; q++) acc[q] = 0;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < g.vh; i += gridDim.x * kBlock) {
+    for (int q = 0; q < 7; q++) acc[q] = f64x4{0, 0, 0, 0};
+    for (int wk = blockIdx.x; wk < tiles * 2 * nrhs; wk += gridDim.x) {
+        const int r = wk % nrhs, p = (wk / nrhs) & 1, i0 = (wk / nrhs >> 1) * kGS;
+        __syncthreads();  // the previous tile has been read
+        // tasks 0..7: g of paths 1..8, 8..15: h of paths 1..8, 16, 17: g, h of
+        // the identity; two tasks of 32 sites per wave and round
+        const S *gs = (p ? in1 : in0) + r * fs, *go = (p ? in0 : in1) + r * fs;
+        const float2 *ds = (p ? dl1 : dl0) + r * fs, *dn = (p ? dl0 : dl1) + r * fs, *lk = p ? links1 : links0;
+        const int site = lane & 31;
+        const bool valid = i0 + site < g.vh;
+        const int i = valid ? i0 + site : g.vh - 1;
         int x, y, z, t;
         eo_coords(g, p, i, x, y, z, t);
 #pragma unroll 1
-        for (int r = 0; r < nrhs; r++) {
-            cx<float> gv[12], hv[12];
-            transport_at<S>(gv, kp, in_same + r * fs, in_other + r * fs, links, g, i, x, y, z, t);
-            transport_at<float2>(hv, kbar, dl_same + r * fs, dl_other + r * fs, links, g, i, x, y, z, t);
+        for (int rd = 0; rd < 3; rd++) {
+            const int task = 8 * rd + 2 * w + (lane >> 5);
+            if (task >= 18) continue;
+            const bool isg = task < 8 || task == 16;
+            const int k = task < 16 ? (task & 7) + 1 : 0;
+            const int kbar = k == 0 ? 0 : (k <= 4 ? k + 4 : k - 4);
+            cx<float> v[12];
+            if (isg)
+                transport_at<S>(v, k, gs, go, lk, g, i, x, y, z, t);
+            else
+                transport_at<float2>(v, kbar, ds, dn, lk, g, i, x, y, z, t);
+            float *M = (isg ? G : H) + 8 * k * kGStride + site;
 #pragma unroll
             for (int a = 0; a < 4; a++)
 #pragma unroll
-                for (int b = 0; b < 4; b++) {
-                    double re = acc[2 * (4 * a + b)], im = acc[2 * (4 * a + b) + 1];
-#pragma unroll
-                    for (int c = 0; c < 3; c++) {
-                        // h_a conj(g_b)
-                        const double hr = hv[3 * a + c].r, hi = hv[3 * a + c].i;
-                        const double gr = gv[3 * b + c].r, gi = gv[3 * b + c].i;
-                        re = fma(hr, gr, re);
-                        re = fma(hi, gi, re);
-                        im = fma(hi, gr, im);
-                        im = fma(-hr, gi, im);
-                    }
-                    acc[2 * (4 * a + b)] = re;
-                    acc[2 * (4 * a + b) + 1] = im;
+                for (int c = 0; c < 3; c++) {
+                    M[(2 * a) * kGStride + kGS * c] = valid ? v[3 * a + c].r : 0.f;
+                    M[(2 * a + 1) * kGStride + kGS * c] = valid ? v[3 * a + c].i : 0.f;
                 }
         }
-    }
-    __shared__ double red[kBlock / 64][32];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        __syncthreads();
+#pragma unroll 2
+        for (int q = 0; q < 3 * kGS / 4; q++) {
+            const int at = n * kGStride + 4 * q + grp;
+            const double a0 = H[16 * w * kGStride + at], a4 = H[64 * kGStride + at];
+            double b[5];
 #pragma unroll
-    for (int q = 0; q < 32; q++) {
-        const double v = wave_sum(acc[q]);
-        if (lane == 0) red[w][q] = v;
+            for (int c = 0; c < 5; c++) b[c] = G[16 * c * kGStride + at];
+            const double bw = G[16 * w * kGStride + at];
+#pragma unroll
+            for (int c = 0; c < 5; c++) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b[c], acc[c], 0, 0, 0);
+            acc[5] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4, bw, acc[5], 0, 0, 0);
+            if (w == 0) acc[6] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4, b[4], acc[6], 0, 0, 0);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x < 32) {
-        double s = 0;
-        for (int ww = 0; ww < kBlock / 64; ww++) s += red[ww][threadIdx.x];
-        part[((size_t)pair * gridDim.x + blockIdx.x) * 32 + threadIdx.x] = s;
+    // part[block][tile row * 5 + tile column][16][16]
+    double *out = part + (size_t)blockIdx.x * kGTiles * 256;
+#pragma unroll
+    for (int q = 0; q < 7; q++) {
+        if (q == 6 && w) break;
+        const int tile = q < 5 ? 5 * w + q : q == 5 ? 20 + w : 24;
+#pragma unroll
+        for (int v = 0; v < 4; v++) out[tile * 256 + (grp + 4 * v) * 16 + n] = acc[q][v];
     }
 }
 
-// dl/dA [81][16] complex from the partials of both parities, fixed order
-__global__ void k_ptc_grad_finish(const double *part0, const double *part1, int nblk, double2 *GA)
+// sum[seg][25 * 256]: the partials of the blocks seg, seg + kGradSeg, ... (fixed order)
+constexpr int kGradSeg = 8;
+__global__ __launch_bounds__(kBlock) void k_ptc_grad_sum(const double *part, int nblk, double *sum)
+{
+    const int e = blockIdx.x * kBlock + threadIdx.x;  // grid (25, kGradSeg)
+    double s = 0;
+#pragma unroll 8
+    for (int b = blockIdx.y; b < nblk; b += kGradSeg) s += part[(size_t)b * kGTiles * 256 + e];
+    sum[blockIdx.y * kGTiles * 256 + e] = s;
+}
+
+// dl/dA [81][16] complex from the sums
+__global__ void k_ptc_grad_finish(const double *sum, double2 *GA)
 {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;  // pair * 16 + element
     if (idx >= 81 * 16) return;
     const int pair = idx / 16, el = idx % 16;
-    double re = 0, im = 0;
-    for (int b = 0; b < nblk; b++) {
-        re += part0[((size_t)pair * nblk + b) * 32 + 2 * el];
-        im += part0[((size_t)pair * nblk + b) * 32 + 2 * el + 1];
-    }
-    for (int b = 0; b < nblk; b++) {
-        re += part1[((size_t)pair * nblk + b) * 32 + 2 * el];
-        im += part1[((size_t)pair * nblk + b) * 32 + 2 * el + 1];
-    }
-    GA[idx] = make_double2(re, im);
+    const int R = 2 * (4 * (pair / 9) + el / 4), C = 2 * (4 * (pair % 9) + el % 4);
+    auto P = [&](int i, int j) {
+        double s = 0;
+        for (int q = 0; q < kGradSeg; q++)
+            s += sum[(q * kGTiles + (i / 16) * 5 + j / 16) * 256 + (i % 16) * 16 + j % 16];
+        return s;
+    };
+    GA[idx] = make_double2(P(R, C) + P(R + 1, C + 1), P(R + 1, C) - P(R, C + 1));
 }
 
 struct AdamArgs {
@@ -621,20 +670,23 @@ void loss_grad_t(tm_ctx *c, LossKind kind, double epsp, const void *r_e, const v
             TM_HIP(hipGetLastError());
         }
     }
-    hipLaunchKernelGGL(k_ptc_loss_finish, dim3(1), dim3(64), 0, s, (const double *)part[0], (const double *)part[1],
+    hipLaunchKernelGGL(k_ptc_loss_finish, dim3(1), dim3(kBlock), 0, s, (const double *)part[0], (const double *)part[1],
                        en2, nbd, nrhs, loss);
     TM_HIP(hipGetLastError());
-    double *gp[2] = {(double *)ws_get(c, "ptc_gpart0", sizeof(double) * 81 * kGradBlocks * 32),
-                     (double *)ws_get(c, "ptc_gpart1", sizeof(double) * 81 * kGradBlocks * 32)};
     const S *rr[2] = {(const S *)r_e, (const S *)r_o};
-    const int nb = std::min(kGradBlocks, site_blocks(c));
-    for (int p = 0; p < 2; p++) {
-        hipLaunchKernelGGL(k_ptc_grad<S>, dim3(nb, 81), dim3(kBlock), 0, s, rr[p], rr[1 - p], (const float2 *)dl[p],
-                           (const float2 *)dl[1 - p], (const float2 *)c->links32[p], c->geo, p, nrhs, gp[p]);
-        TM_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_ptc_grad_finish, dim3((81 * 16 + 255) / 256), dim3(256), 0, s, (const double *)gp[0],
-                       (const double *)gp[1], nb, (double2 *)ws_get(c, "ptc_GA", sizeof(double2) * 81 * 16));
+    const int tiles = (c->geo.vh + kGS - 1) / kGS;
+    TM_REQUIRE(2L * tiles * nrhs <= 0x7fffffffL, "batch too large for the gradient grid");
+    const int nb = (int)std::min<long>(kGradBlocks, 2L * tiles * nrhs);
+    double *part_g = (double *)ws_get(c, "ptc_gpart", sizeof(double) * kGradBlocks * kGTiles * 256);
+    double *sum_g = (double *)ws_get(c, "ptc_gsum", sizeof(double) * kGradSeg * kGTiles * 256);
+    hipLaunchKernelGGL(k_ptc_grad<S>, dim3(nb), dim3(kBlock), 0, s, rr[0], rr[1], (const float2 *)dl[0],
+                       (const float2 *)dl[1], (const float2 *)c->links32[0], (const float2 *)c->links32[1], c->geo,
+                       nrhs, tiles, part_g);
+    TM_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_ptc_grad_sum, dim3(kGTiles, kGradSeg), dim3(kBlock), 0, s, (const double *)part_g, nb, sum_g);
+    TM_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_ptc_grad_finish, dim3((81 * 16 + 255) / 256), dim3(256), 0, s, (const double *)sum_g,
+                       (double2 *)ws_get(c, "ptc_GA", sizeof(double2) * 81 * 16));
     TM_HIP(hipGetLastError());
 }
 
