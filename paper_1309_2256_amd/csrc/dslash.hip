@@ -42,12 +42,14 @@ constexpr int kBlock = 256;  // four waves, one per direction mu
 constexpr int kSites = 64;   // output half-sites of a block
 // resident blocks per CU (and waves per SIMD) requested from the compiler:
 // bounded by the LDS exchange (24 KB per block in FP32, 48 KB in FP64, of
-// 160 KB) and by the registers (512 / waves per lane)
+// 160 KB) and by the registers (512 / waves per lane).  FP16 spinors, 32^3 x 64,
+// 12 right-hand sides: normal operator 2026 us with five, 1974 with six.  FP32
+// and BF16 spill with five.
 template <typename SS, typename LS, typename T, bool ONE = false>
 constexpr int waves_for()
 {
     if (sizeof(T) == 8) return ONE && !std::is_same<LS, L8D>::value ? 4 : 3;
-    return std::is_same<SS, h2>::value && !std::is_same<LS, float2>::value ? 5 : 4;
+    return std::is_same<SS, h2>::value && !std::is_same<LS, float2>::value ? 6 : 4;
 }
 
 // 16-byte aligned so that an array of records keeps every complex field
@@ -639,13 +641,6 @@ __device__ __forceinline__ void load_half_spinor(rawc<L> p[6], rsrc_t sr, int vb
     }
 }
 
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
-}
-
 // value as stored in precision SS (what later kernels will read)
 template <typename SS, typename T>
 __device__ __forceinline__ cx<T> stored(cx<T> v)
@@ -693,7 +688,15 @@ struct Exchange {
     }
     // (w0, w1): one 16-byte access in FP32, one each in FP64
     alignas(16) cx<T> w[sizeof(T) == 4 ? 1 : 2][slots][kSites][sizeof(T) == 4 ? 2 : 1];
-    double norm[2][3][kSites];  // [quantity][colour][site]
+    // norm q of colour c in lane `lane`: the summing wave of that colour leaves
+    // it in the slot of direction 3 that only it reads and only wave 3 writes,
+    // and wave 3 sums the colours before its next hops.  Without memory of
+    // their own six FP32 blocks fit a CU instead of five.
+    typedef double __attribute__((may_alias)) lane_norm;
+    __device__ __forceinline__ lane_norm &norm(int q, int c, int lane)
+    {
+        return reinterpret_cast<lane_norm *>(w[0][first(3) + c][lane])[q];
+    }
 };
 template <int DIR, int A, bool KEEP>
 __device__ __forceinline__ void put_comp(Exchange<double, KEEP> &x, int lane, const cx<double> w[3], cx<double> &kept)
@@ -942,19 +945,19 @@ __device__ __forceinline__ void dslash_block(const DParams<T> &a, int bhw, int n
             }
             if constexpr (EPI != EPI_STORE) {
 #pragma unroll
-                for (int q = 0; q < NQ; q++) ex.norm[q][c][lane] = valid ? nrm[q] : 0.0;
+                for (int q = 0; q < NQ; q++) ex.norm(q, c, lane) = valid ? nrm[q] : 0.0;
             }
         }
         if constexpr (!ONE || EPI != EPI_STORE) lds_barrier();
         if constexpr (EPI != EPI_STORE) {
             // the wave without a colour sums the block's norms (fixed order)
-            // while the others go on; they reach ex.norm again only past the
-            // next barrier
+            // while the others go on; they reach the norms' slots again only
+            // past the next barrier
             if (mu == 3) {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) {
                     if (q == 1 && !track_rho) break;
-                    const double s = wave_sum(ex.norm[q][0][lane] + ex.norm[q][1][lane] + ex.norm[q][2][lane]);
+                    const double s = cgdev::wave_sum(ex.norm(q, 0, lane) + ex.norm(q, 1, lane) + ex.norm(q, 2, lane));
                     if (lane == 0) cgdev::st_coh(a.part + ((size_t)q * a.nrhs + r) * a.nblk + sblk, s);
                 }
             }
