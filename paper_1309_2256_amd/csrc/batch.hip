@@ -22,7 +22,7 @@ struct tm_batch {
     int device = 0;
     std::string err;
     hipStream_t stream = nullptr;  // own stream (graph capture needs a non-null stream)
-    MultiDslash md[4];
+    MultiDslash md[4][kCgRing];  // stages per ring position (1 and 2; 3 and 4 at position 0)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<int> graph_set;  // instances captured in the current graph
@@ -85,14 +85,16 @@ void prepare_stages(tm_batch *b, std::vector<Solver> &S, const std::vector<int> 
 {
     std::vector<tm_ctx *> cs;
     for (int i : set) cs.push_back(S[i].c);
-    for (int k = 0; k < 4; k++) {
-        std::vector<DslashCall> dcs;
-        for (int i : set) dcs.push_back(S[i].stage(k + 1));
-        multi_dslash_prepare(b->md[k], cs, dcs, rpb, b->stream);
-    }
+    for (int k = 0; k < 4; k++)
+        for (int pos = 0; pos < (k < 2 ? S[set[0]].w.ring.m : 1); pos++) {
+            std::vector<DslashCall> dcs;
+            for (int i : set) dcs.push_back(S[i].stage(k + 1, pos));
+            multi_dslash_prepare(b->md[k][pos], cs, dcs, rpb, b->stream);
+        }
 }
 
-void launch_iteration(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set)
+// the it-th iteration of a group (a group starts at position 0 of the ring)
+void launch_iteration(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int it)
 {
     hipStream_t s = b->stream;
     if (b->single_launches) {
@@ -101,14 +103,15 @@ void launch_iteration(tm_batch *b, std::vector<Solver> &S, const std::vector<int
     }
     std::vector<CgTail> t;
     for (int i : set)
-        t.push_back(CgTail{S[i].c, S[i].w.dsc, S[i].w.partq, S[i].w.partb, S[i].nsb, S[i].nrhs, S[i].delta, S[i].w.p,
-                           S[i].w.r, S[i].w.x});
-    multi_dslash_launch(b->md[0], s);
-    multi_dslash_launch(b->md[1], s);
-    cg_finish_alpha_multi(t, s);
-    multi_dslash_launch(b->md[2], s);
-    multi_dslash_launch(b->md[3], s);
-    cg_tail_multi(t, S[set[0]].w.prec, S[set[0]].w.xprec, s);
+        t.push_back(CgTail{S[i].c, S[i].w.dsc, S[i].w.partq, S[i].w.partb, S[i].nsb, S[i].nrhs, S[i].delta,
+                           S[i].w.ring, S[i].w.r, S[i].w.x});
+    const int pos = it % S[set[0]].w.ring.m;
+    multi_dslash_launch(b->md[0][pos], s);
+    multi_dslash_launch(b->md[1][pos], s);
+    cg_finish_alpha_multi(t, pos, s);
+    multi_dslash_launch(b->md[2][0], s);
+    multi_dslash_launch(b->md[3][0], s);
+    cg_tail_multi(t, pos, S[set[0]].w.prec, S[set[0]].w.xprec, s);
 }
 
 // right-hand sides per Dslash block for the batch (results do not depend on it)
@@ -127,7 +130,7 @@ void build_graph(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &se
     if (!b->single_launches) prepare_stages(b, S, set, choose_rpb(S, set));
     TM_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     try {
-        for (int k = 0; k < iters; k++) launch_iteration(b, S, set);
+        for (int k = 0; k < iters; k++) launch_iteration(b, S, set, k);
     } catch (...) {
         hipGraph_t g = nullptr;
         (void)hipStreamEndCapture(b->stream, &g);
@@ -165,7 +168,8 @@ bool run_persist(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &se
         for (int i : set) {
             PersistInst q;
             q.c = S[i].c;
-            for (int k = 0; k < 4; k++) q.st[k] = S[i].stage(k + 1);
+            for (int k = 0; k < 4; k++) q.st[k] = S[i].stage(k + 1, 0);
+            q.ring = S[i].w.ring;
             q.x = S[i].w.x;
             q.sc = S[i].w.dsc;
             q.delta = S[i].delta;
@@ -186,6 +190,11 @@ void run_batch(tm_batch *b, std::vector<Solver> &S)
 {
     const int K = S[0].check_every;
     for (auto &x : S) TM_REQUIRE(x.check_every == K && x.lp == S[0].lp, "batched solves share precision and cadence");
+    // one ring length for all (a solve without the memory for a ring has 1)
+    int m = S[0].w.ring.m;
+    for (auto &x : S)
+        if (x.w.ring.m != m) m = 1;
+    for (auto &x : S) x.w.ring.m = m;
     while (true) {
         std::vector<int> set;
         for (int i = 0; i < (int)S.size(); i++)
@@ -202,6 +211,12 @@ void run_batch(tm_batch *b, std::vector<Solver> &S)
             }
             continue;
         }
+        // a group starts at position 0 of the ring
+        for (int i : set)
+            if (S[i].w.pos != 0) {
+                S[i].end_round(b->stream);
+                drop_graph(b);
+            }
         // the grouped iterations are accounted per instance below, not per
         // recorded launch (a graph is recorded once and replayed)
         for (int i : set) S[i].c->acct_pause++;
@@ -228,7 +243,7 @@ void run_batch(tm_batch *b, std::vector<Solver> &S)
             }
             if (!ran && b->eager) {
                 if (!b->single_launches) prepare_stages(b, S, set, choose_rpb(S, set));
-                for (int k = 0; k < K; k++) launch_iteration(b, S, set);
+                for (int k = 0; k < K; k++) launch_iteration(b, S, set, k);
             } else if (!ran) {
                 if (b->graph_set != set || b->graph_iters != K) build_graph(b, S, set, K);
                 if (timing) TM_HIP(hipEventRecord(b->ev[0], b->stream));  // graph set-up not timed

@@ -112,9 +112,9 @@ __global__ __launch_bounds__(kBlock) void k_finish_sum(const double *part, int n
 }
 
 // part layout: [rhs][nblk] (one slot)
-__global__ __launch_bounds__(kBlock) void k_finish_alpha(CGScalars *sc, const double *part, int nblk)
+__global__ __launch_bounds__(kBlock) void k_finish_alpha(CGScalars *sc, const double *part, int nblk, int pos)
 {
-    cgdev::finish_alpha(sc, part, nblk, blockIdx.x);
+    cgdev::finish_alpha(sc, part, nblk, pos, blockIdx.x);
 }
 
 // part layout: [slot 0: |r|^2 for all rhs][slot 1: |rho|^2 for all rhs]
@@ -124,13 +124,31 @@ __global__ __launch_bounds__(kBlock) void k_finish_beta(CGScalars *sc, const dou
     cgdev::finish_beta(sc, part, nblk, nrhs, delta, blockIdx.x);
 }
 
-// x += alpha p; p = r + beta p  (the solution update of this iteration folded
-// into the search-direction update; both use the p that produced q)
-template <typename S, typename XS>
-__global__ __launch_bounds__(kBlock) void k_update_px(S *p, const S *rv, XS *x, size_t n, const CGScalars *sc)
+template <typename S>
+__global__ __launch_bounds__(kBlock) void k_update_p(S *pout, const S *pin, const S *rv, size_t n, const CGScalars *sc)
 {
-    cgdev::update_px(p, rv, x, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
-                     (size_t)gridDim.x * kBlock);
+    cgdev::update_p(pout, pin, rv, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
+                    (size_t)gridDim.x * kBlock);
+}
+
+struct RingArg {
+    void *p[kCgRing];
+    __device__ void *operator[](int q) const { return p[q]; }
+};
+
+template <int M, typename S, typename XS>
+__global__ __launch_bounds__(kBlock) void k_update_px(const RingArg ring, const S *rv, XS *x, size_t n,
+                                                      const CGScalars *sc)
+{
+    cgdev::update_px<M, S>(ring, rv, x, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
+                           (size_t)gridDim.x * kBlock);
+}
+
+template <typename S, typename XS>
+__global__ __launch_bounds__(kBlock) void k_flush_x(const RingArg ring, int cnt, XS *x, size_t n, const CGScalars *sc)
+{
+    cgdev::flush_x<S>(ring, cnt, x, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
+                      (size_t)gridDim.x * kBlock);
 }
 
 // Several lattices per launch (a batch iteration).  Scalar kernels: block b
@@ -142,14 +160,14 @@ template <typename S, typename XS>
 struct TailArgs {
     CGScalars *sc[kTailInst];
     const double *part[kTailInst];
-    S *p[kTailInst];
+    RingArg ring[kTailInst];
     const S *r[kTailInst];
     XS *x[kTailInst];
     size_t n[kTailInst];
     double delta[kTailInst];
     int nblk[kTailInst], nrhs[kTailInst], gx[kTailInst];
     int rstart[kTailInst + 1], ustart[kTailInst + 1];
-    int ninst;
+    int ninst, pos;
 };
 static_assert(sizeof(TailArgs<double2, double2>) <= 4096, "kernel arguments exceed 4 KiB");
 
@@ -164,7 +182,7 @@ template <typename S, typename XS>
 __global__ __launch_bounds__(kBlock) void k_finish_alpha_multi(const TailArgs<S, XS> a)
 {
     const int i = tail_inst(a.rstart, a.ninst, blockIdx.x);
-    cgdev::finish_alpha(a.sc[i], a.part[i], a.nblk[i], blockIdx.x - a.rstart[i]);
+    cgdev::finish_alpha(a.sc[i], a.part[i], a.nblk[i], a.pos, blockIdx.x - a.rstart[i]);
 }
 
 template <typename S, typename XS>
@@ -174,14 +192,19 @@ __global__ __launch_bounds__(kBlock) void k_finish_beta_multi(const TailArgs<S, 
     cgdev::finish_beta(a.sc[i], a.part[i], a.nblk[i], a.nrhs[i], a.delta[i], blockIdx.x - a.rstart[i]);
 }
 
-template <typename S, typename XS>
-__global__ __launch_bounds__(kBlock) void k_update_px_multi(const TailArgs<S, XS> a)
+// M = 0: a position before the last of the ring
+template <int M, typename S, typename XS>
+__global__ __launch_bounds__(kBlock) void k_update_multi(const TailArgs<S, XS> a)
 {
     const int i = tail_inst(a.ustart, a.ninst, blockIdx.x);
     const int local = blockIdx.x - a.ustart[i], gx = a.gx[i];
     const int r = local / gx, bx = local - r * gx;
-    cgdev::update_px(a.p[i], a.r[i], a.x[i], a.n[i], a.sc[i], r, (size_t)bx * kBlock + threadIdx.x, a.n[i],
-                     (size_t)gx * kBlock);
+    const size_t e0 = (size_t)bx * kBlock + threadIdx.x, step = (size_t)gx * kBlock;
+    if constexpr (M == 0)
+        cgdev::update_p((S *)a.ring[i][a.pos + 1], (const S *)a.ring[i][a.pos], a.r[i], a.n[i], a.sc[i], r, e0, a.n[i],
+                        step);
+    else
+        cgdev::update_px<M, S>(a.ring[i], a.r[i], a.x[i], a.n[i], a.sc[i], r, e0, a.n[i], step);
 }
 
 // complex elements of one right-hand side of a half field, pads included
@@ -266,9 +289,10 @@ void launch_axpby_to_host(tm_ctx *c, void *out, const void *x, const void *y, in
 }
 
 template <typename S, typename XS>
-static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t i1, bool beta)
+static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t i1, int pos, bool beta)
 {
     TailArgs<S, XS> a{};
+    a.pos = pos;
     a.ninst = (int)(i1 - i0);
     a.rstart[0] = a.ustart[0] = 0;
     for (size_t k = i0; k < i1; k++) {
@@ -276,7 +300,7 @@ static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t
         const CgTail &q = t[k];
         a.sc[j] = q.sc;
         a.part[j] = beta ? q.partb : q.partq;
-        a.p[j] = (S *)q.p;
+        std::copy(q.ring.p, q.ring.p + kCgRing, a.ring[j].p);
         a.r[j] = (const S *)q.r;
         a.x[j] = (XS *)q.x;
         a.n[j] = half_elems(q.c);
@@ -302,34 +326,53 @@ static void dispatch_tail(int prec, int xprec, F &&f)
     dispatch_prec(prec, [&](auto *tag) { f(tag, (float2 *)nullptr); });
 }
 
-void cg_finish_alpha_multi(const std::vector<CgTail> &t, hipStream_t s)
+// the kernel form of a ring position: 0 before the last one, else the ring's
+// length (FP64 solves update x in every iteration)
+template <typename S, typename F>
+static void ring_form(int m, int pos, F &&f)
+{
+    if constexpr (!std::is_same<S, double2>::value) {
+        if (pos < m - 1) return f(std::integral_constant<int, 0>{});
+        if (m == 8) return f(std::integral_constant<int, 8>{});
+        if (m == 4) return f(std::integral_constant<int, 4>{});
+        if (m == 2) return f(std::integral_constant<int, 2>{});
+    }
+    TM_REQUIRE(m == 1, "bad ring of search directions");
+    f(std::integral_constant<int, 1>{});
+}
+
+void cg_finish_alpha_multi(const std::vector<CgTail> &t, int pos, hipStream_t s)
 {
     for (size_t i0 = 0; i0 < t.size(); i0 += kTailInst) {
         const size_t i1 = std::min(t.size(), i0 + kTailInst);
-        const TailArgs<double2, double2> a = tail_args<double2, double2>(t, i0, i1, false);
+        const TailArgs<double2, double2> a = tail_args<double2, double2>(t, i0, i1, pos, false);
         hipLaunchKernelGGL((k_finish_alpha_multi<double2, double2>), dim3(a.rstart[a.ninst]), dim3(kBlock), 0, s,
                            a);
         TM_HIP(hipGetLastError());
     }
 }
 
-void cg_tail_multi(const std::vector<CgTail> &t, int prec, int xprec, hipStream_t s)
+void cg_tail_multi(const std::vector<CgTail> &t, int pos, int prec, int xprec, hipStream_t s)
 {
     for (size_t i0 = 0; i0 < t.size(); i0 += kTailInst) {
         const size_t i1 = std::min(t.size(), i0 + kTailInst);
         dispatch_tail(prec, xprec, [&](auto *ts, auto *tx) {
             using S = std::remove_pointer_t<decltype(ts)>;
             using XS = std::remove_pointer_t<decltype(tx)>;
-            const TailArgs<S, XS> a = tail_args<S, XS>(t, i0, i1, true);
+            const TailArgs<S, XS> a = tail_args<S, XS>(t, i0, i1, pos, true);
             hipLaunchKernelGGL((k_finish_beta_multi<S, XS>), dim3(a.rstart[a.ninst]), dim3(kBlock), 0, s, a);
             TM_HIP(hipGetLastError());
-            hipLaunchKernelGGL((k_update_px_multi<S, XS>), dim3(a.ustart[a.ninst]), dim3(kBlock), 0, s, a);
+            auto go = [&](auto m) {
+                hipLaunchKernelGGL((k_update_multi<m(), S, XS>), dim3(a.ustart[a.ninst]), dim3(kBlock), 0, s, a);
+            };
+            ring_form<S>(t[i0].ring.m, pos, go);
             TM_HIP(hipGetLastError());
         });
         for (size_t k = i0; k < i1; k++) {
-            const size_t n = half_elems(t[k].c);
-            account(t[k].c, (double)n * t[k].nrhs * (3 * prec_bytes(prec) + 2 * prec_bytes(xprec)),
-                    8.0 * n * t[k].nrhs);
+            double b, f;
+            cg_update_cost(t[k].ring, pos, prec, xprec, b, f);
+            const double n = (double)half_elems(t[k].c) * t[k].nrhs;
+            account(t[k].c, n * b, n * f);
         }
     }
 }
@@ -365,9 +408,9 @@ void launch_norm2(tm_ctx *c, const void *v, int prec, int nrhs, double *dev_out,
     TM_HIP(hipGetLastError());
 }
 
-void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, hipStream_t s)
+void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, int pos, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finish_alpha, dim3(nrhs), dim3(kBlock), 0, s, sc, part, nblk);
+    hipLaunchKernelGGL(k_finish_alpha, dim3(nrhs), dim3(kBlock), 0, s, sc, part, nblk, pos);
     TM_HIP(hipGetLastError());
 }
 
@@ -405,24 +448,49 @@ void launch_axpy_dev(tm_ctx *c, void *y, int yprec, const void *x, int xprec, in
     TM_HIP(hipGetLastError());
 }
 
-void cg_update_px(tm_ctx *c, void *p, const void *r, void *x, int prec, int xprec, int nrhs, const CGScalars *sc,
-                  hipStream_t s)
+void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &bytes, double &flops)
 {
-    size_t n = half_elems(c);
+    const bool end = pos == ring.m - 1;
+    bytes = (end ? ring.m + 2 : 3) * prec_bytes(prec) + (end ? 2 * prec_bytes(xprec) : 0);
+    flops = end ? 4.0 * ring.m + 4 : 4.0;
+}
+
+void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,
+               const CGScalars *sc, hipStream_t s)
+{
+    const size_t n = half_elems(c);
     dim3 grid(grid_for(n), nrhs);
-    // reads p, r, x; writes p, x; x += alpha p and p = r + beta p
-    account(c, (double)n * nrhs * (3 * prec_bytes(prec) + 2 * prec_bytes(xprec)), 8.0 * n * nrhs);
-    if (prec == TM_F64) {
-        TM_REQUIRE(xprec == TM_F64, "FP64 CG needs an FP64 solution vector");
-        hipLaunchKernelGGL((k_update_px<double2, double2>), grid, dim3(kBlock), 0, s, (double2 *)p,
-                           (const double2 *)r, (double2 *)x, n, sc);
-    } else {
-        TM_REQUIRE(xprec == TM_F32, "low-precision CG accumulates in FP32");
-        dispatch_prec(prec, [&](auto *tag) {
-            using S = std::remove_pointer_t<decltype(tag)>;
-            hipLaunchKernelGGL((k_update_px<S, float2>), grid, dim3(kBlock), 0, s, (S *)p, (const S *)r,
-                               (float2 *)x, n, sc);
+    double b, f;
+    cg_update_cost(ring, pos, prec, xprec, b, f);
+    account(c, b * n * nrhs, f * n * nrhs);
+    RingArg a;
+    std::copy(ring.p, ring.p + kCgRing, a.p);
+    dispatch_tail(prec, xprec, [&](auto *ts, auto *tx) {
+        using S = std::remove_pointer_t<decltype(ts)>;
+        using XS = std::remove_pointer_t<decltype(tx)>;
+        ring_form<S>(ring.m, pos, [&](auto m) {
+            if constexpr (m() == 0)
+                hipLaunchKernelGGL(k_update_p<S>, grid, dim3(kBlock), 0, s, (S *)ring.p[pos + 1],
+                                   (const S *)ring.p[pos], (const S *)r, n, sc);
+            else
+                hipLaunchKernelGGL((k_update_px<m(), S, XS>), grid, dim3(kBlock), 0, s, a, (const S *)r, (XS *)x, n,
+                                   sc);
         });
-    }
+    });
+    TM_HIP(hipGetLastError());
+}
+
+void cg_flush(tm_ctx *c, const CgRing &ring, int cnt, void *x, int prec, int xprec, int nrhs, const CGScalars *sc,
+              hipStream_t s)
+{
+    const size_t n = half_elems(c);
+    account(c, (double)n * nrhs * (cnt * prec_bytes(prec) + 2 * prec_bytes(xprec)), 4.0 * cnt * n * nrhs);
+    RingArg a;
+    std::copy(ring.p, ring.p + kCgRing, a.p);
+    dispatch_tail(prec, xprec, [&](auto *ts, auto *tx) {
+        using S = std::remove_pointer_t<decltype(ts)>;
+        using XS = std::remove_pointer_t<decltype(tx)>;
+        hipLaunchKernelGGL((k_flush_x<S, XS>), dim3(grid_for(n), nrhs), dim3(kBlock), 0, s, a, cnt, (XS *)x, n, sc);
+    });
     TM_HIP(hipGetLastError());
 }

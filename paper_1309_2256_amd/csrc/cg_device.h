@@ -96,8 +96,9 @@ __device__ __forceinline__ double sum_partials(const double *part, int nblk, int
 
 __device__ __forceinline__ bool finite(double v) { return v == v && v - v == 0; }
 
-// alpha = |r|^2 / |q|^2 of right-hand side r; part layout [rhs][nblk]
-__device__ __forceinline__ void finish_alpha(CGScalars *sc, const double *part, int nblk, int r)
+// alpha = |r|^2 / |q|^2 of right-hand side r, also kept for ring position pos;
+// part layout [rhs][nblk]
+__device__ __forceinline__ void finish_alpha(CGScalars *sc, const double *part, int nblk, int pos, int r)
 {
     // the scalars' loads overlap those of the sum
     CGScalars &s = sc[r];
@@ -107,7 +108,9 @@ __device__ __forceinline__ void finish_alpha(CGScalars *sc, const double *part, 
     if (threadIdx.x == 0) {
         st_coh(&s.qq, qq);
         if (!finite(qq) || !finite(rr)) st_coh(&s.bad, 1);
-        st_coh(&s.alpha, (active && qq > 0 && finite(qq)) ? rr / qq : 0.0);
+        const double alpha = (active && qq > 0 && finite(qq)) ? rr / qq : 0.0;
+        st_coh(&s.alpha, alpha);
+        st_coh(&s.hist[pos], alpha);
     }
 }
 
@@ -149,30 +152,86 @@ __device__ __forceinline__ void finish_beta(CGScalars *sc, const double *part, i
     }
 }
 
-// x += alpha p; p = r + beta p for elements [e0, e1) of right-hand side r
-// (n complex per right-hand side), with the element stride `step` between a
-// thread's elements (the solution update of this iteration folded into the
-// search-direction update; both use the p that produced q).  Elementwise:
-// any split of the range gives the same result.
-template <typename S, typename XS>
-__device__ __forceinline__ void update_px(S *p, const S *rv, XS *x, size_t n, const CGScalars *sc, int r,
+// The vector updates of one iteration for elements e0, e0 + step, ... < e1 of
+// right-hand side r (n complex per right-hand side).  Elementwise: any split of
+// the range gives the same result.
+
+// pout = rv + beta pin (the solution follows at the end of the ring)
+template <typename S>
+__device__ __forceinline__ void update_p(S *pout, const S *pin, const S *rv, size_t n, const CGScalars *sc, int r,
+                                         size_t e0, size_t e1, size_t step)
+{
+    using T = typename StoreTraits<S>::real;
+    if (!ld_coh(&sc[r].active)) return;
+    const T b = (T)ld_coh(&sc[r].beta);
+    const size_t base = (size_t)r * n;
+    for (size_t e = e0; e < e1; e += step) {
+        const cx<T> pv = ldT<T>(pin, base + e);
+        stT<T>(pout, base + e, ldT<T>(rv, base + e) + b * pv);
+    }
+}
+
+// x += hist[0] p[0] + ... + hist[M - 1] p[M - 1], one after the other; then
+// p[0] = rv + beta p[M - 1], or the last direction that moved x if the
+// right-hand side is no longer active.  ring: its M buffers (S *const *).
+template <int M, typename S, typename XS, typename R>
+__device__ __forceinline__ void update_px(const R &ring, const S *rv, XS *x, size_t n, const CGScalars *sc, int r,
                                           size_t e0, size_t e1, size_t step)
 {
     using T = typename StoreTraits<S>::real;
     using TX = typename StoreTraits<XS>::real;
-    const int active = ld_coh(&sc[r].active);
-    const double alpha = ld_coh(&sc[r].alpha);
-    if (!active && alpha == 0.0) return;
+    const bool active = ld_coh(&sc[r].active) != 0;
+    double h[M];
+    bool any = active;
+    int last = 0;
+#pragma unroll
+    for (int q = 0; q < M; q++) {
+        h[q] = ld_coh(&sc[r].hist[q]);
+        if (h[q] != 0.0) any = true, last = q;
+    }
+    if (!any) return;
     const T b = active ? (T)ld_coh(&sc[r].beta) : (T)0;
-    const TX ax = (TX)alpha;
-    const bool upd_p = active != 0;
     const size_t base = (size_t)r * n;
     for (size_t e = e0; e < e1; e += step) {
         const size_t k = base + e;
-        cx<T> pv = ldT<T>(p, k);
+        cx<T> pv[M];
+#pragma unroll
+        for (int q = 0; q < M; q++) pv[q] = ldT<T>((const S *)ring[q], k);
         cx<TX> xv = ldT<TX>(x, k);
-        stT<TX>(x, k, xv + ax * cx<TX>{(TX)pv.r, (TX)pv.i});
-        if (upd_p) stT<T>(p, k, ldT<T>(rv, k) + b * pv);
+        cx<T> pn = active ? ldT<T>(rv, k) + b * pv[M - 1] : pv[0];
+#pragma unroll
+        for (int q = 0; q < M; q++) {
+            if (active || h[q] != 0.0) xv = xv + (TX)h[q] * cx<TX>{(TX)pv[q].r, (TX)pv[q].i};
+            if (!active && q == last) pn = pv[q];
+        }
+        stT<TX>(x, k, xv);
+        if (active || last > 0) stT<T>((S *)ring[0], k, pn);
+    }
+}
+
+// an incomplete round of cnt directions: x as above, p[cnt] the current
+// direction of a right-hand side that is no longer active
+template <typename S, typename XS, typename R>
+__device__ __forceinline__ void flush_x(const R &ring, int cnt, XS *x, size_t n, const CGScalars *sc, int r,
+                                        size_t e0, size_t e1, size_t step)
+{
+    using T = typename StoreTraits<S>::real;
+    using TX = typename StoreTraits<XS>::real;
+    const bool active = ld_coh(&sc[r].active) != 0;
+    int last = 0;
+    for (int q = 0; q < cnt; q++)
+        if (ld_coh(&sc[r].hist[q]) != 0.0) last = q;
+    const size_t base = (size_t)r * n;
+    for (size_t e = e0; e < e1; e += step) {
+        const size_t k = base + e;
+        cx<TX> xv = ldT<TX>(x, k);
+        for (int q = 0; q < cnt; q++) {
+            const double h = ld_coh(&sc[r].hist[q]);
+            const cx<T> pv = ldT<T>((const S *)ring[q], k);
+            if (active || h != 0.0) xv = xv + (TX)h * cx<TX>{(TX)pv.r, (TX)pv.i};
+            if (!active && q == last) stT<T>((S *)ring[cnt], k, pv);
+        }
+        stT<TX>(x, k, xv);
     }
 }
 

@@ -1025,7 +1025,11 @@ __device__ __forceinline__ unsigned *bar_fail(unsigned *b) { return b + 17 * kBa
 // block would have to copy to per-lane scratch memory.
 template <typename T>
 struct PersistArgs {
-    DParams<T> st[4][kPersistInst];  // the stage forms of each instance
+    // the stage forms of each instance: rows 0.. stage 1 per ring position,
+    // kCgRing.. stage 2 per ring position, then stages 3 and 4
+    DParams<T> st[2 * kCgRing + 2][kPersistInst];
+    void *ring[kPersistInst][kCgRing];  // search directions, m of them
+    int m;
     void *x[kPersistInst];           // solution accumulator (FP32)
     CGScalars *sc[kPersistInst];
     double delta[kPersistInst];
@@ -1096,7 +1100,7 @@ __device__ __forceinline__ bool grid_sync(unsigned *bar, unsigned long long spin
     return ok != 0;
 }
 
-// One Dslash stage over the virtual blocks of all instances; stage index k.
+// One Dslash stage over the virtual blocks of all instances; row k of the forms.
 template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
 __device__ __forceinline__ void persist_stage(const PersistArgs<T> &a, int k)
 {
@@ -1115,7 +1119,7 @@ __device__ __forceinline__ void persist_stage(const PersistArgs<T> &a, int k)
 // The CG scalars of one right-hand side per block: alpha from the partial
 // sums of stage 2 (BETA = false) or beta and the flags from those of stage 4.
 template <typename T, bool BETA>
-__device__ __forceinline__ void persist_scalars(const PersistArgs<T> &a)
+__device__ __forceinline__ void persist_scalars(const PersistArgs<T> &a, int pos)
 {
     const int total = a.fstart[a.n];
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
@@ -1123,17 +1127,17 @@ __device__ __forceinline__ void persist_scalars(const PersistArgs<T> &a)
         while (i + 1 < a.n && w >= a.fstart[i + 1]) i++;
         const int r = w - a.fstart[i];
         if constexpr (BETA) {
-            const DParams<T> &p = a.st[3][i];
+            const DParams<T> &p = a.st[2 * kCgRing + 1][i];
             cgdev::finish_beta(a.sc[i], p.part, p.nblk, p.nrhs, a.delta[i], r);
         } else {
-            const DParams<T> &p = a.st[1][i];
-            cgdev::finish_alpha(a.sc[i], p.part, p.nblk, r);
+            const DParams<T> &p = a.st[kCgRing][i];
+            cgdev::finish_alpha(a.sc[i], p.part, p.nblk, pos, r);
         }
     }
 }
 
 template <typename SS, typename T>
-__device__ __forceinline__ void persist_update(const PersistArgs<T> &a)
+__device__ __forceinline__ void persist_update(const PersistArgs<T> &a, int pos)
 {
     const int total = a.ustart[a.n];
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
@@ -1141,12 +1145,23 @@ __device__ __forceinline__ void persist_update(const PersistArgs<T> &a)
         while (i + 1 < a.n && w >= a.ustart[i + 1]) i++;
         const int local = w - a.ustart[i];
         const int r = local / a.uchunks[i], ch = local - r * a.uchunks[i];
-        const DParams<T> &p0 = a.st[0][i];  // stage 1 reads p
-        const DParams<T> &p3 = a.st[3][i];  // stage 4 updates r
-        const size_t n = (size_t)12 * p0.g.hs;
+        const DParams<T> &p3 = a.st[2 * kCgRing + 1][i];  // stage 4 updates r
+        const size_t n = (size_t)12 * p3.g.hs;
         const size_t e0 = (size_t)ch * kUpdChunk, e1 = e0 + kUpdChunk < n ? e0 + kUpdChunk : n;
-        cgdev::update_px((SS *)p0.in, (const SS *)p3.r, (float2 *)a.x[i], n, a.sc[i], r, e0 + threadIdx.x, e1,
-                         (size_t)kBlock);
+        const SS *rv = (const SS *)p3.r;
+        float2 *x = (float2 *)a.x[i];
+        void *const *ring = a.ring[i];
+        if (pos < a.m - 1)
+            cgdev::update_p((SS *)ring[pos + 1], (const SS *)ring[pos], rv, n, a.sc[i], r, e0 + threadIdx.x, e1,
+                            (size_t)kBlock);
+        else if (a.m == 8)
+            cgdev::update_px<8, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+        else if (a.m == 4)
+            cgdev::update_px<4, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+        else if (a.m == 2)
+            cgdev::update_px<2, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+        else
+            cgdev::update_px<1, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
     }
 }
 
@@ -1156,19 +1171,19 @@ __global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T>())) void k_batch_pers
                                                                              unsigned long long spin_limit)
 {
     const PersistArgs<T> &a = *pa;
-    for (int it = 0; it < iters; it++) {
-        persist_stage<SS, LS, T, 0, 0, EPI_STORE>(a, 0);  // t = R_oo^-1 H_oe p
+    for (int it = 0, pos = 0; it < iters; it++, pos = pos + 1 == a.m ? 0 : pos + 1) {
+        persist_stage<SS, LS, T, 0, 0, EPI_STORE>(a, pos);            // t = R_oo^-1 H_oe p
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, 0, 1, EPI_NORM>(a, 1);   // q = R_ee p - H_eo t, |q|^2 partials
+        persist_stage<SS, LS, T, 0, 1, EPI_NORM>(a, kCgRing + pos);   // q = R_ee p - H_eo t, |q|^2 partials
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, 1, 0, EPI_STORE>(a, 2);  // t = R_oo^-1 H_oe^dag q
-        persist_scalars<T, false>(a);                       // alpha
+        persist_stage<SS, LS, T, 1, 0, EPI_STORE>(a, 2 * kCgRing);    // t = R_oo^-1 H_oe^dag q
+        persist_scalars<T, false>(a, pos);                            // alpha
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_stage<SS, LS, T, 0, 1, EPI_CG>(a, 3);     // r -= alpha Ahat^dag q, partials
+        persist_stage<SS, LS, T, 0, 1, EPI_CG>(a, 2 * kCgRing + 1);   // r -= alpha Ahat^dag q, partials
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_scalars<T, true>(a);                        // beta, flags
+        persist_scalars<T, true>(a, pos);                             // beta, flags
         if (!grid_sync(a.bar, spin_limit)) return;
-        persist_update<SS, T>(a);                           // x += alpha p, p = r + beta p
+        persist_update<SS, T>(a, pos);                                // p = r + beta p, at the ring's end x
         if (it + 1 < iters && !grid_sync(a.bar, spin_limit)) return;
     }
 }
@@ -1384,8 +1399,23 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     } else {
     PersistArgs<T> a{};
     a.n = (int)v.size();
+    a.m = v[0].ring.m;
     for (int k = 0; k < a.n; k++) {
-        for (int st = 0; st < 4; st++) a.st[st][k] = fill_params<SS, LS, T>(v[k].c, v[k].st[st], pb.rpb);
+        const CgRing &ring = v[k].ring;
+        TM_REQUIRE(ring.m == v[0].ring.m, "batched solves share the ring length");
+        std::copy(ring.p, ring.p + kCgRing, a.ring[k]);
+        auto form = [&](int stage, int pos) {
+            DslashCall dc = v[k].st[stage];
+            if (stage == 0) dc.in = ring.p[pos];
+            if (stage == 1) dc.own = ring.p[pos];
+            return fill_params<SS, LS, T>(v[k].c, dc, pb.rpb);
+        };
+        for (int pos = 0; pos < ring.m; pos++) {
+            a.st[pos][k] = form(0, pos);
+            a.st[kCgRing + pos][k] = form(1, pos);
+        }
+        a.st[2 * kCgRing][k] = form(2, 0);
+        a.st[2 * kCgRing + 1][k] = form(3, 0);
         const int nb = a.st[0][k].nblk * a.st[0][k].ngroups;
         a.start[k + 1] = a.start[k] + (nb + 7) / 8 * 8;
         const size_t n = (size_t)12 * v[k].c->geo.hs;

@@ -51,7 +51,10 @@ struct SolveOut {
 // CG work vectors of one solve (see runtime.hip)
 struct CGWork {
     int nrhs = 0, prec = 0;
-    void *q = nullptr, *p = nullptr, *r = nullptr, *rho = nullptr, *tmp = nullptr;
+    void *q = nullptr, *r = nullptr, *rho = nullptr, *tmp = nullptr;
+    CgRing ring;        // search directions, the current one at `pos`
+    int pos = 0;
+    void *&p() { return ring.p[pos]; }
     void *x = nullptr;  // solution accumulator: FP64 (plain) or FP32 (low precision)
     int xprec = 0;
     CGScalars *dsc = nullptr;
@@ -80,10 +83,15 @@ struct Solver {
     void init(tm_ctx *c, void *xe, void *xo, const void *be, const void *bo, int nrhs, const tm_solve_params &p,
               hipStream_t s);
     void iteration(hipStream_t s);       // one iteration, single-instance launches
-    DslashCall stage(int k) const;       // the k-th (1..4) half-Dslash of an iteration
+    // the k-th (1..4) half-Dslash of an iteration at ring position pos
+    DslashCall stage(int k, int pos) const;
     void iteration_tail(hipStream_t s);  // finish_beta + x/p update
+    // ends an incomplete round of the ring: x up to date, the current
+    // direction at position 0 (the ring's buffers change places)
+    void end_round(hipStream_t s);
     // algorithmic bytes and flops of one iteration (the four half-Dslash
-    // stages and the x/p update), as accounted by single-instance launches
+    // stages and the x/p update), as accounted by single-instance launches,
+    // on average over a round of the ring
     void iter_cost(double &bytes, double &flops) const;
     void count_iteration();
     bool due() const;

@@ -154,9 +154,10 @@ namespace {
 //   t = R^-1(-eps) g5 H^dag q;  s = R(-eps) q + kappa g5 H t,  D3, D4
 //     r -= alpha s, rho -= alpha q (+ partial |r|^2, |rho|^2)
 //   beta, convergence / update flags                            finish
-//   x += alpha p, p = r + beta p                                update
-DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage)
+//   p = r + beta p, at the end of the ring x += sum alpha p     update
+DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage, int pos)
 {
+    void *const p = w.ring.p[pos];
     const double k = c->kappa;
     DslashCall dc{};
     dc.nrhs = w.nrhs;
@@ -164,7 +165,7 @@ DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage)
     switch (stage) {
     case 1:
         dc.out = w.tmp;
-        dc.in = w.p;
+        dc.in = p;
         dc.out_parity = 1;
         dc.d_hop = sd_mul(sd_scalar(-k), sd_twist_inv(epsp));
         dc.d_own = sd_scalar(0);
@@ -172,7 +173,7 @@ DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage)
     case 2:
         dc.out = w.q;
         dc.in = w.tmp;
-        dc.own = w.p;
+        dc.own = p;
         dc.has_own = true;
         dc.d_own = sd_twist(epsp);
         dc.d_hop = sd_scalar(k);
@@ -273,9 +274,9 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
         w.r = r64;
         w.q = q64;
         w.tmp = t64;
-        w.p = ws_get(c, "s_p64", f64);
+        w.ring.p[0] = ws_get(c, "s_p64", f64);
         op_schur_dag(c, r64, rho64, t64, nrhs, TM_F64, epsp, s);
-        copy_field(w.p, r64, f64, s);
+        copy_field(w.p(), r64, f64, s);
         std::vector<double> rr = norms_host(c, r64, TM_F64, nrhs, s);
         std::vector<double> rho2 = norms_host(c, rho64, TM_F64, nrhs, s);
         for (int r = 0; r < nrhs; r++) {
@@ -297,8 +298,24 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
         w.rho = ws_get(c, "s_rho_lo", fl);
         w.r = ws_get(c, "s_r_lo", fl);
         w.q = ws_get(c, "s_q_lo", fl);
-        w.p = ws_get(c, "s_p_lo", fl);
+        w.ring.p[0] = ws_get(c, "s_p_lo", fl);
         w.tmp = ws_get(c, "s_t_lo", fl);
+        // the longest ring that ends at every check; without the memory for
+        // it x is updated in every iteration
+        w.ring.m = check_every % 8 == 0 ? 8 : check_every % 4 == 0 ? 4 : check_every % 2 == 0 ? 2 : 1;
+        static_assert(kCgRing == 8, "ring lengths");
+        if (w.ring.m > 1) {
+            try {
+                char *more = (char *)ws_get(c, "s_p_ring", fl * (w.ring.m - 1));
+                for (int q = 1; q < w.ring.m; q++) w.ring.p[q] = more + (q - 1) * fl;
+                // right-hand sides that do not iterate leave them unwritten,
+                // but the hop kernels read them
+                launch_zero(c, more, lp, nrhs * (w.ring.m - 1), s);
+            } catch (const TmError &e) {
+                if (e.status != TM_ERR_OOM) throw;
+                w.ring.m = 1;
+            }
+        }
         restart(true, s);
     }
     bool any = false;
@@ -327,7 +344,7 @@ void Solver::restart(bool first, hipStream_t s, bool reactivate)
         upload(dscale, hscale.data(), sizeof(double) * nrhs, s);
         launch_copy_convert(c, w.r, lp, r64, TM_F64, nrhs, dscale, s);
         launch_copy_convert(c, w.rho, lp, rho64, TM_F64, nrhs, dscale, s);
-        copy_field(w.p, w.r, fl, s);
+        copy_field(w.p(), w.r, fl, s);
     } else {
         // the true residual rho (FP64) enters the low-precision iteration at
         // unit RMS; r = Ahat^dag rho is formed at the iteration's precision
@@ -350,7 +367,7 @@ void Solver::restart(bool first, hipStream_t s, bool reactivate)
         launch_copy_convert(c, w.rho, lp, rho64, TM_F64, nrhs, dscale, s);
         for (int r = 0; r < nrhs; r++) hscale[r] = sig_new[r] / sigma[r];
         upload_async(c, 0, dscale, hscale.data(), sizeof(double) * nrhs, s);
-        launch_copy_convert(c, w.p, lp, w.p, lp, nrhs, dscale, s);
+        launch_copy_convert(c, w.p(), lp, w.p(), lp, nrhs, dscale, s);
     }
     launch_zero(c, w.x, TM_F32, nrhs, s);
     std::vector<double> rr = norms_host(c, w.r, lp, nrhs, s);
@@ -390,33 +407,46 @@ void Solver::accumulate(hipStream_t s)
 void Solver::iteration_tail(hipStream_t s)
 {
     cg_finish_beta(c, w.dsc, w.partb, nsb, nrhs, delta, s);
-    cg_update_px(c, w.p, w.r, w.x, w.prec, w.xprec, nrhs, w.dsc, s);
+    cg_update(c, w.ring, w.pos, w.r, w.x, w.prec, w.xprec, nrhs, w.dsc, s);
+    w.pos = (w.pos + 1) % w.ring.m;
+}
+
+void Solver::end_round(hipStream_t s)
+{
+    if (w.pos == 0) return;
+    cg_flush(c, w.ring, w.pos, w.x, w.prec, w.xprec, nrhs, w.dsc, s);
+    std::rotate(w.ring.p, w.ring.p + w.pos, w.ring.p + w.ring.m);
+    w.pos = 0;
 }
 
 void Solver::iteration(hipStream_t s)
 {
-    launch_dslash(c, stage_call(c, w, epsp, 1), s);
-    launch_dslash(c, stage_call(c, w, epsp, 2), s);
-    cg_finish_alpha(c, w.dsc, w.partq, nsb, nrhs, s);
-    launch_dslash(c, stage_call(c, w, epsp, 3), s);
-    launch_dslash(c, stage_call(c, w, epsp, 4), s);
+    launch_dslash(c, stage(1, w.pos), s);
+    launch_dslash(c, stage(2, w.pos), s);
+    cg_finish_alpha(c, w.dsc, w.partq, nsb, nrhs, w.pos, s);
+    launch_dslash(c, stage(3, w.pos), s);
+    launch_dslash(c, stage(4, w.pos), s);
     iteration_tail(s);
 }
 
-DslashCall Solver::stage(int k) const { return stage_call(c, w, epsp, k); }
+DslashCall Solver::stage(int k, int pos) const { return stage_call(c, w, epsp, k, pos); }
 
 void Solver::iter_cost(double &bytes, double &flops) const
 {
     bytes = flops = 0;
     for (int k = 1; k <= 4; k++) {
         double b, f;
-        dslash_cost(c, stage(k), b, f);
+        dslash_cost(c, stage(k, 0), b, f);
         bytes += b;
         flops += f;
     }
     const double n = 12.0 * c->geo.vh * nrhs;
-    bytes += n * (3 * prec_bytes(w.prec) + 2 * prec_bytes(w.xprec));
-    flops += 8.0 * n;
+    for (int q = 0; q < w.ring.m; q++) {
+        double b, f;
+        cg_update_cost(w.ring, q, w.prec, w.xprec, b, f);
+        bytes += n * b / w.ring.m;
+        flops += n * f / w.ring.m;
+    }
 }
 
 void Solver::count_iteration()
@@ -431,6 +461,7 @@ bool Solver::due() const { return since_check >= check_every || total >= p.maxit
 void Solver::check(hipStream_t s)
 {
     since_check = 0;
+    end_round(s);
     download(c, hsc.data(), w.dsc, sizeof(CGScalars) * nrhs, s);
     bool any_active = false, any_update = false, any_bad = false;
     for (auto &q : hsc) {

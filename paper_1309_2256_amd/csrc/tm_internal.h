@@ -468,6 +468,21 @@ void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const
 int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst);
 void multi_dslash_launch(const MultiDslash &m, hipStream_t s);
 
+// The low-precision solvers keep the search directions of up to kCgRing
+// iterations in a ring of buffers and add them to the FP32 solution x together,
+// in the order of the iterations (the same FP32 sums as one at a time): x and
+// the directions move (4 m - 1) / m low-precision and 2 / m FP32 accesses per
+// element and iteration instead of 3 and 2.  Bound: memory; FP16, 32^3 x 64, 12
+// right-hand sides: about 440 us per iteration for m = 8, 729 (5.8 TB/s) for
+// m = 1, a mixed solve of 157 iterations 601 ms against 646.
+constexpr int kCgRing = 8;
+// Ring of search directions: ring position q holds the direction of the q-th
+// iteration since x was last brought up to date.
+struct CgRing {
+    int m = 1;                      // 1, 2, 4 or 8
+    void *p[kCgRing] = {nullptr};
+};
+
 // Persistent batch: `iters` CG iterations of up to kPersistInst instances in
 // one cooperative launch (grid barriers between the stages, bounded waits);
 // solvers with FP32 arithmetic (FP32, FP16 or BF16 storage) only.
@@ -475,6 +490,7 @@ constexpr int kPersistInst = 4;
 struct PersistInst {
     tm_ctx *c = nullptr;
     DslashCall st[4];       // the four stage forms of one CG iteration
+    CgRing ring;            // directions (stages 1 and 2 read position 0 as given in st)
     void *x = nullptr;      // solution accumulator of the update
     CGScalars *sc = nullptr;
     double delta = 0;       // reliable-update threshold (0: none)
@@ -517,11 +533,12 @@ void launch_axpy_dev(tm_ctx *c, void *y, int yprec, const void *x, int xprec, in
 // per-rhs |v|^2 into dev_out[nrhs] (device doubles), deterministic
 void launch_norm2(tm_ctx *c, const void *v, int prec, int nrhs, double *dev_out, hipStream_t s);
 
-// CG building blocks (blas.hip; the iteration itself is in runtime.hip)
+// CG building blocks (blas.hip; the iteration itself is in runtime.hip).
 struct CGScalars {
     double rr;       // |r|^2 (normal residual)
     double qq;       // |Ahat p|^2
     double alpha, beta;
+    double hist[kCgRing];  // alpha per position of the ring
     double rho2;     // |rho|^2, iterated Schur residual
     double rho2_ref; // |rho|^2 at the last reliable update
     double target2;  // (tol |b|)^2 in the units of the vectors
@@ -532,12 +549,21 @@ struct CGScalars {
     int bad;         // NaN/Inf seen
 };
 
-void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, hipStream_t s);
+void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, int pos, hipStream_t s);
 void cg_finish_beta(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, double delta,
                     hipStream_t s);
-// x += alpha p; p = r + beta p
-void cg_update_px(tm_ctx *c, void *p, const void *r, void *x, int prec, int xprec, int nrhs, const CGScalars *sc,
-                  hipStream_t s);
+// position pos < m - 1: p[pos + 1] = r + beta p[pos]; last position:
+// x += sum_q hist[q] p[q], p[0] = r + beta p[m - 1].  A right-hand side that
+// is no longer active keeps its last direction, in p[0] from the end of the
+// ring on.
+void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,
+               const CGScalars *sc, hipStream_t s);
+// bytes and flops of cg_update per complex element at one position
+void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &bytes, double &flops);
+// x += sum of the first cnt directions, p[cnt] the current direction of every
+// right-hand side (an incomplete round of the ring)
+void cg_flush(tm_ctx *c, const CgRing &ring, int cnt, void *x, int prec, int xprec, int nrhs, const CGScalars *sc,
+              hipStream_t s);
 
 // The same scalar and vector steps for several lattices in one launch each
 // (a batch's iteration): per lattice its context, CG scalars, partial sums
@@ -551,12 +577,12 @@ struct CgTail {
     int nblk;             // partial-sum blocks
     int nrhs;
     double delta;
-    void *p;
+    CgRing ring;  // the same length for all lattices
     const void *r;
     void *x;
 };
-void cg_finish_alpha_multi(const std::vector<CgTail> &t, hipStream_t s);
-void cg_tail_multi(const std::vector<CgTail> &t, int prec, int xprec, hipStream_t s);  // beta, then x and p
+void cg_finish_alpha_multi(const std::vector<CgTail> &t, int pos, hipStream_t s);
+void cg_tail_multi(const std::vector<CgTail> &t, int pos, int prec, int xprec, hipStream_t s);  // beta, then x and p
 
 // ---------------------------------------------------------------- misc kernels
 
