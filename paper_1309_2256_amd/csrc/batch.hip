@@ -22,7 +22,7 @@ struct tm_batch {
     int device = 0;
     std::string err;
     hipStream_t stream = nullptr;  // own stream (graph capture needs a non-null stream)
-    MultiDslash md[4][kCgRing];  // stages per ring position (1 and 2; 3 and 4 at position 0)
+    MultiDslash md[4][kCgRing];  // stages per ring position (4: position 0 only)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<int> graph_set;  // instances captured in the current graph
@@ -86,7 +86,7 @@ void prepare_stages(tm_batch *b, std::vector<Solver> &S, const std::vector<int> 
     std::vector<tm_ctx *> cs;
     for (int i : set) cs.push_back(S[i].c);
     for (int k = 0; k < 4; k++)
-        for (int pos = 0; pos < (k < 2 ? S[set[0]].w.ring.m : 1); pos++) {
+        for (int pos = 0; pos < (k < 3 ? S[set[0]].w.ring.m : 1); pos++) {
             std::vector<DslashCall> dcs;
             for (int i : set) dcs.push_back(S[i].stage(k + 1, pos));
             multi_dslash_prepare(b->md[k][pos], cs, dcs, rpb, b->stream);
@@ -103,13 +103,12 @@ void launch_iteration(tm_batch *b, std::vector<Solver> &S, const std::vector<int
     }
     std::vector<CgTail> t;
     for (int i : set)
-        t.push_back(CgTail{S[i].c, S[i].w.dsc, S[i].w.partq, S[i].w.partb, S[i].nsb, S[i].nrhs, S[i].delta,
+        t.push_back(CgTail{S[i].c, S[i].w.dsc, S[i].w.partb, S[i].nsb, S[i].nrhs, S[i].delta,
                            S[i].w.ring, S[i].w.r, S[i].w.x});
     const int pos = it % S[set[0]].w.ring.m;
     multi_dslash_launch(b->md[0][pos], s);
     multi_dslash_launch(b->md[1][pos], s);
-    cg_finish_alpha_multi(t, pos, s);
-    multi_dslash_launch(b->md[2][0], s);
+    multi_dslash_launch(b->md[2][pos], s);
     multi_dslash_launch(b->md[3][0], s);
     cg_tail_multi(t, pos, S[set[0]].w.prec, S[set[0]].w.xprec, s);
 }

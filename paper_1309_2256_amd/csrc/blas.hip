@@ -111,12 +111,6 @@ __global__ __launch_bounds__(kBlock) void k_finish_sum(const double *part, int n
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// part layout: [rhs][nblk] (one slot)
-__global__ __launch_bounds__(kBlock) void k_finish_alpha(CGScalars *sc, const double *part, int nblk, int pos)
-{
-    cgdev::finish_alpha(sc, part, nblk, pos, blockIdx.x);
-}
-
 // part layout: [slot 0: |r|^2 for all rhs][slot 1: |rho|^2 for all rhs]
 __global__ __launch_bounds__(kBlock) void k_finish_beta(CGScalars *sc, const double *part, int nblk,
                                                         int nrhs, double delta)
@@ -151,7 +145,7 @@ __global__ __launch_bounds__(kBlock) void k_flush_x(const RingArg ring, int cnt,
                       (size_t)gridDim.x * kBlock);
 }
 
-// Several lattices per launch (a batch iteration).  Scalar kernels: block b
+// Several lattices per launch (a batch iteration).  Scalar kernel: block b
 // is right-hand side b - rstart[i] of lattice i.  Update: lattice i owns
 // blocks [ustart[i], ustart[i+1]) laid out as its single launch's
 // (gx[i] x nrhs) grid, so every element sees the same thread-stride loop.
@@ -176,13 +170,6 @@ __device__ __forceinline__ int tail_inst(const int *start, int n, int b)
     int i = 0;
     while (i + 1 < n && b >= start[i + 1]) i++;
     return i;
-}
-
-template <typename S, typename XS>
-__global__ __launch_bounds__(kBlock) void k_finish_alpha_multi(const TailArgs<S, XS> a)
-{
-    const int i = tail_inst(a.rstart, a.ninst, blockIdx.x);
-    cgdev::finish_alpha(a.sc[i], a.part[i], a.nblk[i], a.pos, blockIdx.x - a.rstart[i]);
 }
 
 template <typename S, typename XS>
@@ -289,7 +276,7 @@ void launch_axpby_to_host(tm_ctx *c, void *out, const void *x, const void *y, in
 }
 
 template <typename S, typename XS>
-static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t i1, int pos, bool beta)
+static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t i1, int pos)
 {
     TailArgs<S, XS> a{};
     a.pos = pos;
@@ -299,7 +286,7 @@ static TailArgs<S, XS> tail_args(const std::vector<CgTail> &t, size_t i0, size_t
         const int j = (int)(k - i0);
         const CgTail &q = t[k];
         a.sc[j] = q.sc;
-        a.part[j] = beta ? q.partb : q.partq;
+        a.part[j] = q.partb;
         std::copy(q.ring.p, q.ring.p + kCgRing, a.ring[j].p);
         a.r[j] = (const S *)q.r;
         a.x[j] = (XS *)q.x;
@@ -341,17 +328,6 @@ static void ring_form(int m, int pos, F &&f)
     f(std::integral_constant<int, 1>{});
 }
 
-void cg_finish_alpha_multi(const std::vector<CgTail> &t, int pos, hipStream_t s)
-{
-    for (size_t i0 = 0; i0 < t.size(); i0 += kTailInst) {
-        const size_t i1 = std::min(t.size(), i0 + kTailInst);
-        const TailArgs<double2, double2> a = tail_args<double2, double2>(t, i0, i1, pos, false);
-        hipLaunchKernelGGL((k_finish_alpha_multi<double2, double2>), dim3(a.rstart[a.ninst]), dim3(kBlock), 0, s,
-                           a);
-        TM_HIP(hipGetLastError());
-    }
-}
-
 void cg_tail_multi(const std::vector<CgTail> &t, int pos, int prec, int xprec, hipStream_t s)
 {
     for (size_t i0 = 0; i0 < t.size(); i0 += kTailInst) {
@@ -359,7 +335,7 @@ void cg_tail_multi(const std::vector<CgTail> &t, int pos, int prec, int xprec, h
         dispatch_tail(prec, xprec, [&](auto *ts, auto *tx) {
             using S = std::remove_pointer_t<decltype(ts)>;
             using XS = std::remove_pointer_t<decltype(tx)>;
-            const TailArgs<S, XS> a = tail_args<S, XS>(t, i0, i1, pos, true);
+            const TailArgs<S, XS> a = tail_args<S, XS>(t, i0, i1, pos);
             hipLaunchKernelGGL((k_finish_beta_multi<S, XS>), dim3(a.rstart[a.ninst]), dim3(kBlock), 0, s, a);
             TM_HIP(hipGetLastError());
             auto go = [&](auto m) {
@@ -405,12 +381,6 @@ void launch_norm2(tm_ctx *c, const void *v, int prec, int nrhs, double *dev_out,
     double *part = (double *)ws_get(c, "norm_part", sizeof(double) * nblk * nrhs);
     partial_norm2(c, v, prec, nrhs, part, nblk, s);
     hipLaunchKernelGGL(k_finish_sum, dim3(nrhs), dim3(kBlock), 0, s, (const double *)part, nblk, dev_out);
-    TM_HIP(hipGetLastError());
-}
-
-void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, int pos, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_finish_alpha, dim3(nrhs), dim3(kBlock), 0, s, sc, part, nblk, pos);
     TM_HIP(hipGetLastError());
 }
 

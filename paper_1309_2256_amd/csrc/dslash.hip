@@ -64,6 +64,7 @@ struct alignas(16) DParams {
     int p;          // output parity
     int nrhs;
     int rpb;        // right-hand sides per block
+    int alpha;      // see DslashCall
     int ngroups;    // right-hand-side groups, ceil(nrhs / rpb)
     cx<T> own_u, own_l, hop_u, hop_l;
     // +1, passed at run time so that the +-1 factors of the spin projection
@@ -966,10 +967,27 @@ __device__ __forceinline__ void dslash_block(const DParams<T> &a, int bhw, int n
     }
 }
 
+// The blocks past the launch's own nblk * ngroups, one per right-hand side:
+// alpha from the partial sums of an earlier launch, which the hops of this one
+// do not read.  A launch of its own cost 3 to 5 us in the chain of an
+// iteration.  True: block `over` had nothing else to do.
+template <int DAG, int OWN, int EPI, typename T>
+__device__ __forceinline__ bool alpha_block(const DParams<T> &a, int over)
+{
+    if (over < 0) return false;
+    if constexpr (DAG == 1 && OWN == 0 && EPI == EPI_STORE)
+        if (a.alpha > 0 && over < a.nrhs)
+            cgdev::finish_alpha(const_cast<CGScalars *>(a.sc), a.part, a.nblk, a.alpha - 1, over);
+    return true;
+}
+int alpha_blocks(const DslashCall &dc) { return dc.alpha > 0 ? dc.nrhs : 0; }
+
 template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI, bool ONE>
 __global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T, ONE>())) void k_dslash(DParams<T> a)
 {
-    dslash_block<SS, LS, T, DAG, OWN, EPI, ONE>(a, blockIdx.x, gridDim.x);
+    const int nreal = a.nblk * a.ngroups;
+    if (alpha_block<DAG, OWN, EPI>(a, (int)blockIdx.x - nreal)) return;
+    dslash_block<SS, LS, T, DAG, OWN, EPI, ONE>(a, blockIdx.x, nreal);
 }
 
 // Several lattices in one launch: instance i owns hardware blocks
@@ -992,7 +1010,7 @@ __global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T>())) void k_dslash_mul
     while (i + 1 < m.n && (int)blockIdx.x >= m.start[i + 1]) i++;
     const int local = (int)blockIdx.x - m.start[i];
     const int nreal = m.p[i].nblk * m.p[i].ngroups;
-    if (local >= nreal) return;
+    if (alpha_block<DAG, OWN, EPI>(m.p[i], local - nreal)) return;
     dslash_block<SS, LS, T, DAG, OWN, EPI>(m.p[i], local, nreal);
 }
 
@@ -1286,6 +1304,7 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
     a.rho = dc.rho;
     a.sc = dc.sc;
     a.part = dc.part;
+    a.alpha = dc.alpha;
     a.nblk = dslash_site_blocks(c);
     a.nb_t = (c->geo.vsh % kSites == 0 && (c->geo.vsh / kSites) % 8 == 0) ? c->geo.vsh / kSites : 0;
     a.t_bc = c->t_bc;
@@ -1299,7 +1318,8 @@ void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
     if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
-    dim3 grid((unsigned)(a.nblk * a.ngroups));
+    TM_REQUIRE(dc.alpha == 0 || (dc.dag && !dc.has_own), "alpha is summed beside the dag hops only");
+    dim3 grid((unsigned)(a.nblk * a.ngroups + alpha_blocks(dc)));
     // separate kernels per projector placement and per presence of the
     // own-site term (the x - H y forms read one more field)
     if (dc.dag) {
@@ -1329,7 +1349,7 @@ void multi_fill(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vect
         for (size_t k = c0; k < c1; k++) {
             const int j = (int)(k - c0);
             a.p[j] = fill_params<SS, LS, T>(cs[k], dcs[k], rpb);
-            const int nb = a.p[j].nblk * a.p[j].ngroups;
+            const int nb = a.p[j].nblk * a.p[j].ngroups + alpha_blocks(dcs[k]);
             a.start[j + 1] = a.start[j] + (nb + 7) / 8 * 8;
         }
         const unsigned char *raw = reinterpret_cast<const unsigned char *>(&a);

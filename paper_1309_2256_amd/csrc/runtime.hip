@@ -148,11 +148,11 @@ void op_bh_power(tm_ctx *c, void *se, void *so, int nrhs, double epsp, int kpow,
 namespace {
 
 // One CG iteration on the Schur normal equations for one instance, as four
-// half-Dslash launches with fused epilogues plus three small kernels:
+// half-Dslash launches with fused epilogues plus two small kernels:
 //   t = R^-1 H p;  q = R p - H t   (+ partial |q|^2)          D1, D2
-//   alpha = rr / |q|^2                                          finish
-//   t = R^-1(-eps) g5 H^dag q;  s = R(-eps) q + kappa g5 H t,  D3, D4
-//     r -= alpha s, rho -= alpha q (+ partial |r|^2, |rho|^2)
+//   t = R^-1(-eps) g5 H^dag q      (+ alpha = rr / |q|^2)      D3
+//   s = R(-eps) q + kappa g5 H t,
+//     r -= alpha s, rho -= alpha q (+ partial |r|^2, |rho|^2)  D4
 //   beta, convergence / update flags                            finish
 //   p = r + beta p, at the end of the ring x += sum alpha p     update
 DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage, int pos)
@@ -187,6 +187,9 @@ DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage, int po
         dc.dag = 1;
         dc.d_hop = sd_mul(sd_scalar(-k), sd_mul(sd_twist_inv(-epsp), sd_gamma5()));
         dc.d_own = sd_scalar(0);
+        dc.sc = w.dsc;
+        dc.part = w.partq;
+        dc.alpha = pos + 1;
         break;
     default:
         dc.in = w.tmp;
@@ -423,7 +426,6 @@ void Solver::iteration(hipStream_t s)
 {
     launch_dslash(c, stage(1, w.pos), s);
     launch_dslash(c, stage(2, w.pos), s);
-    cg_finish_alpha(c, w.dsc, w.partq, nsb, nrhs, w.pos, s);
     launch_dslash(c, stage(3, w.pos), s);
     launch_dslash(c, stage(4, w.pos), s);
     iteration_tail(s);

@@ -436,6 +436,10 @@ struct DslashCall {
     void *r = nullptr, *rho = nullptr;
     const struct CGScalars *sc = nullptr;
     double *part = nullptr;  // [quantity][nrhs][dslash_site_blocks]
+    // store forms with dag and without an own-site term: if > 0, one more block
+    // per right-hand side sums `part` (|q|^2 of an earlier launch) and sets
+    // alpha in sc, for ring position alpha - 1, while the others hop
+    int alpha = 0;
     // FP64 only: read all 18 parameters of the FP64 links whatever the
     // format (the exact operator for reliable updates and true residuals)
     bool links18 = false;
@@ -549,7 +553,6 @@ struct CGScalars {
     int bad;         // NaN/Inf seen
 };
 
-void cg_finish_alpha(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, int pos, hipStream_t s);
 void cg_finish_beta(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int nrhs, double delta,
                     hipStream_t s);
 // position pos < m - 1: p[pos + 1] = r + beta p[pos]; last position:
@@ -572,7 +575,6 @@ void cg_flush(tm_ctx *c, const CgRing &ring, int cnt, void *x, int prec, int xpr
 struct CgTail {
     tm_ctx *c;
     CGScalars *sc;
-    const double *partq;  // |q|^2 partials (alpha)
     const double *partb;  // |r|^2 (and |rho|^2) partials (beta)
     int nblk;             // partial-sum blocks
     int nrhs;
@@ -581,7 +583,6 @@ struct CgTail {
     const void *r;
     void *x;
 };
-void cg_finish_alpha_multi(const std::vector<CgTail> &t, int pos, hipStream_t s);
 void cg_tail_multi(const std::vector<CgTail> &t, int pos, int prec, int xprec, hipStream_t s);  // beta, then x and p
 
 // ---------------------------------------------------------------- misc kernels
