@@ -32,16 +32,17 @@ void ptc_apply_halves(tm_ctx *c, const void *in_e, const void *in_o, void *out_e
 
 // out = D_hop Hop[in] (+ D_own own) on output parity out_par (see DslashCall)
 void op_dslash(tm_ctx *c, void *out, const void *in, const void *own, int nrhs, int prec, int out_par,
-               int dag, SpinDiag dhop, SpinDiag down, hipStream_t s, bool links18 = false);
+               int dag, SpinDiag dhop, SpinDiag down, hipStream_t s, bool links18 = false, double *part = nullptr);
 
 // half-layout operators; tmp is an odd-parity scratch field of nrhs in prec
 // (links18: FP64 with all 18 link parameters, the exact operator)
 void op_schur(tm_ctx *c, void *out, const void *in, void *tmp, int nrhs, int prec, double epsp, hipStream_t s,
               bool links18 = false);
 void op_schur_dag(tm_ctx *c, void *out, const void *in, void *tmp, int nrhs, int prec, double epsp,
-                  hipStream_t s);
-// (B H)^k on a full field given as halves (ping-pong in place), FP64
-void op_bh_power(tm_ctx *c, void *se, void *so, int nrhs, double epsp, int k, hipStream_t s);
+                  hipStream_t s, double *part = nullptr);
+// out = (B H)^k s on full fields given as halves, FP64, k >= 1; out is not s
+void op_bh_power(tm_ctx *c, void *oe, void *oo, const void *se, const void *so, int nrhs, double epsp, int k,
+                 hipStream_t s);
 
 struct SolveOut {
     std::vector<tm_solve_stats> st;
@@ -73,7 +74,7 @@ struct Solver {
     double delta = 0, epsp = 0, t0 = 0;
     void *xe = nullptr, *xo = nullptr;
     const void *be = nullptr, *bo = nullptr;
-    void *bh = nullptr, *t64 = nullptr, *rho64 = nullptr, *r64 = nullptr, *q64 = nullptr;
+    void *bh = nullptr, *t64 = nullptr, *rho64 = nullptr, *r64 = nullptr;
     double *dscale = nullptr;
     CGWork w{};
     std::vector<double> bn2, sigma, iter_res;
@@ -101,7 +102,9 @@ struct Solver {
   private:
     // reactivate: right-hand sides whose true residual is above tol iterate
     // again (truncated solves); otherwise activity is kept
-    void restart(bool first, hipStream_t s, bool reactivate = false);
+    void restart(hipStream_t s, const std::vector<double> &nrho, const std::vector<double> *first,
+                 bool reactivate = false);
+    std::vector<double> true_residual(hipStream_t s);
     void accumulate(hipStream_t s);
 };
 

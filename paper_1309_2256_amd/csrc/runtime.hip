@@ -92,9 +92,11 @@ hipStream_t s_of(tm_ctx *c) { return c->stream; }
 double eps_of(tm_ctx *c, int mu_sign) { return mu_sign >= 0 ? c->eps : -c->eps; }
 
 void op_dslash(tm_ctx *c, void *out, const void *in, const void *own, int nrhs, int prec, int out_par, int dag,
-               SpinDiag dhop, SpinDiag down, hipStream_t s, bool links18)
+               SpinDiag dhop, SpinDiag down, hipStream_t s, bool links18, double *part)
 {
     DslashCall dc{};
+    dc.epi = part ? 1 : 0;
+    dc.part = part;
     dc.links18 = links18;
     dc.out = out;
     dc.in = in;
@@ -106,6 +108,28 @@ void op_dslash(tm_ctx *c, void *out, const void *in, const void *own, int nrhs, 
     dc.d_own = down;
     dc.d_hop = dhop;
     dc.has_own = own != nullptr;
+    launch_dslash(c, dc, s);
+}
+
+// out = b - (D_hop Hop[in] + D_own own), FP64 with the exact links, and its
+// partial norms; out = null: the norms only
+static void op_residual(tm_ctx *c, void *out, const void *b, const void *in, const void *own, int nrhs, int out_par,
+                        SpinDiag dhop, SpinDiag down, double *part, hipStream_t s)
+{
+    DslashCall dc{};
+    dc.links18 = true;
+    dc.out = out;
+    dc.in = in;
+    dc.own = own;
+    dc.r = const_cast<void *>(b);
+    dc.nrhs = nrhs;
+    dc.out_parity = out_par;
+    dc.spinor_prec = TM_F64;
+    dc.d_own = down;
+    dc.d_hop = dhop;
+    dc.has_own = true;
+    dc.epi = 3;
+    dc.part = part;
     launch_dslash(c, dc, s);
 }
 
@@ -122,24 +146,29 @@ void op_schur(tm_ctx *c, void *out, const void *in, void *tmp, int nrhs, int pre
 // Ahat^dag x = gamma5 Ahat(-eps) gamma5 x
 //            = R(-eps) x - gamma5 H_eo t,  t = R^-1(-eps) H_oe gamma5 x = R^-1(-eps) gamma5 H^dag_oe x
 void op_schur_dag(tm_ctx *c, void *out, const void *in, void *tmp, int nrhs, int prec, double epsp,
-                  hipStream_t s)
+                  hipStream_t s, double *part)
 {
     const double k = c->kappa;
     op_dslash(c, tmp, in, nullptr, nrhs, prec, 1, 1,
               sd_mul(sd_scalar(-k), sd_mul(sd_twist_inv(-epsp), sd_gamma5())), sd_scalar(0), s);
-    op_dslash(c, out, tmp, in, nrhs, prec, 0, 0, sd_mul(sd_scalar(k), sd_gamma5()), sd_twist(-epsp), s);
+    op_dslash(c, out, tmp, in, nrhs, prec, 0, 0, sd_mul(sd_scalar(k), sd_gamma5()), sd_twist(-epsp), s, false,
+              part);
 }
 
-void op_bh_power(tm_ctx *c, void *se, void *so, int nrhs, double epsp, int kpow, hipStream_t s)
+void op_bh_power(tm_ctx *c, void *oe, void *oo, const void *se, const void *so, int nrhs, double epsp, int kpow,
+                 hipStream_t s)
 {
-    size_t bytes = field_bytes(c, TM_F64, nrhs);
+    const size_t bytes = field_bytes(c, TM_F64, nrhs);
     void *te = ws_get(c, "bh_e", bytes), *to = ws_get(c, "bh_o", bytes);
-    SpinDiag d = sd_mul(sd_scalar(-c->kappa), sd_twist_inv(epsp));
-    for (int i = 0; i < kpow; i++) {
-        op_dslash(c, to, se, nullptr, nrhs, TM_F64, 1, 0, d, sd_scalar(0), s);
-        op_dslash(c, te, so, nullptr, nrhs, TM_F64, 0, 0, d, sd_scalar(0), s);
-        copy_field(se, te, bytes, s);
-        copy_field(so, to, bytes, s);
+    const SpinDiag d = sd_mul(sd_scalar(-c->kappa), sd_twist_inv(epsp));
+    // alternate between the two fields so that the last power lands in out
+    void *dst[2][2] = {{oe, oo}, {te, to}};
+    for (int k = kpow - 1; k >= 0; k--) {
+        void *const *o = dst[k & 1];
+        op_dslash(c, o[1], se, nullptr, nrhs, TM_F64, 1, 0, d, sd_scalar(0), s);
+        op_dslash(c, o[0], so, nullptr, nrhs, TM_F64, 0, 0, d, sd_scalar(0), s);
+        se = o[0];
+        so = o[1];
     }
 }
 
@@ -239,19 +268,6 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
     t64 = ws_get(c, "s_t64", f64);
     rho64 = ws_get(c, "s_rho64", f64);
     r64 = ws_get(c, "s_r64", f64);
-    q64 = ws_get(c, "s_q64", f64);
-
-    bn2 = norms_host(c, be, TM_F64, nrhs, s);
-    {
-        std::vector<double> bo2 = norms_host(c, bo, TM_F64, nrhs, s);
-        for (int r = 0; r < nrhs; r++) bn2[r] += bo2[r];
-    }
-    for (int r = 0; r < nrhs; r++)
-        if (!std::isfinite(bn2[r])) throw TmError{TM_ERR_NAN, "NaN/Inf in the source"};
-
-    // bhat_e = b_e - H_eo R_oo^-1 b_o
-    launch_spin_diag(c, t64, bo, TM_F64, nrhs, sd_twist_inv(epsp), s);
-    op_dslash(c, bh, t64, be, nrhs, TM_F64, 0, 0, sd_scalar(c->kappa), sd_scalar(1.0), s, true);
 
     hsc.assign(nrhs, CGScalars{});
     n_rel.assign(nrhs, 0);
@@ -269,19 +285,36 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
     w.partb = (double *)ws_get(c, "s_partb", sizeof(double) * nsb * nrhs * 2);
     dscale = (double *)ws_get(c, "s_scale", sizeof(double) * nrhs);
     launch_zero(c, xe, TM_F64, nrhs, s);
-    copy_field(rho64, bh, f64, s);
+
+    // bhat_e = b_e - H_eo R_oo^-1 b_o and r = Ahat^dag bhat_e; the norms of b_e,
+    // b_o, bhat_e and r come with them (one download)
+    const int nb = norm_blocks(c);
+    double *sums = (double *)ws_get(c, "s_sums", sizeof(double) * 4 * nrhs);
+    launch_partial_norm2(c, be, TM_F64, nrhs, w.partb, s);
+    launch_partial_norm2(c, bo, TM_F64, nrhs, w.partb + (size_t)nb * nrhs, s);
+    launch_sum_partials(w.partb, nb, 2 * nrhs, sums, s);
+    launch_spin_diag(c, t64, bo, TM_F64, nrhs, sd_twist_inv(epsp), s);
+    op_dslash(c, bh, t64, be, nrhs, TM_F64, 0, 0, sd_scalar(c->kappa), sd_scalar(1.0), s, true, w.partb);
+    op_schur_dag(c, r64, bh, t64, nrhs, TM_F64, epsp, s, w.partb + (size_t)nsb * nrhs);
+    launch_sum_partials(w.partb, nsb, 2 * nrhs, sums + 2 * nrhs, s);
+    std::vector<double> n4(4 * nrhs);
+    download(c, n4.data(), sums, sizeof(double) * 4 * nrhs, s);
+    bn2.resize(nrhs);
+    for (int r = 0; r < nrhs; r++) {
+        bn2[r] = n4[r] + n4[nrhs + r];
+        if (!std::isfinite(bn2[r])) throw TmError{TM_ERR_NAN, "NaN/Inf in the source"};
+    }
+    const std::vector<double> rho2(n4.begin() + 2 * nrhs, n4.begin() + 3 * nrhs), rr(n4.begin() + 3 * nrhs, n4.end());
     if (lp == TM_F64) {
+        copy_field(rho64, bh, f64, s);
         w.x = xe;
         w.xprec = TM_F64;
         w.rho = rho64;
         w.r = r64;
-        w.q = q64;
+        w.q = ws_get(c, "s_q64", f64);
         w.tmp = t64;
         w.ring.p[0] = ws_get(c, "s_p64", f64);
-        op_schur_dag(c, r64, rho64, t64, nrhs, TM_F64, epsp, s);
         copy_field(w.p(), r64, f64, s);
-        std::vector<double> rr = norms_host(c, r64, TM_F64, nrhs, s);
-        std::vector<double> rho2 = norms_host(c, rho64, TM_F64, nrhs, s);
         for (int r = 0; r < nrhs; r++) {
             CGScalars &q = hsc[r];
             q.rr = rr[r];
@@ -319,34 +352,37 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
                 w.ring.m = 1;
             }
         }
-        restart(true, s);
+        restart(s, rho2, &rr);
     }
     bool any = false;
     for (auto &q : hsc) any |= q.active != 0;
     done = !any;
 }
 
-// (re)start the low-precision iteration from the FP64 residual rho64:
-// r = Ahat^dag rho, new per-RHS scales, p rescaled (kept otherwise)
-void Solver::restart(bool first, hipStream_t s, bool reactivate)
+// (re)start the low-precision iteration from the FP64 residual: r = Ahat^dag
+// rho, new per-RHS scales, p rescaled (kept otherwise).  nrho: the residual's
+// norm; first: that of r64 = Ahat^dag bh (start of the solve, rho = bh), else
+// null; the host's copy of the scalars is current.
+void Solver::restart(hipStream_t s, const std::vector<double> &nrho, const std::vector<double> *first, bool reactivate)
 {
     const double nel = 12.0 * c->geo.vh;
     const size_t fl = field_bytes(c, lp, nrhs);
-    std::vector<double> hscale(nrhs), sig_new(nrhs);
-    std::vector<double> nrho = norms_host(c, rho64, TM_F64, nrhs, s);
+    const int nb = norm_blocks(c);
+    double *sums = (double *)ws_get(c, "s_sums", sizeof(double) * 4 * nrhs);
+    std::vector<double> hscale(nrhs), sig_new(nrhs), n2(2 * nrhs);
     auto unit_scale = [&](double n2) {
         const double v = n2 > 0 ? std::sqrt(nel / n2) : 1.0;
         return std::isfinite(v) ? v : 1.0;
     };
+    // the norms of r and rho as stored come with the conversions; without the
+    // vector rho (its norm follows a recurrence) only its norm is formed
+    double *part_r = w.partb, *part_rho = w.partb + (size_t)nb * nrhs;
     if (first) {
-        // r = Ahat^dag rho in FP64, both scaled to unit RMS of r
-        op_schur_dag(c, r64, rho64, t64, nrhs, TM_F64, epsp, s);
-        std::vector<double> nr = norms_host(c, r64, TM_F64, nrhs, s);
-        for (int r = 0; r < nrhs; r++) sig_new[r] = unit_scale(nr[r]);
-        for (int r = 0; r < nrhs; r++) hscale[r] = sig_new[r];
-        upload(dscale, hscale.data(), sizeof(double) * nrhs, s);
-        launch_copy_convert(c, w.r, lp, r64, TM_F64, nrhs, dscale, s);
-        launch_copy_convert(c, w.rho, lp, rho64, TM_F64, nrhs, dscale, s);
+        // r in FP64; both scaled to unit RMS of r
+        for (int r = 0; r < nrhs; r++) sig_new[r] = unit_scale((*first)[r]);
+        upload_async(c, 3, dscale, sig_new.data(), sizeof(double) * nrhs, s);
+        launch_convert_norm(c, w.r, lp, r64, TM_F64, nrhs, dscale, part_r, s);
+        launch_convert_norm(c, w.rho_vec ? w.rho : nullptr, lp, bh, TM_F64, nrhs, dscale, part_rho, s);
         copy_field(w.p(), w.r, fl, s);
     } else {
         // the true residual rho (FP64) enters the low-precision iteration at
@@ -354,37 +390,37 @@ void Solver::restart(bool first, hipStream_t s, bool reactivate)
         // (the FP64 part of the update is the residual itself), then both
         // are rescaled to unit RMS of r and p follows the new scale
         // the scale uploads go through pinned slots without waiting: slot 0
-        // follows the norms_host synchronisation after accumulate's copy,
-        // slots 1-3 are each used once between two synchronisations
-        std::vector<double> srho(nrhs);
+        // follows the download of the residual's norm after accumulate's copy,
+        // slots 1-4 are each used once between two synchronisations
+        std::vector<double> srho(nrhs), nrl(nrhs);
         for (int r = 0; r < nrhs; r++) srho[r] = unit_scale(nrho[r]);
         upload_async(c, 1, dscale, srho.data(), sizeof(double) * nrhs, s);
         launch_copy_convert(c, w.rho, lp, rho64, TM_F64, nrhs, dscale, s);
-        op_schur_dag(c, w.r, w.rho, w.tmp, nrhs, lp, epsp, s);
-        std::vector<double> nrl = norms_host(c, w.r, lp, nrhs, s);
+        op_schur_dag(c, w.r, w.rho, w.tmp, nrhs, lp, epsp, s, w.partq);
+        launch_sum_partials(w.partq, nsb, nrhs, sums, s);
+        download(c, nrl.data(), sums, sizeof(double) * nrhs, s);
         for (int r = 0; r < nrhs; r++) sig_new[r] = unit_scale(nrl[r] / (srho[r] * srho[r]));
         for (int r = 0; r < nrhs; r++) hscale[r] = sig_new[r] / srho[r];
         upload_async(c, 2, dscale, hscale.data(), sizeof(double) * nrhs, s);
-        launch_copy_convert(c, w.r, lp, w.r, lp, nrhs, dscale, s);
+        launch_convert_norm(c, w.r, lp, w.r, lp, nrhs, dscale, part_r, s);
         upload_async(c, 3, dscale, sig_new.data(), sizeof(double) * nrhs, s);
-        launch_copy_convert(c, w.rho, lp, rho64, TM_F64, nrhs, dscale, s);
+        launch_convert_norm(c, w.rho_vec ? w.rho : nullptr, lp, rho64, TM_F64, nrhs, dscale, part_rho, s);
         for (int r = 0; r < nrhs; r++) hscale[r] = sig_new[r] / sigma[r];
         upload_async(c, 0, dscale, hscale.data(), sizeof(double) * nrhs, s);
         launch_copy_convert(c, w.p(), lp, w.p(), lp, nrhs, dscale, s);
     }
     launch_zero(c, w.x, TM_F32, nrhs, s);
-    std::vector<double> rr = norms_host(c, w.r, lp, nrhs, s);
-    std::vector<double> rho2 = norms_host(c, w.rho, lp, nrhs, s);
-    if (!first) download(c, hsc.data(), w.dsc, sizeof(CGScalars) * nrhs, s);
+    launch_sum_partials(w.partb, nb, 2 * nrhs, sums, s);
+    download(c, n2.data(), sums, sizeof(double) * 2 * nrhs, s);
     for (int r = 0; r < nrhs; r++) {
         CGScalars &q = hsc[r];
         if (first) {
             memset(&q, 0, sizeof(q));
             q.active = 1;
         }
-        q.rr = rr[r];
-        q.rho2 = rho2[r];
-        q.rho2_ref = rho2[r];
+        q.rr = n2[r];
+        q.rho2 = n2[nrhs + r];
+        q.rho2_ref = n2[nrhs + r];
         q.target2 = p.tol * p.tol * bn2[r] * sig_new[r] * sig_new[r];
         q.sigma = sig_new[r];
         q.want_update = 0;
@@ -393,7 +429,7 @@ void Solver::restart(bool first, hipStream_t s, bool reactivate)
         iter_res[r] = std::sqrt(nrho[r] / bn2[r]);
     }
     sigma = sig_new;
-    upload(w.dsc, hsc.data(), sizeof(CGScalars) * nrhs, s);
+    upload_async(c, 4, w.dsc, hsc.data(), sizeof(CGScalars) * nrhs, s);
 }
 
 // x_hi += y / sigma
@@ -405,6 +441,19 @@ void Solver::accumulate(hipStream_t s)
     // use of the slot
     upload_async(c, 0, dscale, hscale.data(), sizeof(double) * nrhs, s);
     launch_axpy_dev(c, xe, TM_F64, w.x, TM_F32, nrhs, dscale, s);
+}
+
+// rho64 = bh - Ahat x with the exact links; returns its norms
+std::vector<double> Solver::true_residual(hipStream_t s)
+{
+    const double k = c->kappa;
+    op_dslash(c, t64, xe, nullptr, nrhs, TM_F64, 1, 0, sd_mul(sd_scalar(-k), sd_twist_inv(epsp)), sd_scalar(0), s, true);
+    op_residual(c, rho64, bh, t64, xe, nrhs, 0, sd_scalar(k), sd_twist(epsp), w.partq, s);
+    double *sums = (double *)ws_get(c, "s_sums", sizeof(double) * 4 * nrhs);
+    launch_sum_partials(w.partq, nsb, nrhs, sums, s);
+    std::vector<double> n(nrhs);
+    download(c, n.data(), sums, sizeof(double) * nrhs, s);
+    return n;
 }
 
 void Solver::iteration_tail(hipStream_t s)
@@ -489,13 +538,11 @@ void Solver::check(hipStream_t s)
             // full-system residual after odd reconstruction); right-hand
             // sides still above tol continue from it, as after a reliable
             // update
-            op_schur(c, q64, xe, t64, nrhs, TM_F64, epsp, s, true);
-            launch_axpby_to_host(c, rho64, q64, bh, TM_F64, nrhs, -1.0, 1.0, s);  // rho = bh - Ahat x
-            std::vector<double> nrho = norms_host(c, rho64, TM_F64, nrhs, s);
+            const std::vector<double> nrho = true_residual(s);
             bool again = false;
             for (int r = 0; r < nrhs; r++) again |= nrho[r] > p.tol * p.tol * bn2[r];
             if (again) {
-                restart(false, s, true);
+                restart(s, nrho, nullptr, true);
                 bool any = false;
                 for (auto &q : hsc) any |= q.active != 0;
                 done = !any;
@@ -506,11 +553,10 @@ void Solver::check(hipStream_t s)
     if (!any_update && !out_of_iters) return;
     // reliable update: FP64 true residual of the accumulated solution
     accumulate(s);
-    op_schur(c, q64, xe, t64, nrhs, TM_F64, epsp, s, true);
-    launch_axpby_to_host(c, rho64, q64, bh, TM_F64, nrhs, -1.0, 1.0, s);  // rho = bh - Ahat x
+    const std::vector<double> nrho = true_residual(s);
     for (int r = 0; r < nrhs; r++)
         if (hsc[r].active) n_rel[r]++;
-    restart(false, s);
+    restart(s, nrho, nullptr);
     bool any = false;
     for (auto &q : hsc) any |= q.active != 0;
     done = !any || out_of_iters;
@@ -523,13 +569,12 @@ SolveOut Solver::finalize(hipStream_t s)
     op_dslash(c, xo, xe, bo, nrhs, TM_F64, 1, 0, sd_mul(sd_scalar(kap), sd_twist_inv(epsp)), sd_twist_inv(epsp), s,
               true);
     // true residual b - M x, both parities, with the exact (18-parameter) links
-    op_dslash(c, rho64, xo, xe, nrhs, TM_F64, 0, 0, sd_scalar(-kap), sd_twist(epsp), s, true);
-    launch_axpby_host(c, rho64, be, TM_F64, nrhs, -1.0, 1.0, s);
-    op_dslash(c, t64, xe, xo, nrhs, TM_F64, 1, 0, sd_scalar(-kap), sd_twist(epsp), s, true);
-    launch_axpby_host(c, t64, bo, TM_F64, nrhs, -1.0, 1.0, s);
-    std::vector<double> re = norms_host(c, rho64, TM_F64, nrhs, s);
-    std::vector<double> ro = norms_host(c, t64, TM_F64, nrhs, s);
-    download(c, hsc.data(), w.dsc, sizeof(CGScalars) * nrhs, s);
+    op_residual(c, nullptr, be, xo, xe, nrhs, 0, sd_scalar(-kap), sd_twist(epsp), w.partb, s);
+    op_residual(c, nullptr, bo, xe, xo, nrhs, 1, sd_scalar(-kap), sd_twist(epsp), w.partb + (size_t)nsb * nrhs, s);
+    double *sums = (double *)ws_get(c, "s_sums", sizeof(double) * 4 * nrhs);
+    launch_sum_partials(w.partb, nsb, 2 * nrhs, sums, s);
+    std::vector<double> n2(2 * nrhs);
+    download(c, n2.data(), sums, sizeof(double) * 2 * nrhs, s);
     const double t1 = now_s();
     SolveOut out;
     out.st.assign(nrhs, tm_solve_stats{});
@@ -537,7 +582,7 @@ SolveOut Solver::finalize(hipStream_t s)
         tm_solve_stats &st = out.st[r];
         st.iters = hsc[r].iters;
         st.n_reliable = n_rel[r];
-        st.true_rel_res = bn2[r] > 0 ? std::sqrt((re[r] + ro[r]) / bn2[r]) : 0.0;
+        st.true_rel_res = bn2[r] > 0 ? std::sqrt((n2[r] + n2[nrhs + r]) / bn2[r]) : 0.0;
         st.iter_rel_res = iter_res[r];
         st.converged = st.true_rel_res <= p.tol ? 1 : 0;
         st.seconds = t1 - t0;
@@ -679,9 +724,7 @@ void contract_noise(tm_ctx *c, int estimators, int derivative, const void *ee, c
         outer_loops(se, so, se, so, G_G5_LEFT, cx<double>{0, 2.0 * epsp}, derivative, dst + per * k++);
     if (estimators & TM_EST_HPE) {
         void *he = ws_get(c, "l_h_e", f64), *ho = ws_get(c, "l_h_o", f64);
-        copy_field(he, se, f64, s_of(c));
-        copy_field(ho, so, f64, s_of(c));
-        op_bh_power(c, he, ho, nrhs, epsp, 4, s_of(c));
+        op_bh_power(c, he, ho, se, so, nrhs, epsp, 4, s_of(c));
         outer_loops(he, ho, ee, eo, G_PLAIN, cx<double>{1, 0}, false, dst + per * k++, true);
     }
     if (estimators & TM_EST_GEN_ONE_END) {

@@ -385,7 +385,7 @@ void *host_stage(tm_ctx *c, size_t bytes);
 // Pinned staging slot `slot` (< kUpSlots) of `bytes` for an asynchronous
 // upload on stream s.  A slot's previous copy must have completed before it
 // is reused (the callers synchronise the stream in between).
-constexpr int kUpSlots = 4;
+constexpr int kUpSlots = 5;
 void *host_upload_slot(tm_ctx *c, int slot, size_t bytes, hipStream_t s);
 void ensure_links32(tm_ctx *c, hipStream_t s);
 void ensure_links16(tm_ctx *c, hipStream_t s);
@@ -431,7 +431,8 @@ struct DslashCall {
     SpinDiag d_own, d_hop;
     bool has_own;
     // fused epilogue (0 store, 1 store + partial |out|^2, 2 CG update of r and
-    // rho with partial |r|^2, |rho|^2; see dslash.hip)
+    // rho with partial |r|^2, |rho|^2, 3 residual r - result with its partial
+    // norm; see dslash.hip)
     int epi = 0;
     void *r = nullptr, *rho = nullptr;
     const struct CGScalars *sc = nullptr;
@@ -527,13 +528,20 @@ void launch_copy_convert(tm_ctx *c, void *out, int out_prec, const void *in, int
 // y = a*x + b*y with host scalars (same prec)
 void launch_axpby_host(tm_ctx *c, void *y, const void *x, int prec, int nrhs, double a, double b,
                        hipStream_t s);
-// out = a x + b y (x, y, out distinct or out == y)
-void launch_axpby_to_host(tm_ctx *c, void *out, const void *x, const void *y, int prec, int nrhs, double a,
-                          double b, hipStream_t s);
 void launch_zero(tm_ctx *c, void *y, int prec, int nrhs, hipStream_t s);
 // y[r] += a_dev[r] * x[r]
 void launch_axpy_dev(tm_ctx *c, void *y, int yprec, const void *x, int xprec, int nrhs, const double *a_dev,
                      hipStream_t s);
+// out = scale[r] in per right-hand side, converted, and the partial |out|^2 of
+// the stored values into part[nrhs][norm_blocks]; out = null: the norm only.
+// in_prec is out_prec or TM_F64.
+void launch_convert_norm(tm_ctx *c, void *out, int out_prec, const void *in, int in_prec, int nrhs,
+                         const double *dscale, double *part, hipStream_t s);
+// partial |v|^2 into part[nrhs][norm_blocks]
+int norm_blocks(tm_ctx *c);
+void launch_partial_norm2(tm_ctx *c, const void *v, int prec, int nrhs, double *part, hipStream_t s);
+// dev_out[k] = sum of part[k][0 .. nblk), k < n, in a fixed order
+void launch_sum_partials(const double *part, int nblk, int n, double *dev_out, hipStream_t s);
 // per-rhs |v|^2 into dev_out[nrhs] (device doubles), deterministic
 void launch_norm2(tm_ctx *c, const void *v, int prec, int nrhs, double *dev_out, hipStream_t s);
 
