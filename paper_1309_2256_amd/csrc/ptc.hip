@@ -7,7 +7,7 @@
 // commutes with spin matrices, so the device evaluates the collapsed form
 //   N(psi) = sum_k T_k u_k,   u_k = sum_k' A[k][k'] T_k' psi,
 //   A[k][k'] = sum_c W2[k][c] W1[k'][c]                               (*)
-// in two passes over the lattice (k_ptc_mix forms the nine u_k of one
+// in two passes over the lattice (k_ptc_mix32 forms the nine u_k of one
 // parity, k_ptc_gather transports them back), and trains through (*): the
 // loss gradient with respect to A is a colour-traced outer product summed
 // over the lattice,
@@ -33,7 +33,6 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kMaxNc = 64;
 constexpr int kGradBlocks = 512;  // blocks of the gradient reduction, two per CU
-constexpr int kKG = 3;            // paths k per thread of k_ptc_mix
 
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -92,52 +91,6 @@ __device__ __forceinline__ void transport_at(cx<float> out[12], int k, const S *
 #pragma unroll
     for (int e = 0; e < 12; e++) f[e] = ldT<float>(other, e * hs + j);
     colour_mul(out, W, f);
-}
-
-// u_k (parity p) = sum_k' A[k][k'] T_k' in, for kKG consecutive k per thread.
-// grid (site blocks, nrhs, 3); u layout [9][nrhs][12][hs].
-template <typename S>
-__global__ __launch_bounds__(kBlock) void k_ptc_mix(const S *in_same, const S *in_other, const float2 *links,
-                                                    const float2 *__restrict__ A, float2 *u, Geo g, int p,
-                                                    int nrhs)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
-    const int r = blockIdx.y, k0 = blockIdx.z * kKG;
-    const size_t fs = (size_t)12 * g.hs;
-    const S *same = in_same + r * fs, *other = in_other + r * fs;
-    int x, y, z, t;
-    eo_coords(g, p, i, x, y, z, t);
-    cx<float> acc[kKG][12];
-#pragma unroll
-    for (int kk = 0; kk < kKG; kk++)
-#pragma unroll
-        for (int e = 0; e < 12; e++) acc[kk][e] = {0, 0};
-#pragma unroll 1
-    for (int kp = 0; kp < 9; kp++) {
-        cx<float> gv[12];
-        transport_at<S>(gv, kp, same, other, links, g, i, x, y, z, t);
-#pragma unroll
-        for (int kk = 0; kk < kKG; kk++) {
-            const float2 *Sm = A + ((k0 + kk) * 9 + kp) * 16;
-#pragma unroll
-            for (int a = 0; a < 4; a++)
-#pragma unroll
-                for (int b = 0; b < 4; b++) {
-                    const float2 w = Sm[4 * a + b];
-                    const cx<float> wc = {w.x, w.y};
-#pragma unroll
-                    for (int c = 0; c < 3; c++) cmac(acc[kk][3 * a + c], wc, gv[3 * b + c]);
-                }
-        }
-    }
-    const size_t hs = (size_t)g.hs;
-#pragma unroll
-    for (int kk = 0; kk < kKG; kk++) {
-        float2 *uo = u + ((size_t)(k0 + kk) * nrhs + r) * fs;
-#pragma unroll
-        for (int e = 0; e < 12; e++) uo[e * hs + i] = make_float2(acc[kk][e].r, acc[kk][e].i);
-    }
 }
 
 // ---------------------------------------------------------------- matrix cores
@@ -240,6 +193,123 @@ __global__ __launch_bounds__(kBlock, 2) void k_ptc_mix_mfma(const S *in_same, co
                         u[(((size_t)k * nrhs + r) * 12 + 3 * a + c) * hs + i] =
                             make_float2(acc[tt][2 * e], acc[tt][2 * e + 1]);
                 }
+        }
+    }
+}
+
+// The same in FP32 on v_mfma_f32_16x16x4_f32.  The instruction is an ascending
+// chain of four FP32 FMAs per element (checked bitwise against fmaf), so with
+// the K values in the order of a complex multiply-add the result has the bits
+// of the scalar loop over (k', b): acc.r += a.r g.r, acc.r -= a.i g.i; acc.i +=
+// a.r g.i, acc.i += a.i g.r.  Real and imaginary rows take the two parts of g
+// in opposite order, so they are separate row tiles (three of 16 for the 36
+// rows of each).  A block takes 32 sites of one right-hand side at a time: a
+// half-wave per path forms its transports into LDS, rows 2 (4 k' + b) + re/im,
+// a column per (colour, site); then even waves multiply the real row tiles, odd
+// waves the imaginary ones, with the A operands in registers for the whole
+// launch and half of the columns each.  Operand lanes: A[i][k] in lane i + 16 k,
+// B[k][n] in lane n + 16 k, D[i][n] in lane (n, g) at i = 4g + v: row 16 t + 4g
+// + v is path k = 4t + g, spin v.  Row stride 112 floats: the four rows of an
+// operand are on different banks.
+// Bound: matrix time, 648 instructions of 32 cycles per 32 sites and right-hand
+// side (69 us for 4 right-hand sides of one parity of 16^3 x 32), beside 45 us
+// of loads and 75 us of stores (the u fields, real and imaginary parts from
+// different waves) that three blocks per CU overlap in part: 157 us.  A thread
+// per site formed every transport three times and issued 19k multiply-adds per
+// site: 200 us.  Measured and slower: transports path by path in registers
+// between the MFMAs (246), a wave per row tile with four blocks per CU (167),
+// waves of their own for the transports (195), both parts in one wave (spills,
+// 250).
+constexpr int kRT = 3, kS32 = 18, kXS = 32, kXStride = 112;
+
+// frag[(t * kS32 + s) * 64 + lane] = A of row tile t (t < kRT real rows, then
+// imaginary rows), step s
+__global__ void k_ptc_afrag32(const float2 *A, float *frag)
+{
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= 2 * kRT * kS32 * 64) return;
+    const int lane = idx % 64, ts = idx / 64, t = ts / kS32, s = ts % kS32, g = lane / 16;
+    const int i = 16 * (t % kRT) + lane % 16, j = 2 * s + g / 2;
+    float v = 0.f;
+    if (i < 36) {
+        const float2 w = A[((i / 4) * 9 + j / 4) * 16 + 4 * (i % 4) + j % 4];
+        v = g % 2 == 0 ? w.x : t < kRT ? -w.y : w.y;
+    }
+    frag[idx] = v;
+}
+
+// u_k (parity p) for all nine k, grid-stride over `tiles` of 32 sites x nrhs.
+// u layout [9][nrhs][12][hs].
+template <typename S>
+__global__ __launch_bounds__(kBlock, 3) void k_ptc_mix32(const S *in_same, const S *in_other, const float2 *links,
+                                                         const float *frag, float2 *u, Geo g, int p, int nrhs, int tiles)
+{
+    __shared__ float G[72 * kXStride];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int n = lane % 16, grp = lane / 16;
+    const int im = w & 1, c0 = 3 * (w >> 1);  // this wave's row tiles (part) and first column tile
+    const size_t fs = (size_t)12 * g.hs, hs = (size_t)g.hs;
+    float A[kRT][kS32];
+#pragma unroll
+    for (int t = 0; t < kRT; t++)
+#pragma unroll
+        for (int q = 0; q < kS32; q++) A[t][q] = frag[((im * kRT + t) * kS32 + q) * 64 + lane];
+    const float *B = G + (im ? grp ^ 1 : grp) * kXStride + 16 * c0 + n;
+    for (int wk = blockIdx.x; wk < tiles * nrhs; wk += gridDim.x) {
+        const int r = wk % nrhs, i0 = (wk / nrhs) * kXS;
+        const S *same = in_same + r * fs, *other = in_other + r * fs;
+        {
+            const int site = threadIdx.x & 31, k = 1 + (threadIdx.x >> 5);
+            const int i = min(i0 + site, g.vh - 1);  // columns past the lattice are not stored
+            int x, y, z, t;
+            eo_coords(g, p, i, x, y, z, t);
+            cx<float> v[12];
+            transport_at<S>(v, k, same, other, links, g, i, x, y, z, t);
+            __syncthreads();  // the previous tile has been read
+            float *M = G + 8 * k * kXStride + site;
+#pragma unroll
+            for (int b = 0; b < 4; b++)
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    M[(2 * b) * kXStride + kXS * c] = v[3 * b + c].r;
+                    M[(2 * b + 1) * kXStride + kXS * c] = v[3 * b + c].i;
+                }
+            for (int e = k - 1; e < 12; e += 8) {  // the identity
+                const cx<float> f = ldT<float>(same, e * hs + i);
+                G[2 * (e / 3) * kXStride + kXS * (e % 3) + site] = f.r;
+                G[(2 * (e / 3) + 1) * kXStride + kXS * (e % 3) + site] = f.i;
+            }
+        }
+        __syncthreads();
+        f32x4 acc[kRT][3];
+#pragma unroll
+        for (int t = 0; t < kRT; t++)
+#pragma unroll
+            for (int c = 0; c < 3; c++) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < kS32; q++) {
+            float b[3];
+#pragma unroll
+            for (int c = 0; c < 3; c++) b[c] = B[4 * q * kXStride + 16 * c];
+#pragma unroll
+            for (int t = 0; t < kRT; t++)
+#pragma unroll
+                for (int c = 0; c < 3; c++)
+                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[t][q], b[c], acc[t][c], 0, 0, 0);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const int col = 16 * (c0 + c) + n, colour = col / kXS, i = i0 + col % kXS;
+            if (i >= g.vh) continue;
+#pragma unroll
+            for (int t = 0; t < kRT; t++) {
+                const int k = 4 * t + grp;
+                if (k < 9) {
+                    float *o = (float *)(u + (((size_t)k * nrhs + r) * 12 + colour) * hs + i) + im;
+#pragma unroll
+                    for (int a = 0; a < 4; a++) o[6 * a * hs] = acc[t][c][a];
+                }
+            }
         }
     }
 }
@@ -575,6 +645,11 @@ void run_update(tm_ctx *c, int mode, const AdamArgs &ad, hipStream_t s)
                        (const float2 *)ws_get(c, "ptc_A", sizeof(float2) * 81 * 16),
                        (bf16x8 *)ws_get(c, "ptc_Afrag", sizeof(bf16x8) * kMT * kKS * 64));
     TM_HIP(hipGetLastError());
+    // and the FP32 ones
+    hipLaunchKernelGGL(k_ptc_afrag32, dim3((2 * kRT * kS32 * 64 + 255) / 256), dim3(256), 0, s,
+                       (const float2 *)ws_get(c, "ptc_A", sizeof(float2) * 81 * 16),
+                       (float *)ws_get(c, "ptc_Afrag32", sizeof(float) * 2 * kRT * kS32 * 64));
+    TM_HIP(hipGetLastError());
 }
 
 // N(in) for nrhs fields given as FP32-or-BF16 halves (S) -> FP32 halves
@@ -585,7 +660,6 @@ void forward_t(tm_ctx *c, const void *in_e, const void *in_o, float2 *out_e, flo
     const size_t fl = (size_t)12 * c->geo.hs * nrhs;
     float2 *u[2] = {(float2 *)ws_get(c, "ptc_u0", sizeof(float2) * 9 * fl),
                     (float2 *)ws_get(c, "ptc_u1", sizeof(float2) * 9 * fl)};
-    const float2 *A = (const float2 *)ws_get(c, "ptc_A", sizeof(float2) * 81 * 16);
     const S *in[2] = {(const S *)in_e, (const S *)in_o};
     if (c->ptc_arith == TM_BF16) {
         const bf16x8 *frag = (const bf16x8 *)ws_get(c, "ptc_Afrag", sizeof(bf16x8) * kMT * kKS * 64);
@@ -596,10 +670,13 @@ void forward_t(tm_ctx *c, const void *in_e, const void *in_o, float2 *out_e, flo
             TM_HIP(hipGetLastError());
         }
     } else {
-        dim3 gm(site_blocks(c), nrhs, 9 / kKG);
+        const float *frag = (const float *)ws_get(c, "ptc_Afrag32", sizeof(float) * 2 * kRT * kS32 * 64);
+        const int tiles = (c->geo.vh + kXS - 1) / kXS;
+        TM_REQUIRE((long)tiles * nrhs <= 0x7fffffffL - 4 * 256, "batch too large for the spin-mixing grid");
+        const int grid = std::min(tiles * nrhs, 3 * 256);  // resident blocks
         for (int p = 0; p < 2; p++) {
-            hipLaunchKernelGGL(k_ptc_mix<S>, gm, dim3(kBlock), 0, s, in[p], in[1 - p], (const float2 *)c->links32[p],
-                               A, u[p], c->geo, p, nrhs);
+            hipLaunchKernelGGL(k_ptc_mix32<S>, dim3(grid), dim3(kBlock), 0, s, in[p], in[1 - p],
+                               (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
             TM_HIP(hipGetLastError());
         }
     }

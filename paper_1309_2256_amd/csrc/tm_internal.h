@@ -478,7 +478,7 @@ void multi_dslash_launch(const MultiDslash &m, hipStream_t s);
 // in the order of the iterations (the same FP32 sums as one at a time): x and
 // the directions move (4 m - 1) / m low-precision and 2 / m FP32 accesses per
 // element and iteration instead of 3 and 2.  Bound: memory; FP16, 32^3 x 64, 12
-// right-hand sides: about 440 us per iteration for m = 8, 729 (5.8 TB/s) for
+// right-hand sides: 462 us per iteration for m = 8, 729 (5.8 TB/s) for
 // m = 1, a mixed solve of 157 iterations 601 ms against 646.
 constexpr int kCgRing = 8;
 // Ring of search directions: ring position q holds the direction of the q-th
