@@ -109,6 +109,7 @@ __device__ __forceinline__ void transport_at(cx<float> out[12], int k, const S *
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMT = 5, kKS = 3;  // row tiles, K steps
+constexpr int kXS = 32;          // sites of a tile
 
 // frag[(t * kKS + q) * 64 + lane] = the A operand of row tile t, K step q
 __global__ void k_ptc_afrag(const float2 *A, bf16x8 *frag)
@@ -131,68 +132,86 @@ __global__ void k_ptc_afrag(const float2 *A, bf16x8 *frag)
     frag[idx] = v;
 }
 
-// u_k (parity p) for all nine k on the matrix cores; block of 4 waves = 64
-// sites, grid (site blocks of 64, nrhs).  u layout [9][nrhs][12][hs].
+// u_k (parity p) for all nine k on the matrix cores, grid-stride over `tiles` of
+// 32 sites x nrhs.  u layout [9][nrhs][12][hs].  A half-wave per path forms the
+// transports of the tile and leaves them in LDS as B operands (16 bytes per path,
+// colour and site); then a wave takes 16 of the sites and the row tiles 0..2 or
+// 3, 4.  Bound: memory (u written, 226 MB for 4 right-hand sides of one parity
+// of 16^3 x 32, 44 us): 98 us.  With the transports in the lanes that multiply
+// them (16 sites a wave, four paths per load, 172 registers) 106 us.
 template <typename S>
-__global__ __launch_bounds__(kBlock, 2) void k_ptc_mix_mfma(const S *in_same, const S *in_other,
-                                                            const float2 *links, const bf16x8 *frag, float2 *u,
-                                                            Geo g, int p, int nrhs)
+__global__ __launch_bounds__(kBlock, 4) void k_ptc_mix_mfma(const S *in_same, const S *in_other, const float2 *links,
+                                                            const bf16x8 *frag, float2 *u, Geo g, int p, int nrhs,
+                                                            int tiles)
 {
+    __shared__ bf16x8 G[9][3][kXS];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n = lane % 16, grp = lane / 16;
-    const int i_raw = blockIdx.x * 64 + w * 16 + n;
-    const bool valid = i_raw < g.vh;
-    const int i = valid ? i_raw : g.vh - 1;
-    const int r = blockIdx.y;
+    const int n = 16 * (w & 1) + lane % 16, grp = lane / 16;  // this lane's column (site of the tile)
+    const int t0 = w < 2 ? 0 : 3;                              // first row tile
     const size_t fs = (size_t)12 * g.hs, hs = (size_t)g.hs;
-    const S *same = in_same + r * fs, *other = in_other + r * fs;
-    int x, y, z, t;
-    eo_coords(g, p, i, x, y, z, t);
-    // B operands: the transports of this lane's paths, per colour
-    bf16x8 bq[3][kKS];
+    const int site = threadIdx.x & 31, task = threadIdx.x >> 5;
+    bf16x8 af[3][kKS];
 #pragma unroll
-    for (int q = 0; q < kKS; q++) {
-        const int kp = 4 * q + grp;
-        cx<float> gv[12];
-        if (kp <= 8) {
-            transport_at<S>(gv, kp, same, other, links, g, i, x, y, z, t);
-        } else {
+    for (int tt = 0; tt < 3; tt++)
 #pragma unroll
-            for (int e = 0; e < 12; e++) gv[e] = {0.f, 0.f};
-        }
+        for (int q = 0; q < kKS; q++) af[tt][q] = frag[(min(t0 + tt, kMT - 1) * kKS + q) * 64 + lane];
+    for (int wk = blockIdx.x; wk < tiles * nrhs; wk += gridDim.x) {
+        const int r = wk % nrhs, i0 = (wk / nrhs) * kXS;
+        const S *same = in_same + r * fs, *other = in_other + r * fs;
+        {
+            const int i = min(i0 + site, g.vh - 1);  // columns past the lattice are not stored
+            int x, y, z, t;
+            eo_coords(g, p, i, x, y, z, t);
+            cx<float> v[12];
+            transport_at<S>(v, task + 1, same, other, links, g, i, x, y, z, t);
+            bf16x8 f;
+            if (task < 3) {  // the identity, a colour each
 #pragma unroll
-        for (int c = 0; c < 3; c++)
-#pragma unroll
-            for (int b = 0; b < 4; b++) {
-                bq[c][q][2 * b] = (__bf16)gv[3 * b + c].r;
-                bq[c][q][2 * b + 1] = (__bf16)gv[3 * b + c].i;
-            }
-    }
-    bf16x8 af[kMT][kKS];
-#pragma unroll
-    for (int tt = 0; tt < kMT; tt++)
-#pragma unroll
-        for (int q = 0; q < kKS; q++) af[tt][q] = frag[(tt * kKS + q) * 64 + lane];
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        f32x4 acc[kMT];
-#pragma unroll
-        for (int tt = 0; tt < kMT; tt++) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < kKS; q++)
-#pragma unroll
-            for (int tt = 0; tt < kMT; tt++)
-                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[tt][q], bq[c][q], acc[tt], 0, 0, 0);
-        if (valid) {
-#pragma unroll
-            for (int tt = 0; tt < kMT; tt++)
-#pragma unroll
-                for (int e = 0; e < 2; e++) {
-                    const int cr = 8 * tt + 2 * grp + e, k = cr / 4, a = cr % 4;
-                    if (k < 9)
-                        u[(((size_t)k * nrhs + r) * 12 + 3 * a + c) * hs + i] =
-                            make_float2(acc[tt][2 * e], acc[tt][2 * e + 1]);
+                for (int b = 0; b < 4; b++) {
+                    const cx<float> id = ldT<float>(same, (3 * b + task) * hs + i);
+                    f[2 * b] = (__bf16)id.r;
+                    f[2 * b + 1] = (__bf16)id.i;
                 }
+            }
+            __syncthreads();  // the previous tile has been read
+            if (task < 3) G[0][task][site] = f;
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+#pragma unroll
+                for (int b = 0; b < 4; b++) {
+                    f[2 * b] = (__bf16)v[3 * b + c].r;
+                    f[2 * b + 1] = (__bf16)v[3 * b + c].i;
+                }
+                G[task + 1][c][site] = f;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            f32x4 acc[3];
+#pragma unroll
+            for (int tt = 0; tt < 3; tt++) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < kKS; q++) {
+                const int kp = 4 * q + grp;
+                bf16x8 bq = {};
+                if (kp < 9) bq = G[kp][c][n];
+#pragma unroll
+                for (int tt = 0; tt < 3; tt++)
+                    if (t0 + tt < kMT)  // uniform
+                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[tt][q], bq, acc[tt], 0, 0, 0);
+            }
+            if (i0 + n < g.vh) {
+#pragma unroll
+                for (int tt = 0; tt < 3; tt++)
+#pragma unroll
+                    for (int e = 0; e < 2; e++) {
+                        const int cr = 8 * (t0 + tt) + 2 * grp + e, k = cr / 4, a = cr % 4;
+                        if (k < 9)
+                            u[(((size_t)k * nrhs + r) * 12 + 3 * a + c) * hs + i0 + n] =
+                                make_float2(acc[tt][2 * e], acc[tt][2 * e + 1]);
+                    }
+            }
         }
     }
 }
@@ -220,7 +239,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_ptc_mix_mfma(const S *in_same, co
 // between the MFMAs (246), a wave per row tile with four blocks per CU (167),
 // waves of their own for the transports (195), both parts in one wave (spills,
 // 250).
-constexpr int kRT = 3, kS32 = 18, kXS = 32, kXStride = 112;
+constexpr int kRT = 3, kS32 = 18, kXStride = 112;
 
 // frag[(t * kS32 + s) * 64 + lane] = A of row tile t (t < kRT real rows, then
 // imaginary rows), step s
@@ -661,22 +680,21 @@ void forward_t(tm_ctx *c, const void *in_e, const void *in_o, float2 *out_e, flo
     float2 *u[2] = {(float2 *)ws_get(c, "ptc_u0", sizeof(float2) * 9 * fl),
                     (float2 *)ws_get(c, "ptc_u1", sizeof(float2) * 9 * fl)};
     const S *in[2] = {(const S *)in_e, (const S *)in_o};
+    const int tiles = (c->geo.vh + kXS - 1) / kXS;
+    TM_REQUIRE((long)tiles * nrhs <= 0x7fffffffL - 4 * 256, "batch too large for the spin-mixing grid");
+    // grids: the resident blocks, each walks its tiles
     if (c->ptc_arith == TM_BF16) {
         const bf16x8 *frag = (const bf16x8 *)ws_get(c, "ptc_Afrag", sizeof(bf16x8) * kMT * kKS * 64);
-        dim3 gm((c->geo.vh + 63) / 64, nrhs);
         for (int p = 0; p < 2; p++) {
-            hipLaunchKernelGGL(k_ptc_mix_mfma<S>, gm, dim3(kBlock), 0, s, in[p], in[1 - p],
-                               (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs);
+            hipLaunchKernelGGL(k_ptc_mix_mfma<S>, dim3(std::min(tiles * nrhs, 4 * 256)), dim3(kBlock), 0, s, in[p],
+                               in[1 - p], (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
             TM_HIP(hipGetLastError());
         }
     } else {
         const float *frag = (const float *)ws_get(c, "ptc_Afrag32", sizeof(float) * 2 * kRT * kS32 * 64);
-        const int tiles = (c->geo.vh + kXS - 1) / kXS;
-        TM_REQUIRE((long)tiles * nrhs <= 0x7fffffffL - 4 * 256, "batch too large for the spin-mixing grid");
-        const int grid = std::min(tiles * nrhs, 3 * 256);  // resident blocks
         for (int p = 0; p < 2; p++) {
-            hipLaunchKernelGGL(k_ptc_mix32<S>, dim3(grid), dim3(kBlock), 0, s, in[p], in[1 - p],
-                               (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
+            hipLaunchKernelGGL(k_ptc_mix32<S>, dim3(std::min(tiles * nrhs, 3 * 256)), dim3(kBlock), 0, s, in[p],
+                               in[1 - p], (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
             TM_HIP(hipGetLastError());
         }
     }
