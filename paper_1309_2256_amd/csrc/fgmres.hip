@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "cg_device.h"
 #include "runtime.h"
 
 namespace {
@@ -21,14 +22,11 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kChunk = 8;   // basis vectors per multi-dot / multi-axpy launch
 constexpr int kDotBlk = 256;
+constexpr int kMaxpyBlk = 2048;
+static_assert(kMaxpyBlk <= kChunk * kDotBlk, "partials of the norm");
 constexpr int kMaxM = 32;
 
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
-}
+using cgdev::wave_sum;
 
 template <typename SV>
 __device__ __forceinline__ cx<double> ldv(const SV *p, size_t k)
@@ -38,38 +36,39 @@ __device__ __forceinline__ cx<double> ldv(const SV *p, size_t k)
 
 // part[((r*kChunk + i)*2 + h)*nblk + blk] (re, im) = block sums of conj(v_i) w
 // over half h of right-hand side r (the vh valid sites of its 12 planes of
-// stride ps; pad sites skipped); grid (nblk, nrhs, 2)
-template <typename SV>
-__global__ __launch_bounds__(kBlock) void k_mdot(const SV *V, size_t vstride, int nb, const double2 *w, size_t n,
-                                                 size_t half, int vh, int ps, double2 *part)
+// stride ps; pad sites skipped), i < NB; grid (nblk, nrhs, 2).  Bound: memory.
+// NB at compile time lets all loads of a site go out together, and the sums of
+// a wave are DPP adds: sixteen of them through the LDS crossbar were 7 us a block.
+template <int NB, typename SV>
+__global__ __launch_bounds__(kBlock) void k_mdot(const SV *V, size_t vstride, const double2 *w, size_t n, size_t half,
+                                                 int vh, int ps, double2 *part)
 {
     const int r = blockIdx.y, h = blockIdx.z, nblk = gridDim.x;
     const size_t base = h * half + (size_t)r * n;
-    double acc[2 * kChunk];
+    double acc[2 * NB];
 #pragma unroll
-    for (int q = 0; q < 2 * kChunk; q++) acc[q] = 0;
+    for (int q = 0; q < 2 * NB; q++) acc[q] = 0;
     for (int k = 0; k < 12; k++) {
         for (int si = blockIdx.x * kBlock + threadIdx.x; si < vh; si += nblk * kBlock) {
             const size_t e = (size_t)k * ps + si;
             const double2 wv = w[base + e];
 #pragma unroll
-            for (int i = 0; i < kChunk; i++)
-                if (i < nb) {
-                    const cx<double> v = ldv(V, i * vstride + base + e);
-                    acc[2 * i] = fma(v.r, wv.x, fma(v.i, wv.y, acc[2 * i]));
-                    acc[2 * i + 1] = fma(v.r, wv.y, fma(-v.i, wv.x, acc[2 * i + 1]));
-                }
+            for (int i = 0; i < NB; i++) {
+                const cx<double> v = ldv(V, i * vstride + base + e);
+                acc[2 * i] = fma(v.r, wv.x, fma(v.i, wv.y, acc[2 * i]));
+                acc[2 * i + 1] = fma(v.r, wv.y, fma(-v.i, wv.x, acc[2 * i + 1]));
+            }
         }
     }
-    __shared__ double red[kBlock / 64][2 * kChunk];
+    __shared__ double red[kBlock / 64][2 * NB];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q < 2 * kChunk; q++) {
+    for (int q = 0; q < 2 * NB; q++) {
         const double s = wave_sum(acc[q]);
         if (lane == 0) red[wv][q] = s;
     }
     __syncthreads();
-    if (threadIdx.x < kChunk && (int)threadIdx.x < nb) {
+    if (threadIdx.x < NB) {
         const int i = threadIdx.x;
         double re = 0, im = 0;
         for (int k = 0; k < kBlock / 64; k++) {
@@ -80,13 +79,14 @@ __global__ __launch_bounds__(kBlock) void k_mdot(const SV *V, size_t vstride, in
     }
 }
 
-// out[r*ld + i0 + i] = sum over halves and blocks (fixed order); one wave per
-// (r, i), block r * nb + i (a thread each walked the 512 partials in series,
-// 46 us a launch; now 3)
-__global__ __launch_bounds__(64) void k_mdot_finish(const double2 *part, int nb, int nblk, double2 *out, int ld, int i0)
+// out[r*ld + i0 + i] = sum over halves and blocks (fixed order) of the partials
+// of vector i of `per` per right-hand side; one wave per (r, i), block r * nb + i
+// (a thread each walked the 512 partials in series, 46 us a launch; now 3)
+__global__ __launch_bounds__(64) void k_mdot_finish(const double2 *part, int per, int nb, int nblk, double2 *out,
+                                                    int ld, int i0)
 {
     const int r = blockIdx.x / nb, i = blockIdx.x % nb;
-    const double2 *p = part + ((size_t)r * kChunk + i) * 2 * nblk;
+    const double2 *p = part + ((size_t)r * per + i) * 2 * nblk;
     double re = 0, im = 0;
     for (int b = threadIdx.x; b < 2 * nblk; b += 64) {
         re += p[b].x;
@@ -97,27 +97,49 @@ __global__ __launch_bounds__(64) void k_mdot_finish(const double2 *part, int nb,
     if (threadIdx.x == 0) out[(size_t)r * ld + i0 + i] = make_double2(re, im);
 }
 
-// w += sign * sum_i coef[r*ld + i0 + i] v_i; grid (blocks, nrhs, 2)
-template <typename SV>
-__global__ __launch_bounds__(kBlock) void k_maxpy(double2 *w, const SV *V, size_t vstride, int nb,
+// w += sign * sum_i coef[r*ld + i0 + i] v_i, i < NB; grid (blocks, nrhs, 2).
+// NORM: also the partial |w|^2 of each half (vh valid sites per plane of stride
+// ps) as part[(r * 2 + h) * blocks + block], which saves reading w again
+template <int NB, bool NORM, typename SV>
+__global__ __launch_bounds__(kBlock) void k_maxpy(double2 *w, const SV *V, size_t vstride,
                                                   const double2 *__restrict__ coef, int ld, int i0, double sign,
-                                                  size_t n, size_t half)
+                                                  size_t n, size_t half, int vh, int ps, double2 *part)
 {
     const int r = blockIdx.y, h = blockIdx.z;
     const size_t base = h * half + (size_t)r * n;
-    cx<double> cf[kChunk];
+    cx<double> cf[NB];
 #pragma unroll
-    for (int i = 0; i < kChunk; i++) {
-        const double2 v = i < nb ? coef[(size_t)r * ld + i0 + i] : make_double2(0, 0);
+    for (int i = 0; i < NB; i++) {
+        const double2 v = coef[(size_t)r * ld + i0 + i];
         cf[i] = {sign * v.x, sign * v.y};
     }
+    double s = 0;
     for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < n; e += (size_t)gridDim.x * kBlock) {
         double2 a = w[base + e];
         cx<double> acc = {a.x, a.y};
 #pragma unroll
-        for (int i = 0; i < kChunk; i++)
-            if (i < nb) cmac(acc, cf[i], ldv(V, i * vstride + base + e));
+        for (int i = 0; i < NB; i++) cmac(acc, cf[i], ldv(V, i * vstride + base + e));
         w[base + e] = make_double2(acc.r, acc.i);
+        if constexpr (NORM)
+            if ((int)((unsigned)e % (unsigned)ps) < vh) s = fma(acc.r, acc.r, fma(acc.i, acc.i, s));
+    }
+    if constexpr (NORM) {
+        s = cgdev::block_sum(s);
+        if (threadIdx.x == 0) part[((size_t)r * 2 + h) * gridDim.x + blockIdx.x] = make_double2(s, 0.0);
+    }
+}
+
+// v = scale[r] w, and z = v in FP32 (z may be null); n elements per (half,
+// right-hand side), grid (blocks, 2 nrhs)
+__global__ __launch_bounds__(kBlock) void k_next(double2 *v, float2 *z, const double2 *w, size_t n, const double *scale)
+{
+    const size_t base = (size_t)blockIdx.y * n;
+    const double sc = scale[blockIdx.y];
+    for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < n; e += (size_t)gridDim.x * kBlock) {
+        const double2 a = w[base + e];
+        const double2 o = make_double2(sc * a.x, sc * a.y);
+        v[base + e] = o;
+        if (z) z[base + e] = make_float2((float)o.x, (float)o.y);
     }
 }
 
@@ -226,6 +248,23 @@ struct Fg {
     double2 *part;
 };
 
+// f(integral constant nb), 1 <= nb <= kChunk
+template <typename F>
+void with_count(int nb, F &&f)
+{
+    static_assert(kChunk == 8);
+    switch (nb) {
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 7: return f(std::integral_constant<int, 7>{});
+    default: return f(std::integral_constant<int, 8>{});
+    }
+}
+
 // out[r*ld + i0 .. i0 + nb) = <v_i, w> for nb basis vectors in chunks
 template <typename SV>
 void mdot(Fg &f, const SV *V, size_t vstride, int nb, const double2 *w, double2 *out, int ld, int i0)
@@ -234,26 +273,52 @@ void mdot(Fg &f, const SV *V, size_t vstride, int nb, const double2 *w, double2 
     account(f.c, 2.0 * f.n * f.nrhs * (nb * sizeof(SV) + sizeof(double2)), 16.0 * f.n * f.nrhs * nb);
     for (int c0 = 0; c0 < nb; c0 += kChunk) {
         const int k = std::min(kChunk, nb - c0);
-        hipLaunchKernelGGL(k_mdot<SV>, dim3(kDotBlk, f.nrhs, 2), dim3(kBlock), 0, f.s, V + c0 * vstride, vstride, k,
-                           w, f.n, f.hs, f.c->geo.vh, f.c->geo.hs, f.part);
+        with_count(k, [&](auto m) {
+            hipLaunchKernelGGL((k_mdot<m(), SV>), dim3(kDotBlk, f.nrhs, 2), dim3(kBlock), 0, f.s, V + c0 * vstride,
+                               vstride, w, f.n, f.hs, f.c->geo.vh, f.c->geo.hs, f.part);
+        });
         TM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_mdot_finish, dim3(f.nrhs * k), dim3(64), 0, f.s, (const double2 *)f.part, k, kDotBlk,
-                           out, ld, i0 + c0);
+        hipLaunchKernelGGL(k_mdot_finish, dim3(f.nrhs * k), dim3(64), 0, f.s, (const double2 *)f.part, kChunk, k,
+                           kDotBlk, out, ld, i0 + c0);
         TM_HIP(hipGetLastError());
     }
 }
 
+// norm: also |w|^2 of the result into norm[r*ld] (re)
 template <typename SV>
-void maxpy(Fg &f, double2 *w, const SV *V, size_t vstride, int nb, const double2 *coef, int ld, double sign)
+void maxpy(Fg &f, double2 *w, const SV *V, size_t vstride, int nb, const double2 *coef, int ld, double sign,
+           double2 *norm = nullptr)
 {
-    const int blocks = (int)std::min<size_t>((f.n + kBlock - 1) / kBlock, 2048);
+    const int blocks = (int)std::min<size_t>((f.n + kBlock - 1) / kBlock, kMaxpyBlk);
     account(f.c, 2.0 * f.n * f.nrhs * (nb * sizeof(SV) + 2 * sizeof(double2)), 16.0 * f.n * f.nrhs * nb);
     for (int c0 = 0; c0 < nb; c0 += kChunk) {
         const int k = std::min(kChunk, nb - c0);
-        hipLaunchKernelGGL(k_maxpy<SV>, dim3(blocks, f.nrhs, 2), dim3(kBlock), 0, f.s, w, V + c0 * vstride, vstride,
-                           k, coef, ld, c0, sign, f.n, f.hs);
+        with_count(k, [&](auto m) {
+            const dim3 grid(blocks, f.nrhs, 2);
+            if (norm && c0 + k == nb)
+                hipLaunchKernelGGL((k_maxpy<m(), true, SV>), grid, dim3(kBlock), 0, f.s, w, V + c0 * vstride, vstride,
+                                   coef, ld, c0, sign, f.n, f.hs, f.c->geo.vh, f.c->geo.hs, f.part);
+            else
+                hipLaunchKernelGGL((k_maxpy<m(), false, SV>), grid, dim3(kBlock), 0, f.s, w, V + c0 * vstride, vstride,
+                                   coef, ld, c0, sign, f.n, f.hs, f.c->geo.vh, f.c->geo.hs, f.part);
+        });
         TM_HIP(hipGetLastError());
     }
+    if (norm) {
+        hipLaunchKernelGGL(k_mdot_finish, dim3(f.nrhs), dim3(64), 0, f.s, (const double2 *)f.part, 1, 1, blocks, norm,
+                           ld, 0);
+        TM_HIP(hipGetLastError());
+    }
+}
+
+// v = scale w per half and right-hand side, z = v in FP32 (may be null)
+void next_vector(Fg &f, double2 *v, float2 *z, const double2 *w, const double *scale)
+{
+    const size_t all = 2 * f.n * f.nrhs;
+    account(f.c, (double)all * (2 * sizeof(double2) + (z ? sizeof(float2) : 0)), 2.0 * all);
+    const int blocks = (int)std::min<size_t>((f.n + 4 * kBlock - 1) / (4 * kBlock), 4096);
+    hipLaunchKernelGGL(k_next, dim3(blocks, 2 * f.nrhs), dim3(kBlock), 0, f.s, v, z, w, f.n, scale);
+    TM_HIP(hipGetLastError());
 }
 
 // out = M in on full FP64 fields (halves consecutive)
@@ -357,14 +422,13 @@ SolveOut fgmres_halves(tm_ctx *c, void *xe, void *xo, const void *be, const void
         std::vector<int> zero(nrhs, 0);
         upload(st.ncol, zero.data(), sizeof(int) * nrhs, s);
         upload(st.vscale, hscale.data(), sizeof(double) * 2 * nrhs, s);
-        launch_copy_convert(c, V, TM_F64, V, TM_F64, 2 * nrhs, st.vscale, s);
+        next_vector(f, V, zin, V, st.vscale);
         int j = 0;
         for (; j < m && total < p.maxiter; j++) {
             double2 *vj = V + (size_t)j * vs;
-            // w = M z_j, z_j = N(v_j) (FP32) or v_j
+            // w = M z_j, z_j = N(v_j) (zin: v_j in FP32) or v_j
             if (ptc) {
                 float2 *zj = Z + (size_t)j * vs;
-                launch_copy_convert(c, zin, TM_F32, vj, TM_F64, 2 * nrhs, nullptr, s);
                 ptc_apply_halves(c, zin, zin + f.hs, zj, zj + f.hs, nrhs, s);
                 launch_copy_convert(c, zt, TM_F64, zj, TM_F32, 2 * nrhs, nullptr, s);
                 apply_M(f, w, zt, epsp);
@@ -373,11 +437,10 @@ SolveOut fgmres_halves(tm_ctx *c, void *xe, void *xo, const void *be, const void
             }
             // classical Gram-Schmidt against v_0..v_j, then |w|^2
             mdot(f, V, vs, j + 1, w, st.dots, m + 1, 0);
-            maxpy(f, w, V, vs, j + 1, st.dots, m + 1, -1.0);
-            mdot(f, w, vs, 1, w, st.dots, m + 1, j + 1);
+            maxpy(f, w, V, vs, j + 1, st.dots, m + 1, -1.0, st.dots + j + 1);
             hipLaunchKernelGGL(k_arnoldi, dim3((nrhs + 63) / 64), dim3(64), 0, s, st, j, m, nrhs);
             TM_HIP(hipGetLastError());
-            launch_copy_convert(c, V + (size_t)(j + 1) * vs, TM_F64, w, TM_F64, 2 * nrhs, st.vscale, s);
+            next_vector(f, V + (size_t)(j + 1) * vs, zin, w, st.vscale);
             total++;
             for (int r = 0; r < nrhs; r++) iters[r] += act[r];
             download(c, act.data(), st.active, sizeof(int) * nrhs, s);
