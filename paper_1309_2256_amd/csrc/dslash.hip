@@ -44,12 +44,14 @@ constexpr int kSites = 64;   // output half-sites of a block
 // bounded by the LDS exchange (24 KB per block in FP32, 48 KB in FP64, of
 // 160 KB) and by the registers (512 / waves per lane).  FP16 spinors, 32^3 x 64,
 // 12 right-hand sides: normal operator 2026 us with five, 1974 with six.  FP32
-// and BF16 spill with five.
+// and BF16 spill with five; BF16 with one right-hand side per block, which does
+// not hold the links, fits six.
 template <typename SS, typename LS, typename T, bool ONE = false>
 constexpr int waves_for()
 {
     if (sizeof(T) == 8) return ONE && !std::is_same<LS, L8D>::value ? 4 : 3;
-    return std::is_same<SS, h2>::value && !std::is_same<LS, float2>::value ? 6 : 4;
+    if (std::is_same<SS, float2>::value || std::is_same<LS, float2>::value) return 4;
+    return std::is_same<SS, h2>::value || ONE ? 6 : 4;
 }
 
 // 16-byte aligned so that an array of records keeps every complex field
@@ -1245,7 +1247,10 @@ void launch_epi(const DslashCall &dc, dim3 grid, hipStream_t s, const DParams<T>
 }
 
 // Right-hand sides per block (at most), for instances given as (site blocks,
-// nrhs) and `slots` resident blocks: every instance splits its right-hand
+// nrhs) and `slots` resident blocks (slots_one where a block takes a single
+// right-hand side: half a link set less in registers; BF16, 12 x 20 x 14 x 22, 5
+// right-hand sides: 53.4 us for the normal operator at one per block, 63 at
+// two, 72 at three, 69 at five): every instance splits its right-hand
 // sides evenly over the fewest blocks that keep the limit.  More of them per
 // block share one load and one rebuild of the links and keep the resident
 // blocks on fewer sites, so that neighbouring blocks find each other's spinors
@@ -1259,7 +1264,7 @@ int even_split(int nrhs, int most)
     const int groups = (nrhs + most - 1) / most;
     return (nrhs + groups - 1) / groups;
 }
-int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots)
+int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long slots_one)
 {
     int top = 1, best = 1;
     for (const auto &[nb, nrhs] : inst) top = std::max(top, nrhs);
@@ -1273,7 +1278,7 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots)
             length += (double)nb * (g + nrhs);
             longest = std::max(longest, 1 + rpb);
         }
-        const double cost = std::max((double)longest, std::ceil(blocks / slots) * length / blocks);
+        const double cost = std::max((double)longest, std::ceil(blocks / (lim == 1 ? slots_one : slots)) * length / blocks);
         if (lim == 1 || cost < least) {
             least = cost;
             best = lim;
@@ -1282,8 +1287,8 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots)
     return best;
 }
 
-template <typename SS, typename LS, typename T>
-constexpr long slots_of() { return 256 * waves_for<SS, LS, T>(); }
+template <typename SS, typename LS, typename T, bool ONE = false>
+constexpr long slots_of() { return 256 * waves_for<SS, LS, T, ONE>(); }
 
 template <typename SS, typename LS, typename T>
 DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
@@ -1324,7 +1329,7 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
 template <typename SS, typename LS, typename T>
 void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
 {
-    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>());
+    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(), slots_of<SS, LS, T, true>());
     if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
@@ -1615,7 +1620,7 @@ int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst)
 {
     std::vector<std::pair<int, int>> v;
     for (const auto &[c, nrhs] : inst) v.push_back({dslash_site_blocks(c), nrhs});
-    return rhs_per_block(v, slots_of<h2, L12, float>());
+    return rhs_per_block(v, slots_of<h2, L12, float>(), slots_of<h2, L12, float>());
 }
 
 void dslash_cost(tm_ctx *c, const DslashCall &dc, double &bytes, double &flops)
