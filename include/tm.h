@@ -178,8 +178,7 @@ int tm_dslash(tm_ctx *ctx, void *out, const void *in, int nrhs, int kind, int mu
 /* tm_dslash without device allocation, for callers that cannot allocate
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, operator and results as tm_dslash (the same
- * kernels; the right-hand-side tile is the tuned one when tm_dslash already
- * tuned this case, else the default, bit-identical either way).  The
+ * kernels).  The
  * intermediate fields of TM_SCHUR, TM_SCHUR_DAG (one half field of nrhs in
  * spinor_prec), TM_NORMAL (two) and TM_FULL/TM_FULL_DAG (four FP64 half
  * fields), each rounded up to 256 bytes, come from one 64 MiB device array
@@ -433,7 +432,7 @@ int tm_batch_loops(tm_batch *batch, const tm_loop_params *p, double *const *loop
 
 /* Arithmetic of the network's forward pass (tm_ptc_apply, the FGMRES
  * preconditioner, the training forward): TM_F32 (default; FP32 weights and
- * fields on the vector units) or TM_BF16 (the spin mixing u_k = sum_k'
+ * fields, ascending FP32 FMA chains on the matrix cores) or TM_BF16 (the spin mixing u_k = sum_k'
  * A[k][k'] T_k' psi on the matrix cores, v_mfma_f32_16x16x32_bf16: A and the
  * transported fields rounded to bfloat16, FP32 accumulation; transports and
  * the gather stay FP32).  Gradients are FP32/FP64 either way.  TM_ERR_ARG for

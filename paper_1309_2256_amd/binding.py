@@ -271,7 +271,7 @@ class Context:
                                        W2.ctypes.data_as(_dp)))
 
     def ptc_set_arith(self, prec):
-        """Network forward arithmetic: TM_F32 (vector units) or TM_BF16 (matrix cores)."""
+        """Network forward arithmetic: TM_F32 or TM_BF16 operands (both on the matrix cores)."""
         self._check(tm_ptc_set_arith(self.h, prec))
 
     def ptc_get_weights(self, nc):
