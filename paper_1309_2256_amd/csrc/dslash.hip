@@ -1287,8 +1287,12 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long
     return best;
 }
 
+// FP64 counts the same blocks for both forms: hops of 4 right-hand sides of
+// 16^3 x 32 take longer with one of them per block than with two
+// (preconditioned FGMRES 109.1 ms against 107.2), although four blocks fit
+// instead of three
 template <typename SS, typename LS, typename T, bool ONE = false>
-constexpr long slots_of() { return 256 * waves_for<SS, LS, T, ONE>(); }
+constexpr long slots_of() { return 256 * waves_for<SS, LS, T, ONE && sizeof(T) == 4>(); }
 
 template <typename SS, typename LS, typename T>
 DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
