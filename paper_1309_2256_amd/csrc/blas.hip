@@ -135,24 +135,26 @@ __global__ __launch_bounds__(kBlock) void k_finish_beta(CGScalars *sc, const dou
     cgdev::finish_beta(sc, part, nblk, nrhs, delta, blockIdx.x);
 }
 
-template <typename S>
-__global__ __launch_bounds__(kBlock) void k_update_p(S *pout, const S *pin, const S *rv, size_t n, const CGScalars *sc)
-{
-    cgdev::update_p(pout, pin, rv, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
-                    (size_t)gridDim.x * kBlock);
-}
-
 struct RingArg {
     void *p[kCgRing];
     __device__ void *operator[](int q) const { return p[q]; }
 };
 
-template <int M, typename S, typename XS>
-__global__ __launch_bounds__(kBlock) void k_update_px(const RingArg ring, const S *rv, XS *x, size_t n,
-                                                      const CGScalars *sc)
+// M = 0: position pos before the last of the ring; else its end, M directions.
+// BETA: beta from the partial sums in every block instead of from a launch of
+// its own, 4 to 5 us in the chain of an iteration.
+template <int M, bool BETA, typename S, typename XS>
+__global__ __launch_bounds__(kBlock) void k_update(const RingArg ring, int pos, const S *rv, XS *x, size_t n,
+                                                   const CGScalars *sc, const double *part, int nblk, int nrhs,
+                                                   double delta)
 {
-    cgdev::update_px<M, S>(ring, rv, x, n, sc, blockIdx.y, (size_t)blockIdx.x * kBlock + threadIdx.x, n,
-                           (size_t)gridDim.x * kBlock);
+    const int r = blockIdx.y;
+    const cgdev::NextBeta nb = BETA ? cgdev::next_beta(sc, part, nblk, nrhs, delta, r) : cgdev::stored_beta(sc, r);
+    const size_t e0 = (size_t)blockIdx.x * kBlock + threadIdx.x, step = (size_t)gridDim.x * kBlock;
+    if constexpr (M == 0)
+        cgdev::update_p((S *)ring[pos + 1], (const S *)ring[pos], rv, n, nb, r, e0, n, step);
+    else
+        cgdev::update_px<M, S>(ring, rv, x, n, sc, nb, r, e0, n, step);
 }
 
 template <typename S, typename XS>
@@ -205,10 +207,11 @@ __global__ __launch_bounds__(kBlock) void k_update_multi(const TailArgs<S, XS> a
     const int r = local / gx, bx = local - r * gx;
     const size_t e0 = (size_t)bx * kBlock + threadIdx.x, step = (size_t)gx * kBlock;
     if constexpr (M == 0)
-        cgdev::update_p((S *)a.ring[i][a.pos + 1], (const S *)a.ring[i][a.pos], a.r[i], a.n[i], a.sc[i], r, e0, a.n[i],
-                        step);
+        cgdev::update_p((S *)a.ring[i][a.pos + 1], (const S *)a.ring[i][a.pos], a.r[i], a.n[i],
+                        cgdev::stored_beta(a.sc[i], r), r, e0, a.n[i], step);
     else
-        cgdev::update_px<M, S>(a.ring[i], a.r[i], a.x[i], a.n[i], a.sc[i], r, e0, a.n[i], step);
+        cgdev::update_px<M, S>(a.ring[i], a.r[i], a.x[i], a.n[i], a.sc[i], cgdev::stored_beta(a.sc[i], r), r, e0, a.n[i],
+                               step);
 }
 
 // complex elements of one right-hand side of a half field, pads included
@@ -455,7 +458,7 @@ void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &by
 }
 
 void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,
-               const CGScalars *sc, hipStream_t s)
+               const CGScalars *sc, hipStream_t s, const double *part, int nblk, double delta)
 {
     const size_t n = half_elems(c);
     dim3 grid(grid_for(n), nrhs);
@@ -468,12 +471,12 @@ void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, i
         using S = std::remove_pointer_t<decltype(ts)>;
         using XS = std::remove_pointer_t<decltype(tx)>;
         ring_form<S>(ring.m, pos, [&](auto m) {
-            if constexpr (m() == 0)
-                hipLaunchKernelGGL(k_update_p<S>, grid, dim3(kBlock), 0, s, (S *)ring.p[pos + 1],
-                                   (const S *)ring.p[pos], (const S *)r, n, sc);
+            if (part)
+                hipLaunchKernelGGL((k_update<m(), true, S, XS>), grid, dim3(kBlock), 0, s, a, pos, (const S *)r,
+                                   (XS *)x, n, sc, part, nblk, nrhs, delta);
             else
-                hipLaunchKernelGGL((k_update_px<m(), S, XS>), grid, dim3(kBlock), 0, s, a, (const S *)r, (XS *)x, n,
-                                   sc);
+                hipLaunchKernelGGL((k_update<m(), false, S, XS>), grid, dim3(kBlock), 0, s, a, pos, (const S *)r,
+                                   (XS *)x, n, sc, part, nblk, nrhs, delta);
         });
     });
     TM_HIP(hipGetLastError());

@@ -152,18 +152,45 @@ __device__ __forceinline__ void finish_beta(CGScalars *sc, const double *part, i
     }
 }
 
+// what finish_beta will leave: whether right-hand side r iterates on, and beta;
+// in every thread
+struct NextBeta {
+    bool active;
+    double beta;
+};
+__device__ __forceinline__ NextBeta next_beta(const CGScalars *sc, const double *part, int nblk, int nrhs, double delta,
+                                              int r)
+{
+    __shared__ NextBeta next;
+    const CGScalars &s = sc[r];
+    const int active = ld_coh(&s.active);
+    const double rr_old = ld_coh(&s.rr), target2 = ld_coh(&s.target2);
+    const double rr = sum_partials(part, nblk, r);
+    const double rho2 = delta > 0 ? 0.0 : sum_partials(part, nblk, nrhs + r);
+    if (threadIdx.x == 0) {
+        next.active = active && (delta > 0 || !(rho2 <= target2));
+        next.beta = active && rr_old > 0 ? rr / rr_old : 0.0;
+    }
+    __syncthreads();
+    return next;
+}
+__device__ __forceinline__ NextBeta stored_beta(const CGScalars *sc, int r)
+{
+    return {ld_coh(&sc[r].active) != 0, ld_coh(&sc[r].beta)};
+}
+
 // The vector updates of one iteration for elements e0, e0 + step, ... < e1 of
 // right-hand side r (n complex per right-hand side).  Elementwise: any split of
 // the range gives the same result.
 
 // pout = rv + beta pin (the solution follows at the end of the ring)
 template <typename S>
-__device__ __forceinline__ void update_p(S *pout, const S *pin, const S *rv, size_t n, const CGScalars *sc, int r,
-                                         size_t e0, size_t e1, size_t step)
+__device__ __forceinline__ void update_p(S *pout, const S *pin, const S *rv, size_t n, NextBeta nb, int r, size_t e0,
+                                         size_t e1, size_t step)
 {
     using T = typename StoreTraits<S>::real;
-    if (!ld_coh(&sc[r].active)) return;
-    const T b = (T)ld_coh(&sc[r].beta);
+    if (!nb.active) return;
+    const T b = (T)nb.beta;
     const size_t base = (size_t)r * n;
     for (size_t e = e0; e < e1; e += step) {
         const cx<T> pv = ldT<T>(pin, base + e);
@@ -175,12 +202,12 @@ __device__ __forceinline__ void update_p(S *pout, const S *pin, const S *rv, siz
 // p[0] = rv + beta p[M - 1], or the last direction that moved x if the
 // right-hand side is no longer active.  ring: its M buffers (S *const *).
 template <int M, typename S, typename XS, typename R>
-__device__ __forceinline__ void update_px(const R &ring, const S *rv, XS *x, size_t n, const CGScalars *sc, int r,
-                                          size_t e0, size_t e1, size_t step)
+__device__ __forceinline__ void update_px(const R &ring, const S *rv, XS *x, size_t n, const CGScalars *sc, NextBeta nb,
+                                          int r, size_t e0, size_t e1, size_t step)
 {
     using T = typename StoreTraits<S>::real;
     using TX = typename StoreTraits<XS>::real;
-    const bool active = ld_coh(&sc[r].active) != 0;
+    const bool active = nb.active;
     double h[M];
     bool any = active;
     int last = 0;
@@ -190,7 +217,7 @@ __device__ __forceinline__ void update_px(const R &ring, const S *rv, XS *x, siz
         if (h[q] != 0.0) any = true, last = q;
     }
     if (!any) return;
-    const T b = active ? (T)ld_coh(&sc[r].beta) : (T)0;
+    const T b = active ? (T)nb.beta : (T)0;
     const size_t base = (size_t)r * n;
     for (size_t e = e0; e < e1; e += step) {
         const size_t k = base + e;

@@ -66,7 +66,7 @@ struct alignas(16) DParams {
     int p;          // output parity
     int nrhs;
     int rpb;        // right-hand sides per block
-    int alpha;      // see DslashCall
+    int alpha;      // see DslashCall; -1: its beta
     int ngroups;    // right-hand-side groups, ceil(nrhs / rpb)
     cx<T> own_u, own_l, hop_u, hop_l;
     // +1, passed at run time so that the +-1 factors of the spin projection
@@ -75,7 +75,10 @@ struct alignas(16) DParams {
     T one;
     // fused epilogues: partial sums [quantity][rhs][site block]
     void *r;        // EPI_CG: normal residual, updated in place; EPI_RES: b
-    void *rho;      // EPI_CG: Schur residual, updated in place
+    union {
+        void *rho;     // EPI_CG: Schur residual, updated in place
+        double delta;  // beta step: threshold of the reliable updates
+    };
     const CGScalars *sc;
     double *part;
     int nblk;       // site blocks
@@ -978,8 +981,8 @@ __device__ __forceinline__ void dslash_block(const DParams<T> &a, int bhw, int n
 }
 
 // The blocks past the launch's own nblk * ngroups, one per right-hand side:
-// alpha from the partial sums of an earlier launch, which the hops of this one
-// do not read.  A launch of its own cost 3 to 5 us in the chain of an
+// alpha, or the beta step, from the partial sums of an earlier launch, which the
+// hops of this one do not read.  A launch of its own cost 3 to 5 us in the chain of an
 // iteration.  True: block `over` had nothing else to do.
 template <int DAG, int OWN, int EPI, typename T>
 __device__ __forceinline__ bool alpha_block(const DParams<T> &a, int over)
@@ -988,9 +991,12 @@ __device__ __forceinline__ bool alpha_block(const DParams<T> &a, int over)
     if constexpr (DAG == 1 && OWN == 0 && EPI == EPI_STORE)
         if (a.alpha > 0 && over < a.nrhs)
             cgdev::finish_alpha(const_cast<CGScalars *>(a.sc), a.part, a.nblk, a.alpha - 1, over);
+    if constexpr (DAG == 0 && OWN == 0 && EPI == EPI_STORE)
+        if (a.alpha < 0 && over < a.nrhs)
+            cgdev::finish_beta(const_cast<CGScalars *>(a.sc), a.part, a.nblk, a.nrhs, a.delta, over);
     return true;
 }
-int alpha_blocks(const DslashCall &dc) { return dc.alpha > 0 ? dc.nrhs : 0; }
+int alpha_blocks(const DslashCall &dc) { return dc.alpha > 0 || dc.beta > 0 ? dc.nrhs : 0; }
 
 template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI, bool ONE>
 __global__ __launch_bounds__(kBlock, (waves_for<SS, LS, T, ONE>())) void k_dslash(DParams<T> a)
@@ -1179,17 +1185,18 @@ __device__ __forceinline__ void persist_update(const PersistArgs<T> &a, int pos)
         const SS *rv = (const SS *)p3.r;
         float2 *x = (float2 *)a.x[i];
         void *const *ring = a.ring[i];
+        const cgdev::NextBeta nb = cgdev::stored_beta(a.sc[i], r);
         if (pos < a.m - 1)
-            cgdev::update_p((SS *)ring[pos + 1], (const SS *)ring[pos], rv, n, a.sc[i], r, e0 + threadIdx.x, e1,
+            cgdev::update_p((SS *)ring[pos + 1], (const SS *)ring[pos], rv, n, nb, r, e0 + threadIdx.x, e1,
                             (size_t)kBlock);
         else if (a.m == 8)
-            cgdev::update_px<8, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+            cgdev::update_px<8, SS>(ring, rv, x, n, a.sc[i], nb, r, e0 + threadIdx.x, e1, (size_t)kBlock);
         else if (a.m == 4)
-            cgdev::update_px<4, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+            cgdev::update_px<4, SS>(ring, rv, x, n, a.sc[i], nb, r, e0 + threadIdx.x, e1, (size_t)kBlock);
         else if (a.m == 2)
-            cgdev::update_px<2, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+            cgdev::update_px<2, SS>(ring, rv, x, n, a.sc[i], nb, r, e0 + threadIdx.x, e1, (size_t)kBlock);
         else
-            cgdev::update_px<1, SS>(ring, rv, x, n, a.sc[i], r, e0 + threadIdx.x, e1, (size_t)kBlock);
+            cgdev::update_px<1, SS>(ring, rv, x, n, a.sc[i], nb, r, e0 + threadIdx.x, e1, (size_t)kBlock);
     }
 }
 
@@ -1320,10 +1327,13 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
     a.hop_l = cvt<T>(dc.d_hop.l);
     a.one = (T)1;
     a.r = dc.r;
-    a.rho = dc.rho;
+    if (dc.beta)
+        a.delta = dc.delta;
+    else
+        a.rho = dc.rho;
     a.sc = dc.sc;
     a.part = dc.part;
-    a.alpha = dc.alpha;
+    a.alpha = dc.beta ? -1 : dc.alpha;
     a.nblk = dslash_site_blocks(c);
     a.nb_t = (c->geo.vsh % kSites == 0 && (c->geo.vsh / kSites) % 8 == 0) ? c->geo.vsh / kSites : 0;
     a.t_bc = c->t_bc;
@@ -1338,6 +1348,7 @@ void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
     TM_REQUIRE(dc.alpha == 0 || (dc.dag && !dc.has_own), "alpha is summed beside the dag hops only");
+    TM_REQUIRE(dc.beta == 0 || (!dc.dag && !dc.has_own), "beta is summed beside the plain hops only");
     dim3 grid((unsigned)(a.nblk * a.ngroups + alpha_blocks(dc)));
     // separate kernels per projector placement and per presence of the
     // own-site term (the x - H y forms read one more field)

@@ -458,8 +458,13 @@ std::vector<double> Solver::true_residual(hipStream_t s)
 
 void Solver::iteration_tail(hipStream_t s)
 {
-    cg_finish_beta(c, w.dsc, w.partb, nsb, nrhs, delta, s);
-    cg_update(c, w.ring, w.pos, w.r, w.x, w.prec, w.xprec, nrhs, w.dsc, s);
+    if (beta_late) {
+        cg_update(c, w.ring, w.pos, w.r, w.x, w.prec, w.xprec, nrhs, w.dsc, s, w.partb, nsb, delta);
+        beta_due = true;
+    } else {
+        cg_finish_beta(c, w.dsc, w.partb, nsb, nrhs, delta, s);
+        cg_update(c, w.ring, w.pos, w.r, w.x, w.prec, w.xprec, nrhs, w.dsc, s);
+    }
     w.pos = (w.pos + 1) % w.ring.m;
 }
 
@@ -473,7 +478,15 @@ void Solver::end_round(hipStream_t s)
 
 void Solver::iteration(hipStream_t s)
 {
-    launch_dslash(c, stage(1, w.pos), s);
+    DslashCall first = stage(1, w.pos);
+    if (beta_due) {
+        first.sc = w.dsc;
+        first.part = w.partb;
+        first.beta = 1;
+        first.delta = delta;
+        beta_due = false;
+    }
+    launch_dslash(c, first, s);
     launch_dslash(c, stage(2, w.pos), s);
     launch_dslash(c, stage(3, w.pos), s);
     launch_dslash(c, stage(4, w.pos), s);
@@ -512,6 +525,8 @@ bool Solver::due() const { return since_check >= check_every || total >= p.maxit
 void Solver::check(hipStream_t s)
 {
     since_check = 0;
+    if (beta_due) cg_finish_beta(c, w.dsc, w.partb, nsb, nrhs, delta, s);
+    beta_due = false;
     end_round(s);
     download(c, hsc.data(), w.dsc, sizeof(CGScalars) * nrhs, s);
     bool any_active = false, any_update = false, any_bad = false;
@@ -598,6 +613,9 @@ SolveOut solve_halves(tm_ctx *c, void *xe, void *xo, const void *be, const void 
     if (p.solver == TM_FGMRES || p.solver == TM_FGMRES_PTC) return fgmres_halves(c, xe, xo, be, bo, nrhs, p, s);
     Solver S;
     S.init(c, xe, xo, be, bo, nrhs, p, s);
+    // the sum in every block of the update costs nsb loads a block: up to 2048
+    // partial sums that is less than a launch
+    S.beta_late = S.nsb <= 2048;
     while (!S.done) {
         S.iteration(s);
         S.count_iteration();

@@ -441,6 +441,11 @@ struct DslashCall {
     // per right-hand side sums `part` (|q|^2 of an earlier launch) and sets
     // alpha in sc, for ring position alpha - 1, while the others hop
     int alpha = 0;
+    // store forms without dag and own-site term: if > 0, one more block per
+    // right-hand side runs the beta step of the iteration before on `part`
+    // ([2][nrhs][blocks]) with the threshold delta (which may be 0)
+    int beta = 0;
+    double delta = 0;
     // FP64 only: read all 18 parameters of the FP64 links whatever the
     // format (the exact operator for reliable updates and true residuals)
     bool links18 = false;
@@ -566,9 +571,11 @@ void cg_finish_beta(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int 
 // position pos < m - 1: p[pos + 1] = r + beta p[pos]; last position:
 // x += sum_q hist[q] p[q], p[0] = r + beta p[m - 1].  A right-hand side that
 // is no longer active keeps its last direction, in p[0] from the end of the
-// ring on.
+// ring on.  part: null, the beta step has run; else its partial sums, of nblk
+// blocks: every block of the update forms beta itself, and the beta step follows
+// later (with the next iteration's first launch).
 void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,
-               const CGScalars *sc, hipStream_t s);
+               const CGScalars *sc, hipStream_t s, const double *part = nullptr, int nblk = 0, double delta = 0);
 // bytes and flops of cg_update per complex element at one position
 void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &bytes, double &flops);
 // x += sum of the first cnt directions, p[cnt] the current direction of every
