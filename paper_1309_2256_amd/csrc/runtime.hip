@@ -182,7 +182,8 @@ namespace {
 //   t = R^-1(-eps) g5 H^dag q      (+ alpha = rr / |q|^2)      D3
 //   s = R(-eps) q + kappa g5 H t,
 //     r -= alpha s, rho -= alpha q (+ partial |r|^2, |rho|^2)  D4
-//   beta, convergence / update flags                            finish
+//   beta, convergence / update flags                            finish, or (small
+//     lattices) in the update and beside the next iteration's D1
 //   p = r + beta p, at the end of the ring x += sum alpha p     update
 DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage, int pos)
 {
