@@ -338,9 +338,19 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
         w.ring.p[0] = ws_get(c, "s_p_lo", fl);
         w.tmp = ws_get(c, "s_t_lo", fl);
         // the longest ring that ends at every check; without the memory for
-        // it x is updated in every iteration
+        // it (and for what a loop call allocates after its first solve, up to
+        // eight FP64 fields) x is updated in every iteration
         w.ring.m = check_every % 8 == 0 ? 8 : check_every % 4 == 0 ? 4 : check_every % 2 == 0 ? 2 : 1;
         static_assert(kCgRing == 8, "ring lengths");
+        if (w.ring.m > 1) {
+            const size_t need = fl * (w.ring.m - 1);
+            const auto have = c->ws.find("s_p_ring");
+            size_t spare = 0, all = 0;
+            if (have == c->ws.end() || have->second.bytes < need) {
+                TM_HIP(hipMemGetInfo(&spare, &all));
+                if (spare < need + 8 * f64) w.ring.m = 1;
+            }
+        }
         if (w.ring.m > 1) {
             try {
                 char *more = (char *)ws_get(c, "s_p_ring", fl * (w.ring.m - 1));
