@@ -349,8 +349,7 @@ struct BufIO<b2> {
     template <typename T>
     __device__ __forceinline__ static void st(rsrc_t r, int voff, int soff, cx<T> c)
     {
-        unsigned v = (unsigned)f32_to_bf16((float)c.r) | ((unsigned)f32_to_bf16((float)c.i) << 16);
-        __builtin_amdgcn_raw_buffer_store_b32(v, r, voff, soff, kNT);
+        __builtin_amdgcn_raw_buffer_store_b32(bf16_pair((float)c.r, (float)c.i), r, voff, soff, kNT);
     }
 };
 
@@ -658,7 +657,8 @@ __device__ __forceinline__ cx<T> stored(cx<T> v)
     } else if constexpr (std::is_same<SS, h2>::value) {
         return {(T)(float)(_Float16)(float)v.r, (T)(float)(_Float16)(float)v.i};
     } else {
-        return {(T)bf16_to_f32(f32_to_bf16((float)v.r)), (T)bf16_to_f32(f32_to_bf16((float)v.i))};
+        const b2 s = __builtin_bit_cast(b2, bf16_pair((float)v.r, (float)v.i));
+        return {(T)bf16_to_f32(s.x), (T)bf16_to_f32(s.y)};
     }
 }
 
