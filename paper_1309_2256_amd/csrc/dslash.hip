@@ -40,6 +40,21 @@ namespace {
 
 constexpr int kBlock = 256;  // four waves, one per direction mu
 constexpr int kSites = 64;   // output half-sites of a block
+// A single right-hand side per block has a form of its own (ONE: the links are
+// loaded where they are used, the summing waves keep a colour in registers) where
+// that is the faster one: 12-parameter links, whose rebuilt rows then take no
+// registers across the hops (BF16 Schur operator, one right-hand side, 24^3 x 48,
+// 48 -> 40 us), BF16 with binary16 links, and the exact FP64 links, for the
+// residuals (a truncated solve of one right-hand side on 32^3 x 16 2.40 ms
+// against 2.45).  Otherwise links with all their parameters, or with eight, are
+// better loaded ahead of the spinors' arithmetic, as for several: Schur operator,
+// 32^3 x 16, one right-hand side, FP32 93 -> 90 us, FP64 with 8 parameters 123 ->
+// 120, BF16 with FP32 links 74 -> 72.
+template <typename SS, typename LS>
+constexpr bool kOneForm = std::is_same<LS, L12>::value || std::is_same<LS, L12D>::value || std::is_same<LS, L12F>::value ||
+                          std::is_same<LS, double2>::value ||
+                          (std::is_same<SS, b2>::value && std::is_same<LS, h2>::value);
+
 // resident blocks per CU (and waves per SIMD) requested from the compiler:
 // bounded by the LDS exchange (24 KB per block in FP32, 48 KB in FP64, of
 // 160 KB) and by the registers (512 / waves per lane).  FP16 spinors, 32^3 x 64,
@@ -49,7 +64,7 @@ constexpr int kSites = 64;   // output half-sites of a block
 template <typename SS, typename LS, typename T, bool ONE = false>
 constexpr int waves_for()
 {
-    if (sizeof(T) == 8) return ONE && !std::is_same<LS, L8D>::value ? 4 : 3;
+    if (sizeof(T) == 8) return ONE ? 4 : 3;
     if (std::is_same<SS, float2>::value || std::is_same<LS, float2>::value) return 4;
     return std::is_same<SS, h2>::value || ONE ? 6 : 4;
 }
@@ -1234,10 +1249,12 @@ cx<T> cvt(cx<double> v)
 template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
 void launch_form(dim3 grid, hipStream_t s, const DParams<T> &a)
 {
-    if (a.rpb == 1)
-        hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, true>), grid, dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, false>), grid, dim3(kBlock), 0, s, a);
+    if constexpr (kOneForm<SS, LS>)
+        if (a.rpb == 1) {
+            hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, true>), grid, dim3(kBlock), 0, s, a);
+            return;
+        }
+    hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, false>), grid, dim3(kBlock), 0, s, a);
 }
 
 template <typename SS, typename LS, typename T, int DAG, int OWN>
@@ -1294,12 +1311,21 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long
     return best;
 }
 
-// FP64 counts the same blocks for both forms: hops of 4 right-hand sides of
-// 16^3 x 32 take longer with one of them per block than with two
-// (preconditioned FGMRES 109.1 ms against 107.2), although four blocks fit
-// instead of three
-template <typename SS, typename LS, typename T, bool ONE = false>
-constexpr long slots_of() { return 256 * waves_for<SS, LS, T, ONE && sizeof(T) == 4>(); }
+// The blocks that the limit of one counts with (see kOneForm).  BF16: six per CU
+// with 12-parameter links; 5.5 with full ones, where blocks of one load half as
+// much again (32^3 x 64, 3 right-hand sides: 409 us for the Schur operator at one
+// per block, 354 at three; counting six took one).  FP64: as for several,
+// although four blocks fit instead of three, since each rebuilds its rows in FP64
+// (16^3 x 32, 4 right-hand sides: 78 us at one per block, 74 at two; counting
+// four made 21 of 290 calls slower, by up to 16%).
+template <typename SS, typename LS, typename T>
+constexpr long slots_of() { return 256 * waves_for<SS, LS, T>(); }
+template <typename SS, typename LS, typename T>
+constexpr long slots_of_one()
+{
+    if (sizeof(T) == 8 || !kOneForm<SS, LS>) return slots_of<SS, LS, T>();
+    return 256 * waves_for<SS, LS, T, true>() - (std::is_same<LS, h2>::value ? 128 : 0);
+}
 
 template <typename SS, typename LS, typename T>
 DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
@@ -1343,7 +1369,7 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
 template <typename SS, typename LS, typename T>
 void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
 {
-    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(), slots_of<SS, LS, T, true>());
+    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(), slots_of_one<SS, LS, T>());
     if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
