@@ -142,7 +142,7 @@ struct RingArg {
 
 // M = 0: position pos before the last of the ring; else its end, M directions.
 // BETA: beta from the partial sums in every block instead of from a launch of
-// its own, 4 to 5 us in the chain of an iteration.
+// its own (see cg_beta_late).
 template <int M, bool BETA, typename S, typename XS>
 __global__ __launch_bounds__(kBlock) void k_update(const RingArg ring, int pos, const S *rv, XS *x, size_t n,
                                                    const CGScalars *sc, const double *part, int nblk, int nrhs,
@@ -455,6 +455,19 @@ void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &by
     const bool end = pos == ring.m - 1;
     bytes = (end ? ring.m + 2 : 3) * prec_bytes(prec) + (end ? 2 * prec_bytes(xprec) : 0);
     flops = end ? 4.0 * ring.m + 4 : 4.0;
+}
+
+// A launch of the beta step costs 1.5 us in the chain of an iteration; without it
+// every block of the update reads the partial sums of its right-hand side, with
+// reliable updates one quantity, else two.  The two break even at about 18 MB of
+// such reads (12 TB/s, from the L2): FP16 with reliable updates on 16^3 x 32 (1024
+// partial sums), an iteration of one right-hand side 37.3 us with the launch and
+// 36.0 without, of three (19 MB) 93.0 and 92.8, of 24 466 and 476; truncated, 24^4
+// (2592), 24 right-hand sides, 974 and 1086.
+bool cg_beta_late(tm_ctx *c, int nrhs, int nblk, double delta)
+{
+    const double blocks = (double)grid_for(half_elems(c)) * nrhs;
+    return blocks * nblk * sizeof(double) * (delta > 0 ? 1 : 2) <= 18e6;
 }
 
 void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,

@@ -71,9 +71,9 @@ struct Solver {
     tm_solve_params p{};
     int nrhs = 0, lp = 0, check_every = 8, nsb = 0, total = 0, since_check = 0;
     bool done = false;
-    // single solves on small lattices: the update forms beta itself, and the
-    // beta step runs beside the next iteration's first launch (beta_due until
-    // then) or before a check
+    // single solves with few partial sums (cg_beta_late): the update forms beta
+    // itself, and the beta step runs beside the next iteration's first launch
+    // (beta_due until then) or before a check
     bool beta_late = false, beta_due = false;
     double delta = 0, epsp = 0, t0 = 0;
     void *xe = nullptr, *xo = nullptr;

@@ -182,8 +182,8 @@ namespace {
 //   t = R^-1(-eps) g5 H^dag q      (+ alpha = rr / |q|^2)      D3
 //   s = R(-eps) q + kappa g5 H t,
 //     r -= alpha s, rho -= alpha q (+ partial |r|^2, |rho|^2)  D4
-//   beta, convergence / update flags                            finish, or (small
-//     lattices) in the update and beside the next iteration's D1
+//   beta, convergence / update flags                            finish, or (few
+//     partial sums) in the update and beside the next iteration's D1
 //   p = r + beta p, at the end of the ring x += sum alpha p     update
 DslashCall stage_call(tm_ctx *c, const CGWork &w, double epsp, int stage, int pos)
 {
@@ -624,9 +624,7 @@ SolveOut solve_halves(tm_ctx *c, void *xe, void *xo, const void *be, const void 
     if (p.solver == TM_FGMRES || p.solver == TM_FGMRES_PTC) return fgmres_halves(c, xe, xo, be, bo, nrhs, p, s);
     Solver S;
     S.init(c, xe, xo, be, bo, nrhs, p, s);
-    // the sum in every block of the update costs nsb loads a block: up to 2048
-    // partial sums that is less than a launch
-    S.beta_late = S.nsb <= 2048;
+    S.beta_late = cg_beta_late(c, nrhs, S.nsb, S.delta);
     while (!S.done) {
         S.iteration(s);
         S.count_iteration();

@@ -572,6 +572,8 @@ void cg_finish_beta(tm_ctx *c, CGScalars *sc, const double *part, int nblk, int 
 // later (with the next iteration's first launch).
 void cg_update(tm_ctx *c, const CgRing &ring, int pos, const void *r, void *x, int prec, int xprec, int nrhs,
                const CGScalars *sc, hipStream_t s, const double *part = nullptr, int nblk = 0, double delta = 0);
+// whether that form is the faster one for a solve's sizes
+bool cg_beta_late(tm_ctx *c, int nrhs, int nblk, double delta);
 // bytes and flops of cg_update per complex element at one position
 void cg_update_cost(const CgRing &ring, int pos, int prec, int xprec, double &bytes, double &flops);
 // x += sum of the first cnt directions, p[cnt] the current direction of every
