@@ -185,6 +185,10 @@ extern "C" int tm_create(tm_ctx **out, const tm_lattice *lat, int device)
     c->geo.by_lxh = fast_div(c->geo.lxh);
     c->geo.by_y = fast_div(lat->L[1]);
     c->geo.by_z = fast_div(lat->L[2]);
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || c->cus < 1) {
+        delete c;
+        return TM_ERR_HIP;
+    }
     c->kappa = lat->kappa;
     c->eps = lat->two_kappa_mu;
     c->t_bc = lat->t_bc;

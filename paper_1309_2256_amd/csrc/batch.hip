@@ -120,7 +120,7 @@ int choose_rpb(const std::vector<Solver> &S, const std::vector<int> &set)
         if (atoi(e) > 0) return atoi(e);
     std::vector<std::pair<tm_ctx *, int>> inst;
     for (int i : set) inst.push_back({S[i].c, S[i].nrhs});
-    return multi_rhs_per_block(inst);
+    return multi_rhs_per_block(inst, S[set[0]].lp);
 }
 
 void build_graph(tm_batch *b, std::vector<Solver> &S, const std::vector<int> &set, int iters)

@@ -1319,12 +1319,12 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long
 // (16^3 x 32, 4 right-hand sides: 78 us at one per block, 74 at two; counting
 // four made 21 of 290 calls slower, by up to 16%).
 template <typename SS, typename LS, typename T>
-constexpr long slots_of() { return 256 * waves_for<SS, LS, T>(); }
+long slots_of(const tm_ctx *c) { return (long)c->cus * waves_for<SS, LS, T>(); }
 template <typename SS, typename LS, typename T>
-constexpr long slots_of_one()
+long slots_of_one(const tm_ctx *c)
 {
-    if (sizeof(T) == 8 || !kOneForm<SS, LS>) return slots_of<SS, LS, T>();
-    return 256 * waves_for<SS, LS, T, true>() - (std::is_same<LS, h2>::value ? 128 : 0);
+    if (sizeof(T) == 8 || !kOneForm<SS, LS>) return slots_of<SS, LS, T>(c);
+    return (long)c->cus * waves_for<SS, LS, T, true>() - (std::is_same<LS, h2>::value ? c->cus / 2 : 0);
 }
 
 template <typename SS, typename LS, typename T>
@@ -1369,7 +1369,7 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
 template <typename SS, typename LS, typename T>
 void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
 {
-    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(), slots_of_one<SS, LS, T>());
+    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(c), slots_of_one<SS, LS, T>(c));
     if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
@@ -1512,11 +1512,10 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     pb.dev_args = ws_get(v[0].c, "persist_args", sizeof(a));
     TM_HIP(hipMemcpy(pb.dev_args, &a, sizeof(a), hipMemcpyHostToDevice));
     // co-resident blocks of this instantiation: the grid of the cooperative launch
-    int per_cu = 0, ncu = 0;
+    int per_cu = 0;
     TM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_persist<SS, LS, T>, kBlock, 0));
-    TM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, v[0].c->device));
     if (pb.blocks_per_cu > 0) per_cu = std::min(per_cu, pb.blocks_per_cu);
-    const int cap = per_cu * ncu / 8 * 8;
+    const int cap = per_cu * v[0].c->cus / 8 * 8;
     TM_REQUIRE(cap >= 8, "the persistent batch kernel does not fit the device");
     pb.grid = std::min(cap, (pb.work + 7) / 8 * 8);
     }
@@ -1657,11 +1656,17 @@ bool persist_failed(const PersistBatch &pb, hipStream_t s)
 
 int dslash_site_blocks(tm_ctx *c) { return (c->geo.vh + kSites - 1) / kSites; }
 
-int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst)
+// launches over several lattices take the form of several right-hand sides per
+// block for one, too
+int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst, int prec)
 {
     std::vector<std::pair<int, int>> v;
     for (const auto &[c, nrhs] : inst) v.push_back({dslash_site_blocks(c), nrhs});
-    return rhs_per_block(v, slots_of<h2, L12, float>(), slots_of<h2, L12, float>());
+    tm_ctx *c = inst[0].first;
+    long slots = 0;
+    multi_dispatch(prec, recon12_ok(c, prec), recon8_wanted(c) && c->links8_usable,
+                   [&]<typename SS, typename LS, typename T>() { slots = slots_of<SS, LS, T>(c); });
+    return rhs_per_block(v, slots, slots);
 }
 
 void dslash_cost(tm_ctx *c, const DslashCall &dc, double &bytes, double &flops)

@@ -681,19 +681,19 @@ void forward_t(tm_ctx *c, const void *in_e, const void *in_o, float2 *out_e, flo
                     (float2 *)ws_get(c, "ptc_u1", sizeof(float2) * 9 * fl)};
     const S *in[2] = {(const S *)in_e, (const S *)in_o};
     const int tiles = (c->geo.vh + kXS - 1) / kXS;
-    TM_REQUIRE((long)tiles * nrhs <= 0x7fffffffL - 4 * 256, "batch too large for the spin-mixing grid");
+    TM_REQUIRE((long)tiles * nrhs <= 0x7fffffffL - 4 * c->cus, "batch too large for the spin-mixing grid");
     // grids: the resident blocks, each walks its tiles
     if (c->ptc_arith == TM_BF16) {
         const bf16x8 *frag = (const bf16x8 *)ws_get(c, "ptc_Afrag", sizeof(bf16x8) * kMT * kKS * 64);
         for (int p = 0; p < 2; p++) {
-            hipLaunchKernelGGL(k_ptc_mix_mfma<S>, dim3(std::min(tiles * nrhs, 4 * 256)), dim3(kBlock), 0, s, in[p],
+            hipLaunchKernelGGL(k_ptc_mix_mfma<S>, dim3(std::min(tiles * nrhs, 4 * c->cus)), dim3(kBlock), 0, s, in[p],
                                in[1 - p], (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
             TM_HIP(hipGetLastError());
         }
     } else {
         const float *frag = (const float *)ws_get(c, "ptc_Afrag32", sizeof(float) * 2 * kRT * kS32 * 64);
         for (int p = 0; p < 2; p++) {
-            hipLaunchKernelGGL(k_ptc_mix32<S>, dim3(std::min(tiles * nrhs, 3 * 256)), dim3(kBlock), 0, s, in[p],
+            hipLaunchKernelGGL(k_ptc_mix32<S>, dim3(std::min(tiles * nrhs, 3 * c->cus)), dim3(kBlock), 0, s, in[p],
                                in[1 - p], (const float2 *)c->links32[p], frag, u[p], c->geo, p, nrhs, tiles);
             TM_HIP(hipGetLastError());
         }

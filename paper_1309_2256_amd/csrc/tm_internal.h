@@ -323,6 +323,7 @@ struct tm_ctx {
     // links of the FP16/BF16-spinor kernels when no call overrides them
     // (tm_set_half_spinor_links): false = binary16 copy, true = FP32 (18)
     bool half_links_f32_default = false;
+    int cus = 256;  // compute units of the device (fewer in a partition)
     std::map<std::string, DevBuf> ws;
     std::string err;
     hipStream_t stream = nullptr;  // stream of the current loop-driver call
@@ -470,8 +471,8 @@ struct MultiDslash {
 constexpr int kMultiInst = 16;  // instances per launch (kernel-argument space)
 void multi_dslash_prepare(MultiDslash &m, const std::vector<tm_ctx *> &cs, const std::vector<DslashCall> &dcs, int rpb,
                           hipStream_t s);
-// right-hand sides per block of a launch over several (context, nrhs)
-int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst);
+// right-hand sides per block of a launch over several (context, nrhs) in prec
+int multi_rhs_per_block(const std::vector<std::pair<tm_ctx *, int>> &inst, int prec);
 void multi_dslash_launch(const MultiDslash &m, hipStream_t s);
 
 // The low-precision solvers keep the search directions of up to kCgRing
