@@ -1517,7 +1517,13 @@ void persist_fill(PersistBatch &pb, const std::vector<PersistInst> &v, hipStream
     if (pb.blocks_per_cu > 0) per_cu = std::min(per_cu, pb.blocks_per_cu);
     const int cap = per_cu * v[0].c->cus / 8 * 8;
     TM_REQUIRE(cap >= 8, "the persistent batch kernel does not fit the device");
-    pb.grid = std::min(cap, (pb.work + 7) / 8 * 8);
+    // about eight work items per block, at least a block per CU: a grid barrier
+    // takes longer the more blocks arrive (FP16, 16^3 x 32, 12^3 x 24 and 8^3 x 16,
+    // one right-hand side each, 1412 items: 12.0 ms a batch with 256 blocks, 12.8
+    // with 512, 21.0 with one per item; 12, 24 and 48 each, 5800 items: 46.3 with
+    // 768, 53.1 with 1536)
+    const int most = std::max(v[0].c->cus, pb.work / 8);
+    pb.grid = std::min(cap, (std::min(most, pb.work) + 7) / 8 * 8);
     }
 }
 
