@@ -21,20 +21,43 @@ void *ws_get(tm_ctx *c, const std::string &name, size_t bytes)
     }
     DevBuf &b = c->ws[name];
     if (b.p && b.bytes >= bytes) return b.p;
-    if (b.p) {
+    auto release = [c](DevBuf &d) {
         TM_HIP(hipDeviceSynchronize());
-        TM_HIP(hipFree(b.p));
-        b.p = nullptr;
-        b.bytes = 0;
-    }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes ? bytes : 16) != hipSuccess) {
+        TM_HIP(hipFree(d.p));
+        c->ws_total -= d.bytes;
+        d.p = nullptr;
+        d.bytes = 0;
+    };
+    auto allocate = [&]() -> void * {
+        void *p = nullptr;
+        if (c->ws_limit && c->ws_total + bytes > c->ws_limit) return nullptr;
+        if (hipMalloc(&p, bytes ? bytes : 16) == hipSuccess) return p;
         (void)hipGetLastError();
-        throw TmError{TM_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed (" + name + ")"};
+        return nullptr;
+    };
+    if (b.p) release(b);
+    void *p = allocate();
+    if (!p && c->ring_users == 0) {
+        // the ring of search directions only saves time: it makes room
+        auto ring = c->ws.find("s_p_ring");
+        if (ring != c->ws.end() && ring->second.p) {
+            release(ring->second);
+            p = allocate();
+        }
     }
+    if (!p) throw TmError{TM_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed (" + name + ")"};
     b.p = p;
     b.bytes = bytes;
+    c->ws_total += bytes;
     return p;
+}
+
+size_t ws_room(tm_ctx *c)
+{
+    size_t spare = 0, all = 0;
+    TM_HIP(hipMemGetInfo(&spare, &all));
+    if (c->ws_limit) spare = std::min(spare, c->ws_limit - std::min(c->ws_limit, c->ws_total));
+    return spare;
 }
 
 void *host_stage(tm_ctx *c, size_t bytes)
@@ -192,6 +215,7 @@ extern "C" int tm_create(tm_ctx **out, const tm_lattice *lat, int device)
     c->kappa = lat->kappa;
     c->eps = lat->two_kappa_mu;
     c->t_bc = lat->t_bc;
+    if (const char *e = getenv("TM_WORKSPACE_LIMIT")) c->ws_limit = strtoull(e, nullptr, 10);
     *out = c;
     return TM_OK;
 }

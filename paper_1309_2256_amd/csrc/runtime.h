@@ -80,6 +80,20 @@ struct Solver {
     const void *be = nullptr, *bo = nullptr;
     void *bh = nullptr, *t64 = nullptr, *rho64 = nullptr, *r64 = nullptr;
     double *dscale = nullptr;
+    // keeps the context's ring of search directions until finalize
+    struct RingUse {
+        tm_ctx *c = nullptr;
+        RingUse() = default;
+        RingUse(const RingUse &) = delete;
+        RingUse &operator=(const RingUse &) = delete;
+        ~RingUse() { hold(nullptr); }
+        void hold(tm_ctx *ctx)
+        {
+            if (c) c->ring_users--;
+            c = ctx;
+            if (c) c->ring_users++;
+        }
+    } ring_use;
     CGWork w{};
     std::vector<double> bn2, sigma, iter_res;
     std::vector<int> n_rel;

@@ -337,32 +337,27 @@ void Solver::init(tm_ctx *ctx, void *xe_, void *xo_, const void *be_, const void
         w.q = ws_get(c, "s_q_lo", fl);
         w.ring.p[0] = ws_get(c, "s_p_lo", fl);
         w.tmp = ws_get(c, "s_t_lo", fl);
-        // the longest ring that ends at every check; without the memory for
-        // it (and for what a loop call allocates after its first solve, up to
-        // eight FP64 fields) x is updated in every iteration
-        w.ring.m = check_every % 8 == 0 ? 8 : check_every % 4 == 0 ? 4 : check_every % 2 == 0 ? 2 : 1;
+        // the longest ring that ends at every check and either is there already,
+        // or takes no more than the FP64 vector that only plain solves need (m = 4
+        // in 16 bits, 2 in FP32) or an eighth of the free memory; without the
+        // memory x is updated in every iteration
         static_assert(kCgRing == 8, "ring lengths");
-        if (w.ring.m > 1) {
-            const size_t need = fl * (w.ring.m - 1);
-            const auto have = c->ws.find("s_p_ring");
-            size_t spare = 0, all = 0;
-            if (have == c->ws.end() || have->second.bytes < need) {
-                TM_HIP(hipMemGetInfo(&spare, &all));
-                if (spare < need + 8 * f64) w.ring.m = 1;
-            }
-        }
-        if (w.ring.m > 1) {
+        for (int m = kCgRing; m > 1 && w.ring.m == 1; m /= 2) {
+            const size_t need = fl * (m - 1);
+            if (check_every % m != 0) continue;
+            if (c->ws["s_p_ring"].bytes < need && need > f64 && need > ws_room(c) / 8) continue;
             try {
-                char *more = (char *)ws_get(c, "s_p_ring", fl * (w.ring.m - 1));
-                for (int q = 1; q < w.ring.m; q++) w.ring.p[q] = more + (q - 1) * fl;
+                char *more = (char *)ws_get(c, "s_p_ring", need);
+                w.ring.m = m;
+                for (int q = 1; q < m; q++) w.ring.p[q] = more + (q - 1) * fl;
                 // right-hand sides that do not iterate leave them unwritten,
                 // but the hop kernels read them
-                launch_zero(c, more, lp, nrhs * (w.ring.m - 1), s);
+                launch_zero(c, more, lp, nrhs * (m - 1), s);
             } catch (const TmError &e) {
                 if (e.status != TM_ERR_OOM) throw;
-                w.ring.m = 1;
             }
         }
+        if (w.ring.m > 1) ring_use.hold(c);
         restart(s, rho2, &rr);
     }
     bool any = false;
@@ -590,6 +585,7 @@ void Solver::check(hipStream_t s)
 
 SolveOut Solver::finalize(hipStream_t s)
 {
+    ring_use.hold(nullptr);
     const double kap = c->kappa;
     // odd reconstruction psi_o = R^-1 (b_o - H_oe psi_e)
     op_dslash(c, xo, xe, bo, nrhs, TM_F64, 1, 0, sd_mul(sd_scalar(kap), sd_twist_inv(epsp)), sd_twist_inv(epsp), s,

@@ -325,6 +325,11 @@ struct tm_ctx {
     bool half_links_f32_default = false;
     int cus = 256;  // compute units of the device (fewer in a partition)
     std::map<std::string, DevBuf> ws;
+    size_t ws_total = 0;  // bytes in ws
+    // bytes that ws may hold (0: no limit), TM_WORKSPACE_LIMIT in the environment
+    // when the context is created; an allocation beyond it fails as on a full device
+    size_t ws_limit = 0;
+    int ring_users = 0;  // solves that hold the ring of search directions
     std::string err;
     hipStream_t stream = nullptr;  // stream of the current loop-driver call
     // pinned host staging for scalar read-back
@@ -378,6 +383,8 @@ inline void account(tm_ctx *c, double bytes, double flops)
 }
 
 void *ws_get(tm_ctx *c, const std::string &name, size_t bytes);
+// bytes that an allocation may take now
+size_t ws_room(tm_ctx *c);
 void *host_stage(tm_ctx *c, size_t bytes);
 // Pinned staging slot `slot` (< kUpSlots) of `bytes` for an asynchronous
 // upload on stream s.  A slot's previous copy must have completed before it
@@ -483,6 +490,8 @@ void multi_dslash_launch(const MultiDslash &m, hipStream_t s);
 // right-hand sides: 462 us per iteration for m = 8, 729 (5.8 TB/s) for
 // m = 1, a mixed solve of 157 iterations 601 ms against 646.
 constexpr int kCgRing = 8;
+// The ring lives in the workspace "s_p_ring", which an allocation that would fail
+// takes back from a context between its solves (ws_get).
 // Ring of search directions: ring position q holds the direction of the q-th
 // iteration since x was last brought up to date.
 struct CgRing {
