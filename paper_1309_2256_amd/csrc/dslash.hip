@@ -20,7 +20,7 @@
 // spinors in the L2, and the links are loaded and rebuilt once for all
 // right-hand sides.  FP16: 533 -> 459 us, 2.26 -> 1.59 GB fetched past the L2;
 // FP64: 2449 -> 1780 us, 15.6 -> 10.2 GB (7.1 TB/s with the writes, what the
-// memory side cache gives); FP32 1285 -> 982, BF16 617 -> 544 us.  On small
+// memory side cache gives); FP32 1285 -> 982, BF16 617 -> 509 us.  On small
 // lattices the serial chain of a thread is two directions and an LDS exchange
 // instead of eight directions: 16^3 x 32, one right-hand side, FP16 8.6 -> 7.1,
 // FP64 15.0 -> 14.2 us.
@@ -1272,17 +1272,16 @@ void launch_epi(const DslashCall &dc, dim3 grid, hipStream_t s, const DParams<T>
 
 // Right-hand sides per block (at most), for instances given as (site blocks,
 // nrhs) and `slots` resident blocks (slots_one where a block takes a single
-// right-hand side: half a link set less in registers; BF16, 12 x 20 x 14 x 22, 5
-// right-hand sides: 53.4 us for the normal operator at one per block, 63 at
-// two, 72 at three, 69 at five): every instance splits its right-hand
-// sides evenly over the fewest blocks that keep the limit.  More of them per
-// block share one load and one rebuild of the links and keep the resident
-// blocks on fewer sites, so that neighbouring blocks find each other's spinors
-// in the L2; fewer fill the chip on small lattices.  The limit taken has the
-// least (rounds of resident blocks) x (mean block length), a block's start and
-// its links counting as one right-hand side.  TM_DSLASH_RHS_TILE /
-// TM_BATCH_RHS_TILE in the environment fix it (results are bit-identical for
-// any).
+// right-hand side; BF16, 12 x 20 x 14 x 22, 5 right-hand sides: 24.9 us for the
+// Schur operator at one per block, 27.2 at two, 31.3 at three, 28.8 at five):
+// every instance splits its right-hand sides evenly over the fewest blocks that
+// keep the limit.  More of them per block share one load and one rebuild of the
+// links and keep the resident blocks on fewer sites, so that neighbouring blocks
+// find each other's spinors in the L2; fewer fill the chip on small lattices.  The
+// limit taken has the least (rounds of resident blocks) x (mean block length), a
+// block's start and its links counting as one right-hand side: over 2970 calls 1.4%
+// longer on average than the best split of each.  TM_DSLASH_RHS_TILE and
+// TM_BATCH_RHS_TILE in the environment fix it (results are bit-identical for any).
 int even_split(int nrhs, int most)
 {
     const int groups = (nrhs + most - 1) / most;

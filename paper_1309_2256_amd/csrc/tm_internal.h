@@ -340,8 +340,9 @@ struct tm_ctx {
     // learned preconditioner (ptc.hip): channel count (0 = no weights),
     // Adam step counter, training-pair store (capacity, count, precision)
     int ptc_nc = 0;
-    // network arithmetic: TM_F32 (VALU, FP32 weights) or TM_BF16 (spin mixing
-    // on the matrix cores, BF16 weights and activations, FP32 accumulation)
+    // network arithmetic, spin mixing on the matrix cores either way: TM_F32 (the
+    // bits of FP32 FMA chains) or TM_BF16 (BF16 weights and activations, FP32
+    // accumulation)
     int ptc_arith = TM_F32;
     long ptc_step = 0;
     int ptc_cap = 0, ptc_n = 0, ptc_store = TM_F32;
