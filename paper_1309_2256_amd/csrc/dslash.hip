@@ -40,21 +40,6 @@ namespace {
 
 constexpr int kBlock = 256;  // four waves, one per direction mu
 constexpr int kSites = 64;   // output half-sites of a block
-// A single right-hand side per block has a form of its own (ONE: the links are
-// loaded where they are used, the summing waves keep a colour in registers) where
-// that is the faster one: 12-parameter links, whose rebuilt rows then take no
-// registers across the hops (BF16 Schur operator, one right-hand side, 24^3 x 48,
-// 48 -> 40 us), BF16 with binary16 links, and the exact FP64 links, for the
-// residuals (a truncated solve of one right-hand side on 32^3 x 16 2.40 ms
-// against 2.45).  Otherwise links with all their parameters, or with eight, are
-// better loaded ahead of the spinors' arithmetic, as for several: Schur operator,
-// 32^3 x 16, one right-hand side, FP32 93 -> 90 us, FP64 with 8 parameters 123 ->
-// 120, BF16 with FP32 links 74 -> 72.
-template <typename SS, typename LS>
-constexpr bool kOneForm = std::is_same<LS, L12>::value || std::is_same<LS, L12D>::value || std::is_same<LS, L12F>::value ||
-                          std::is_same<LS, double2>::value ||
-                          (std::is_same<SS, b2>::value && std::is_same<LS, h2>::value);
-
 // resident blocks per CU (and waves per SIMD) requested from the compiler:
 // bounded by the LDS exchange (24 KB per block in FP32, 48 KB in FP64, of
 // 160 KB) and by the registers (512 / waves per lane).  FP16 spinors, 32^3 x 64,
@@ -64,7 +49,7 @@ constexpr bool kOneForm = std::is_same<LS, L12>::value || std::is_same<LS, L12D>
 template <typename SS, typename LS, typename T, bool ONE = false>
 constexpr int waves_for()
 {
-    if (sizeof(T) == 8) return ONE ? 4 : 3;
+    if (sizeof(T) == 8) return ONE && !std::is_same<LS, L8D>::value ? 4 : 3;
     if (std::is_same<SS, float2>::value || std::is_same<LS, float2>::value) return 4;
     return std::is_same<SS, h2>::value || ONE ? 6 : 4;
 }
@@ -1246,10 +1231,27 @@ cx<T> cvt(cx<double> v)
 
 // The fused epilogues belong to the second halves of the Schur operator
 // (dag = 0 with the own-site term); the other forms store only.
+//
+// A single right-hand side per block has a form of its own (ONE: the links are
+// loaded where they are used, the summing waves keep a colour in registers and
+// load the fields of the own site ahead of the barrier) where that is the faster
+// one: the CG update and the residual, which read two of those fields (FP64 with
+// 8-parameter links, 32^3 x 64, one right-hand side: 361 us against 467);
+// 12-parameter links, whose rebuilt rows then take no registers across the hops
+// (BF16 Schur operator, 24^3 x 48, 40 us against 48); BF16 with binary16 links.
+// Otherwise links with all their parameters, or with eight, are better loaded ahead
+// of the spinors' arithmetic, as for several: Schur operator, 32^3 x 16, one
+// right-hand side, FP32 90 us against 93, FP64 with 8 parameters 120 against 123,
+// BF16 with FP32 links 72 against 74.
+template <typename SS, typename LS, int EPI>
+constexpr bool kOneForm = EPI == EPI_CG || EPI == EPI_RES || std::is_same<LS, L12>::value ||
+                          std::is_same<LS, L12D>::value || std::is_same<LS, L12F>::value ||
+                          (std::is_same<SS, b2>::value && std::is_same<LS, h2>::value);
+
 template <typename SS, typename LS, typename T, int DAG, int OWN, int EPI>
 void launch_form(dim3 grid, hipStream_t s, const DParams<T> &a)
 {
-    if constexpr (kOneForm<SS, LS>)
+    if constexpr (kOneForm<SS, LS, EPI>)
         if (a.rpb == 1) {
             hipLaunchKernelGGL((k_dslash<SS, LS, T, DAG, OWN, EPI, true>), grid, dim3(kBlock), 0, s, a);
             return;
@@ -1322,8 +1324,9 @@ long slots_of(const tm_ctx *c) { return (long)c->cus * waves_for<SS, LS, T>(); }
 template <typename SS, typename LS, typename T>
 long slots_of_one(const tm_ctx *c)
 {
-    if (sizeof(T) == 8 || !kOneForm<SS, LS>) return slots_of<SS, LS, T>(c);
-    return (long)c->cus * waves_for<SS, LS, T, true>() - (std::is_same<LS, h2>::value ? c->cus / 2 : 0);
+    if (sizeof(T) == 8) return slots_of<SS, LS, T>(c);
+    const bool full = std::is_same<SS, b2>::value && std::is_same<LS, h2>::value;
+    return (long)c->cus * waves_for<SS, LS, T, true>() - (full ? c->cus / 2 : 0);
 }
 
 template <typename SS, typename LS, typename T>
