@@ -1282,14 +1282,15 @@ void launch_epi(const DslashCall &dc, dim3 grid, hipStream_t s, const DParams<T>
 // find each other's spinors in the L2; fewer fill the chip on small lattices.  The
 // limit taken has the least (rounds of resident blocks) x (mean block length), a
 // block's start and its links counting as one right-hand side: over 2970 calls 1.4%
-// longer on average than the best split of each.  TM_DSLASH_RHS_TILE and
-// TM_BATCH_RHS_TILE in the environment fix it (results are bit-identical for any).
+// longer on average than the best split of each.  equal: only splits into blocks of
+// one length.  TM_DSLASH_RHS_TILE and TM_BATCH_RHS_TILE in the environment fix the
+// limit (results are bit-identical for any).
 int even_split(int nrhs, int most)
 {
     const int groups = (nrhs + most - 1) / most;
     return (nrhs + groups - 1) / groups;
 }
-int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long slots_one)
+int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long slots_one, bool equal = false)
 {
     int top = 1, best = 1;
     for (const auto &[nb, nrhs] : inst) top = std::max(top, nrhs);
@@ -1297,12 +1298,15 @@ int rhs_per_block(const std::vector<std::pair<int, int>> &inst, long slots, long
     for (int lim = 1; lim <= top; lim++) {
         double blocks = 0, length = 0;
         int longest = 0;
+        bool skip = false;
         for (const auto &[nb, nrhs] : inst) {
             const int rpb = even_split(nrhs, lim), g = (nrhs + rpb - 1) / rpb;
+            skip |= equal && nrhs % rpb != 0;
             blocks += (double)nb * g;
             length += (double)nb * (g + nrhs);
             longest = std::max(longest, 1 + rpb);
         }
+        if (skip) continue;
         const double cost = std::max((double)longest, std::ceil(blocks / (lim == 1 ? slots_one : slots)) * length / blocks);
         if (lim == 1 || cost < least) {
             least = cost;
@@ -1371,7 +1375,14 @@ DParams<T> fill_params(tm_ctx *c, const DslashCall &dc, int most)
 template <typename SS, typename LS, typename T>
 void launch_t(tm_ctx *c, const DslashCall &dc, hipStream_t s)
 {
-    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(c), slots_of_one<SS, LS, T>(c));
+    // FP64, three or five right-hand sides: blocks of one length.  Blocks of two and
+    // of one fill the chip unevenly (12^3 x 24, 3 right-hand sides, 18 / 12
+    // parameters: Schur operator 29.0 / 26.2 us against 24.0 / 22.2 at one per block;
+    // 20 x 16 x 18 x 24, 82.8 / 76.1 against 78.0 / 67.6 at three).  The 8-parameter
+    // links, the dearest to rebuild, are shared all the same (12^3 x 24, 5: 38.3
+    // against 41.8), and from seven on neither side is ahead throughout.
+    const bool equal = sizeof(T) == 8 && !std::is_same<LS, L8D>::value && dc.nrhs <= 5;
+    int rpb = rhs_per_block({{dslash_site_blocks(c), dc.nrhs}}, slots_of<SS, LS, T>(c), slots_of_one<SS, LS, T>(c), equal);
     if (const char *e = getenv("TM_DSLASH_RHS_TILE"))
         if (atoi(e) > 0) rpb = atoi(e);
     const DParams<T> a = fill_params<SS, LS, T>(c, dc, rpb);
